@@ -251,18 +251,22 @@ int sse_state_get_edge_variant(const sse_state *s, int *variant);
  * mesh is cut into patches of a few hundred cells, and one workgroup carries
  * its patch, extended by the halo rings the substep's evaluations read,
  * through all evaluations of the substep in LDS.  2: one cooperative launch
- * per loop (persistent): every patch has its own workgroup for all M
- * substeps, keeps its stencil tables, frozen forcing and F^zeta sums in
- * registers, and waits at a grid barrier between substeps; available when
- * the device holds a workgroup for every patch at once (small meshes: a few
- * hundred patches).  A barrier wait is bounded: if one runs out, the step
- * call reports SSE_EDEVICE and the state is not valid.  Steps captured in a
- * HIP graph, and batch members, run variant 1 in place of 2.  The default is
- * 1 when the mesh has such patches (sse_mesh_create builds them when every
- * patch's halo region fits a workgroup and every reconstruction stencil stays
- * within the two cells of its edge) and they fit the device's LDS, else 0.
- * SSE_EINVAL for 1 or 2 where they do not apply.  Each member of a batch uses
- * its own variant. */
+ * per loop: every patch has its own workgroup for all M substeps and keeps
+ * its tables, frozen forcing and F^zeta sums on chip; between substeps the
+ * patches exchange their halos and each waits for its neighbours (on meshes
+ * whose reconstruction weights do not factor by cell: a grid barrier);
+ * available when the device holds a workgroup for every patch at once.  A
+ * wait is bounded: if one runs out, the step call reports SSE_EDEVICE and the
+ * state is not valid.  A stream under graph capture runs variant 1 in place of
+ * 2; a state asked to replay its steps as a graph runs them as they are where
+ * 2 is in use (a step then has few launches); a batch takes one launch per
+ * loop when the device holds the patches of all its members at once and none
+ * was set to another variant by its caller.  The default is 2 where it is
+ * available for factored weights and M repays the launch, else 1 when the
+ * mesh has patches (sse_mesh_create builds them when every patch's halo region
+ * fits a workgroup and every reconstruction stencil stays within the two cells
+ * of its edge) and they fit the device's LDS, else 0.  SSE_EINVAL for 1 or 2
+ * where they do not apply. */
 int sse_state_set_bt_variant(sse_state *s, int variant);
 int sse_state_get_bt_variant(const sse_state *s, int *variant);
 
@@ -389,9 +393,10 @@ int sse_debug_thickness_stage(sse_state *s, const double *h_in, const double *u,
  * but on DEVICE arrays in the caller's numbering: inputs ubar [E], zeta [C],
  * G [E]; outputs ubar1 [E], zeta1 [C], Fzeta [E] (outputs may alias inputs:
  * every input is read before any output is written).  The state supplies the
- * mesh, gravity, the barotropic kernel variant (variant 2, the persistent
- * loop kernel, runs as variant 1 here) and the stream; its own fields and
- * workspace are not touched.  The loop's stages live in a static
+ * mesh, gravity, the barotropic kernel variant (variant 2, one launch per
+ * loop, runs as variant 1 while the stream is captured into a graph, or where
+ * the mesh's reconstruction weights do not factor by cell) and the stream; its
+ * own fields and workspace are not touched.  The loop's stages live in a static
  * device array of 64 MiB per device, reserved when the library's code is
  * loaded on that device and held until the process ends; its address is
  * resolved by sse_state_create.  The call allocates nothing, enqueues its

@@ -37,11 +37,17 @@ using namespace sse;
 // address reaches kernels.
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
 static __device__ __align__(256) double scratch[kStaticScratchBytes / sizeof(double)];
+// Substep counters and error word of the resident loop in that entry point
+// (the largest mesh the scratch takes has fewer than 2^19 cells; see
+// done_patches); zero when the code is loaded.
+constexpr size_t kStaticCounters = ((size_t(1) << 19) / 32 + 32) * kDoneStride;
+static __device__ __align__(256) unsigned long long scratch_done[kStaticCounters + kDoneStride];
 
 namespace {
 
 constexpr int kMaxDevices = 64;
-std::atomic<void *> g_scratch[kMaxDevices];
+std::atomic<void *> g_scratch[kMaxDevices], g_scratch_done[kMaxDevices];
+std::atomic<unsigned long long> g_scratch_count[kMaxDevices];  // at least every value its counters hold
 
 // Resolves (once per device, with that device current) the address of this
 // device's scratch array; nullptr if the runtime cannot give it.
@@ -49,11 +55,13 @@ void *scratch_address(int dev) {
     if (dev < 0 || dev >= kMaxDevices) return nullptr;
     void *p = g_scratch[dev].load(std::memory_order_acquire);
     if (p) return p;
-    void *q = nullptr;
-    if (hipGetSymbolAddress(&q, HIP_SYMBOL(scratch)) != hipSuccess) {
+    void *q = nullptr, *c = nullptr;
+    if (hipGetSymbolAddress(&q, HIP_SYMBOL(scratch)) != hipSuccess ||
+        hipGetSymbolAddress(&c, HIP_SYMBOL(scratch_done)) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
+    g_scratch_done[dev].store(c, std::memory_order_release);
     g_scratch[dev].store(q, std::memory_order_release);
     return q;
 }
@@ -78,6 +86,8 @@ struct Work {
                                              // of the first stage and of the n+1/2 stage
     void *ubar_r;                            // R [E]: the barotropic velocity an edge pass adds or
                                              // subtracts, rounded to R (mixed precision)
+    unsigned long long *bt_done;             // [done_patches(C)][kDoneStride] substep counters of the
+                                             // resident barotropic loop
 };
 
 constexpr int kR3E = 3, kR3C = 2, kR3V = 1, kR2E = 4, kR2C = 4;  // arrays of type R
@@ -89,6 +99,11 @@ size_t real_size(int precision) { return precision == SSE_FP64 ? sizeof(double) 
 
 // Bytes of the barotropic loop's real type: FP32 only in SSE_MIXED.
 size_t bt_size(int precision) { return precision == SSE_MIXED ? sizeof(float) : sizeof(double); }
+
+// Patches the workspace holds substep counters for (meshes cut into more do
+// not take the resident loop).
+int done_patches(int C) { return C / 32 + 32; }
+size_t done_bytes(int C) { return align_up((size_t)done_patches(C) * kDoneStride * 8); }
 
 size_t workspace_bytes(int C, int E, int V, int L, size_t rs, size_t bs, int hdiff, int tracer) {
     size_t b = 0;
@@ -105,6 +120,7 @@ size_t workspace_bytes(int C, int E, int V, int L, size_t rs, size_t bs, int hdi
     b += kD2E * align_up((size_t)E * 8);
     b += kD2C * align_up((size_t)C * 8);
     b += kAlign;  // flag
+    b += done_bytes(C);
     return b;
 }
 
@@ -148,6 +164,7 @@ Work carve(void *buf, int C, int E, int V, int L, size_t rs, size_t bs, int hdif
         w.Th = static_cast<double *>(take((size_t)C * L * 8));
     }
     w.ubar_r = take((size_t)E * rs);
+    w.bt_done = static_cast<unsigned long long *>(take(done_bytes(C)));
     return w;
 }
 
@@ -218,7 +235,7 @@ bool all_finite(const double *x, size_t n) {
 // key (seq = launch site in step order; j = substep evaluation inside a
 // barotropic loop), so that the same launch of every member can be merged
 // into one batched launch.
-enum class Kind : int { FE_CELL, FE_VERTEX, FE_EDGE, BT_EVAL, BT_TILE, THICK, THICK_ISO, RECON, ASSEMBLE, CONV_DF, CONV_FD, LAP, DIV, TRACER };
+enum class Kind : int { FE_CELL, FE_VERTEX, FE_EDGE, BT_EVAL, BT_LOOP, BT_TILE, THICK, THICK_ISO, RECON, ASSEMBLE, CONV_DF, CONV_FD, LAP, DIV, TRACER };
 
 struct RecEntry {
     Kind kind;
@@ -256,8 +273,11 @@ struct sse_state {
                              // 2: one cooperative launch per loop, one workgroup per patch
     int bt_capacity[2] = {0, 0};  // workgroups of the persistent loop kernel the device holds at once
                                   // (SSPRK2, SSPRK3 forms)
+    bool bt_auto = true;          // the variant is the default, not the caller's
+    int bt_tight[2] = {0, 0};     // the form of that kernel
     bool capturing = false;  // a HIP graph capture of the step is in progress
     hipError_t launch_error = hipSuccess;  // the last failed cooperative launch, reported by the step call
+    unsigned long long bt_count = 0;  // at least every value the counters w.bt_done hold
     unsigned barrier_spins = kBarrierSpins;  // polls before a barrier of the persistent loop gives up
     size_t lds_max = 0;      // LDS bytes per workgroup on the state's device
     Recorder *rec = nullptr; // non-null while a batch records this state's step
@@ -337,9 +357,28 @@ bool bt_tiles_fit(const sse_state *s) {
 
 // The persistent loop kernel can give every patch its own workgroup at once
 // (a cooperative launch of the XCD-padded patch count) for this scheme.
+bool resident_able(const DevBtTiles &t, int C) { return t.fact && t.resident && t.nP <= done_patches(C); }
 bool bt_loop_fits(const sse_state *s, int scheme) {
-    const int nP = s->mesh->bt.nP;
+    const DevBtTiles &t = s->mesh->bt;
+    if (t.fact && !resident_able(t, s->mesh->C)) return false;
+    const int nP = t.fact ? t.nA : t.nP;
     return bt_tiles_fit(s) && kXcd * ((nP + kXcd - 1) / kXcd) <= s->bt_capacity[scheme == SSE_SCHEME_SSPRK3 ? 1 : 0];
+}
+
+// Fewest substeps for which a loop is worth a cooperative launch, which costs
+// about 17 us more than an ordinary one (a mesh of one patch takes an ordinary
+// one); a substep of it takes 2-5 us less than a launch of its own.  A loop of
+// 7 SSPRK2 substeps on 4,462 cells came out even (0.99x a whole step).
+bool resident_pays(const DevBtTiles &t, int M) { return M >= (t.nA == 1 ? 2 : 10); }
+
+// The stream is being captured into a graph, which takes no cooperative launch.
+bool stream_capturing(hipStream_t st) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;  // e.g. the legacy stream while another one captures: stay with plain launches
+    }
+    return c != hipStreamCaptureStatusNone;
 }
 
 // ---- building blocks -------------------------------------------------------
@@ -457,9 +496,14 @@ void convert(sse_state *s, const Tin *src, Tout *dst, size_t n) {
 // before widening (ua, za, uo, zo).
 struct BtBufs {
     void *u1, *uh, *z1, *zh, *ua, *za, *uo, *zo;
+    unsigned long long *done;   // substep counters and error word of the resident loop
+    int *err;
+    std::atomic<unsigned long long> *count;  // the counters' upper bound (null: the state's)
 };
 
-BtBufs bt_bufs(const Work &w) { return {w.bt_u1, w.bt_uh, w.bt_z1, w.bt_zh, w.bt_ua, w.bt_za, w.bt_uo, w.bt_zo}; }
+BtBufs bt_bufs(const Work &w) {
+    return {w.bt_u1, w.bt_uh, w.bt_z1, w.bt_zh, w.bt_ua, w.bt_za, w.bt_uo, w.bt_zo, w.bt_done, w.flag + 32, nullptr};
+}
 
 // Algorithm 3 (scheme 2) / Algorithm 4 (scheme 3): M substeps of dt / M with
 // G frozen, accumulating F^zeta in FP64.  The inputs are not modified.  In
@@ -487,18 +531,45 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
         oz = rp<R>(w.zo);
     }
     R *u1 = rp<R>(w.u1), *uh = rp<R>(w.uh), *z1 = rp<R>(w.z1), *zh = rp<R>(w.zh);
-    if (s->bt_variant == 2 && !s->rec && !s->capturing && bt_loop_fits(s, scheme)) {
+    const DevBtTiles &tiles = s->rec ? s->mesh->bt_batch : s->mesh->bt;
+    BTTileArgs<R> base{};
+    base.t = tiles;
+    base.G = G;
+    base.F = F;
+    base.zeroF = 1;
+    base.tau = dt / M;
+    base.g = s->p.gravity;
+    base.w1 = scheme == SSE_SCHEME_SSPRK3 ? 1.0 / (6.0 * M) : 1.0 / (2.0 * M);
+    base.w3 = scheme == SSE_SCHEME_SSPRK3 ? 2.0 / (3.0 * M) : 0.0;
+    const BtResident<R> res{base, M, iu, iz, u1, uh, z1, zh, ou, oz, w.done, w.err,
+                            w.count ? kBarrierSpins : s->barrier_spins};
+    const bool resident = s->rec ? (s->bt_variant == 2 || (s->bt_auto && s->bt_variant == 1)) && resident_able(tiles, m.C)
+                                 : s->bt_variant == 2 && tiles.fact && !s->capturing && bt_loop_fits(s, scheme) &&
+                                       !stream_capturing(s->stream);
+    if (s->rec && resident) {
+        // a batch takes this launch, or the substeps recorded after it
+        record(s, Kind::BT_LOOP, res, 1, false, tiles.nA);
+    } else if (s->rec) {
+        s->rec->seq++;
+    } else if (resident) {
+        {
+            ProfScope ps(s, SSE_PROF_BT_EVAL);
+            const unsigned long long from = w.count ? w.count->fetch_add((unsigned long long)M) : s->bt_count;
+            const hipError_t e = launch_bt_resident<R>(res, scheme, s->bt_tight[scheme == SSE_SCHEME_SSPRK3 ? 1 : 0], from, s->stream);
+            if (!w.count) s->bt_count += (unsigned long long)M;
+            if (e != hipSuccess) s->launch_error = e;
+        }
+        if constexpr (!std::is_same<R, double>::value) {
+            convert<R, double>(s, ou, out_u, m.E);
+            convert<R, double>(s, oz, out_z, m.C);
+        }
+        return;
+    }
+    if (s->bt_variant == 2 && !tiles.fact && !s->rec && !s->capturing && !w.count && bt_loop_fits(s, scheme) &&
+        !stream_capturing(s->stream)) {
         // one cooperative launch: every patch in its own workgroup for all M
         // substeps, grid barriers between them
-        BTTileArgs<R> a{};
-        a.t = s->mesh->bt;
-        a.G = G;
-        a.F = F;
-        a.zeroF = 1;
-        a.tau = dt / M;
-        a.g = s->p.gravity;
-        a.w1 = scheme == SSE_SCHEME_SSPRK3 ? 1.0 / (6.0 * M) : 1.0 / (2.0 * M);
-        a.w3 = scheme == SSE_SCHEME_SSPRK3 ? 2.0 / (3.0 * M) : 0.0;
+        const BTTileArgs<R> &a = base;
         BtLoop<R> l{};
         l.M = M;
         l.u_in = iu;
@@ -528,14 +599,7 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
         // one launch per substep; outputs alternate between the loop's
         // output and a scratch pair so that no launch reads what another
         // workgroup of the same launch writes, ending in the output
-        BTTileArgs<R> a{};
-        a.t = s->mesh->bt;
-        a.G = G;
-        a.F = F;
-        a.tau = dt / M;
-        a.g = s->p.gravity;
-        a.w1 = scheme == SSE_SCHEME_SSPRK3 ? 1.0 / (6.0 * M) : 1.0 / (2.0 * M);
-        a.w3 = scheme == SSE_SCHEME_SSPRK3 ? 2.0 / (3.0 * M) : 0.0;
+        BTTileArgs<R> a = base;
         const R *pu = iu, *pz = iz;
         if (s->rec) s->rec->loop_seq = s->rec->seq++;
         for (int sub = 0; sub < M; ++sub) {
@@ -547,7 +611,7 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
             a.zo = tz;
             a.zeroF = sub == 0;
             if (s->rec) {
-                record(s, Kind::BT_TILE, a, 1, false, a.t.nP, sub, a.t.ks);
+                record(s, Kind::BT_TILE, a, 1, false, a.t.nP, sub, a.t.fact ? kFactVar : a.t.ks);
                 s->rec->entries.back().lds = std::is_same<R, double>::value ? a.t.lds_d : a.t.lds_f;
             } else {
                 ProfScope ps(s, SSE_PROF_BT_EVAL);
@@ -566,6 +630,8 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
     const int nblk = bt_blocks(m.E, m.C, s->geom);
     BTEvalArgs<R> a{};
     a.m = m;
+    a.fk = s->mesh->bt.g;
+    a.fact = s->mesh->bt.fact;
     a.G = G;
     a.F = F;
     a.tau = dt / M;
@@ -863,6 +929,68 @@ int download_real(const sse_state *s, double *dst, const void *src, size_t n) {
 // ===========================================================================
 // Mesh
 // ===========================================================================
+namespace {
+
+std::vector<float> to_float(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
+
+// Uploads one set of patches in the factored form; the tables per mesh entity
+// are shared with `share` if that is given.
+int upload_fact(DevBtTiles &b, const HostBtTiles &h, const HostMeshTables &t, const DevFact *share, char *base,
+                size_t cursor, hipStream_t s) {
+    hipError_t err = hipSuccess;
+    // one table; synchronous, so that a converted copy may go
+    auto put = [&](const auto &v) {
+        using T = typename std::decay_t<decltype(v)>::value_type;
+        char *dst = base + cursor;
+        if (!v.empty() && err == hipSuccess) {
+            err = hipMemcpyAsync(dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
+            if (err == hipSuccess) err = hipStreamSynchronize(s);
+        }
+        cursor += align_up(v.size() * sizeof(T));
+        return reinterpret_cast<const T *>(dst);
+    };
+    b.patch = put(h.patch);
+    b.eid = put(h.eid);
+    b.cid = put(h.cid);
+    b.cH = put(h.cH);
+    b.order = put(h.order);
+    b.nbr = put(h.nbr);
+    b.fec = put(h.fec);
+    b.fcen = put(h.fcen);
+    b.cflag = put(h.cflag);
+    b.elh = put(h.elh);
+    b.efh = put(h.efh);
+    b.fidc = put(h.fidc);
+    b.cS = put(h.cS);
+    b.cia = put(h.cia);
+    b.elh_f = put(to_float(h.elh));
+    b.efh_f = put(to_float(h.efh));
+    b.fidc_f = put(to_float(h.fidc));
+    b.cS_f = put(to_float(h.cS));
+    b.cia_f = put(to_float(h.cia));
+    if (share) {
+        b.g = *share;
+    } else {
+        b.g.lh = put(t.flh);
+        b.g.fh = put(t.ffh);
+        b.g.S = put(t.fS);
+        b.g.ia = put(t.fia);
+        b.g.lh_f = put(to_float(t.flh));
+        b.g.fh_f = put(to_float(t.ffh));
+        b.g.S_f = put(to_float(t.fS));
+        b.g.ia_f = put(to_float(t.fia));
+    }
+    if (err != hipSuccess) return hip_fail(err, "upload of the barotropic tables");
+    b.fact = 1;
+    b.nP = h.nP;
+    b.nA = h.nA;
+    b.resident = h.resident;
+    b.nt = h.nt;
+    return SSE_OK;
+}
+
+}  // namespace
+
 extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t bytes, void *stream, sse_mesh **out) {
     if (!out) { set_error("out is NULL"); return SSE_EINVAL; }
     *out = nullptr;
@@ -888,13 +1016,15 @@ extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t byt
     MeshLayout lay = mesh_layout(d->n_cells, d->n_edges, d->n_vertices);
     size_t need = lay.total;
     for (int q = 0; q < kTileVariants; ++q) need += tiles_bytes(d, kTileSizes[q]);
-    need += bt_tiles_bytes(d0);
+    const size_t bt_space = bt_tiles_bytes(d0);
+    need += bt_space;
     need += wpair_f_bytes(d);
     if (!dev_buf || bytes < need) { set_error("mesh device buffer too small"); return SSE_ENOMEM; }
     if (reinterpret_cast<uintptr_t>(dev_buf) % kAlign) { set_error("mesh device buffer must be 256-byte aligned"); return SSE_EINVAL; }
     HostMeshTables t;
     if (canonical) t.chain.swap(chain);
     build_tables(d, t);
+    factor_weights(d, t);
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *base = static_cast<char *>(dev_buf);
     const void *src[] = {t.cell_edges.data(), t.cell_nbrs.data(), t.cell_nedges.data(), t.cell_div.data(),
@@ -975,16 +1105,35 @@ extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t byt
         m->tiles[q].T = 0;
         cursor += tiles_bytes(d, kTileSizes[q]);
     }
+    const size_t bt_off = cursor;
     // Patches of the tiled barotropic substeps (partitioned in the caller's
     // numbering, the same partition the device-bytes query sizes).
     {
-        std::vector<int32_t> pid0, pid;
-        int nP = 0;
+        BtPartition coarse, fine;
+        bt_cached_partitions(d0, coarse, fine);
+        auto internal = [&](const BtPartition &q) {
+            std::vector<int32_t> pid(d->n_cells);
+            for (int i = 0; i < d->n_cells; ++i) pid[i] = q.pid[ord.cell_old[i]];
+            return pid;
+        };
         HostBtTiles hb;
-        if (bt_cached_partition(d0, pid0, nP)) {
-            pid.resize(d->n_cells);
-            for (int i = 0; i < d->n_cells; ++i) pid[i] = pid0[ord.cell_old[i]];
-            if (build_bt_tiles(d, pid, nP, &t, hb)) {
+        if (coarse.ok) {
+            const std::vector<int32_t> pid = internal(coarse);
+            const int nP = coarse.nP;
+            if (build_fact_tiles(d, pid, nP, t, kBtThreads, hb)) {
+                int rc_up = upload_fact(m->bt, hb, t, nullptr, base, cursor, s);
+                m->bt_batch = m->bt;
+                HostBtTiles hf;
+                if (rc_up == SSE_OK && fine.ok && build_fact_tiles(d, internal(fine), fine.nP, t, kFactSmall, hf)) {
+                    DevBtTiles b;
+                    rc_up = upload_fact(b, hf, t, &m->bt.g, base, bt_off + coarse.bytes, s);
+                    m->bt = b;
+                }
+                if (rc_up != SSE_OK) {
+                    delete m;
+                    return rc_up;
+                }
+            } else if (build_bt_tiles(d, pid, nP, &t, hb)) {
                 hipError_t put_err = hipSuccess;
                 auto put = [&](const void *src, size_t n) -> const void * {
                     char *dst = base + cursor;
@@ -1015,9 +1164,12 @@ extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t byt
                 b.ks = hb.ks;
                 b.lds_d = hb.lds_d;
                 b.lds_f = hb.lds_f;
+                m->bt_batch = b;
             }
         }
     }
+    // the space the size query reserved for the patches, whichever form they took
+    cursor = bt_off + bt_space;
     // FP32 weight pairs of the edge pass in mixed precision, last in the image
     if (cursor + wpair_f_bytes(d) > need) {
         delete m;
@@ -1138,11 +1290,22 @@ extern "C" int sse_state_create(const sse_mesh *m, const sse_params *p, void *de
     set_tiled_lds_limit((size_t)lds_max);
     s->lds_max = (size_t)lds_max;
     s->edge_variant = -1;
-    s->bt_variant = bt_tiles_fit(s) ? 1 : 0;
-    for (int q = 0; q < 2; ++q)
-        s->bt_capacity[q] = !bt_tiles_fit(s) ? 0
-                            : s->bt64 ? bt_loop_capacity<double>(s->mesh->bt, 2 + q)
-                                      : bt_loop_capacity<float>(s->mesh->bt, 2 + q);
+    for (int q = 0; q < 2 && bt_tiles_fit(s); ++q)
+        for (int tight = 0; tight < kResidentForms; ++tight) {
+            s->bt_capacity[q] = s->bt64 ? bt_loop_capacity<double>(s->mesh->bt, 2 + q, tight)
+                                        : bt_loop_capacity<float>(s->mesh->bt, 2 + q, tight);
+            s->bt_tight[q] = tight;
+            if (!s->mesh->bt.fact || bt_loop_fits(s, 2 + q)) break;
+        }
+    // the resident loop where the device holds all patches at once, else one launch per substep
+    s->bt_variant = !bt_tiles_fit(s)                                                                           ? 0
+                    : s->mesh->bt.fact && bt_loop_fits(s, s->p.scheme) && resident_pays(s->mesh->bt, s->p.substeps) ? 2
+                                                                                                                     : 1;
+    if (hipMemsetAsync(s->w.bt_done, 0, done_bytes(m->C), s->stream) != hipSuccess ||
+        hipMemsetAsync(s->w.flag, 0, kAlign, s->stream) != hipSuccess) {
+        delete s;
+        return hip_fail(hipGetLastError(), "clearing the substep counters");
+    }
     *out = s;
     return SSE_OK;
 }
@@ -1159,6 +1322,7 @@ extern "C" int sse_state_set_bt_variant(sse_state *s, int variant) {
         return SSE_EINVAL;
     }
     s->bt_variant = variant;
+    s->bt_auto = false;
     if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
     s->graph_exec = nullptr;
     return SSE_OK;
@@ -1346,7 +1510,11 @@ extern "C" int sse_step_async(sse_state *s, int32_t n) {
     if (!s->initialized) { set_error("state not initialised"); return SSE_ESTATE; }
     if (s->p.tracer && !s->tracer_set) { set_error("tracer runs need sse_state_set_tracer before stepping"); return SSE_ESTATE; }
     if (n < 0) { set_error("n must be >= 0"); return SSE_EINVAL; }
-    if (s->use_graph) {
+    // a step with the resident loop is few launches, cooperative ones among
+    // them, which a graph does not take: it runs as it is (0.43 ms per 64 x 64
+    // x 20 step against 0.48 as a graph with a launch per substep)
+    const bool resident = s->bt_variant == 2 && s->mesh->bt.fact && bt_loop_fits(s, s->p.scheme);
+    if (s->use_graph && !(resident && !stream_capturing(s->stream))) {
         if (!s->graph_exec) {
             // the captured step uses the per-substep barotropic kernel: the
             // persistent one is a cooperative launch
@@ -1595,18 +1763,19 @@ extern "C" int sse_barotropic_substep_noalloc(sse_state *s, int32_t scheme, int3
     launch_permute(ubar, dm.edge_old, iu, (int)E, false, s->geom, st);
     launch_permute(zeta, dm.cell_old, iz, (int)C, false, s->geom, st);
     launch_permute(G, dm.edge_old, iG, (int)E, false, s->geom, st);
-    const bool prof = s->prof, capturing = s->capturing;
+    const bool prof = s->prof;
     s->prof = false;  // no per-class events: their bookkeeping would grow host vectors
-    // callers may capture this call in a graph, and it must leave the state's
-    // workspace alone: never the persistent (cooperative) loop kernel, whose
-    // barrier words live in the workspace
-    s->capturing = true;
+    // the state's workspace is left alone: the resident loop takes the static
+    // counters (and, captured in a graph, one launch per substep runs in its
+    // place)
+    b.done = static_cast<unsigned long long *>(g_scratch_done[dev].load(std::memory_order_acquire));
+    b.err = reinterpret_cast<int *>(b.done + kStaticCounters);
+    b.count = &g_scratch_count[dev];
     if (s->bt64)
         bt_loop<double>(s, scheme, M, dt, iu, iz, iG, ou, oz, oF, b);
     else
         bt_loop<float>(s, scheme, M, dt, iu, iz, iG, ou, oz, oF, b);
     s->prof = prof;
-    s->capturing = capturing;
     if (int rc = take_launch_error(s)) return rc;
     launch_permute(ou, dm.edge_old, ubar1, (int)E, true, s->geom, st);
     launch_permute(oz, dm.cell_old, zeta1, (int)C, true, s->geom, st);
@@ -1666,6 +1835,7 @@ struct BatchOp {
     int blocks;
     size_t args_off, table_off;
     size_t lds;
+    int substeps;   // BT_LOOP: the most of any member
 };
 
 }  // namespace
@@ -1682,6 +1852,9 @@ struct sse_batch {
     bool use_graph = false;
     hipGraphExec_t graph_exec = nullptr;
     size_t launches_per_step = 0;
+    bool resident = false;        // the loops run as resident loops (outside graph capture),
+    int tight = 0;                // in this form
+    hipError_t launch_error = hipSuccess;
 };
 
 namespace {
@@ -1694,6 +1867,13 @@ void batch_invalidate(sse_batch *b) {
     b->prog.clear();
     b->image.clear();
     b->dev = nullptr;
+}
+
+// Whether an op of the program runs: the resident loop, or the substep
+// launches recorded beside it.
+bool batch_runs(const BatchOp &op, bool resident) {
+    if (op.kind == Kind::BT_LOOP) return resident;
+    return !(resident && op.kind == Kind::BT_TILE && (op.var & kFactVar));
 }
 
 // Record one step of every member and merge equal launches into batched ones.
@@ -1734,7 +1914,7 @@ int batch_record(sse_batch *b) {
     size_t off = 0;
     for (auto &kv : groups) {
         auto &v = kv.second;
-        BatchOp op{v[0].second.kind, v[0].second.nk, v[0].second.var, v[0].second.add, 0, 0, 0, 0};
+        BatchOp op{v[0].second.kind, v[0].second.nk, v[0].second.var, v[0].second.add, 0, 0, 0, 0, 0};
         const size_t asz = v[0].second.args.size();
         std::vector<int2> table;
         for (size_t q = 0; q < v.size(); ++q) {
@@ -1744,6 +1924,7 @@ int batch_record(sse_batch *b) {
             }
             for (int blk = 0; blk < v[q].second.blocks; ++blk) table.push_back(int2{(int)q, blk});
             op.lds = std::max(op.lds, v[q].second.lds);
+            op.substeps = std::max(op.substeps, b->members[v[q].first]->p.substeps);
         }
         op.blocks = (int)table.size();
         op.args_off = off;
@@ -1756,7 +1937,27 @@ int batch_record(sse_batch *b) {
         std::memcpy(b->image.data() + op.table_off, table.data(), table.size() * sizeof(int2));
         b->prog.push_back(op);
     }
-    b->launches_per_step = b->prog.size();
+    // the resident loop in the place of the substep launches: when it can take
+    // every member with factored weights, all their patches at once
+    bool able = true, pays = false;
+    int blocks = 0;
+    for (const sse_state *s : b->members) {
+        const DevBtTiles &t = s->mesh->bt_batch;
+        if (s->bt_variant == 0 || !t.fact) continue;
+        able = able && (s->bt_variant == 2 || s->bt_auto) && resident_able(t, s->mesh->C);
+        pays = pays || resident_pays(t, s->p.substeps);
+        blocks += t.nA;
+    }
+    b->resident = false;
+    for (int tight = 0; tight < kResidentForms; ++tight) {
+        const int cap = s0->bt64 ? bt_resident_batch_capacity<double>(s0->p.scheme, tight)
+                                 : bt_resident_batch_capacity<float>(s0->p.scheme, tight);
+        b->tight = tight;
+        b->resident = able && pays && kXcd * ((blocks + kXcd - 1) / kXcd) <= cap;
+        if (b->resident) break;
+    }
+    b->launches_per_step = 0;
+    for (const BatchOp &op : b->prog) b->launches_per_step += batch_runs(op, b->resident);
     b->recorded = true;
     return SSE_OK;
 }
@@ -1769,12 +1970,24 @@ BatchLaunch<A> bl(const sse_batch *b, const BatchOp &op) {
 }
 
 template <typename R>
-void batch_enqueue(const sse_batch *b) {
+void batch_enqueue(sse_batch *b, bool resident) {
     const Geom &g = b->geom;
     hipStream_t st = b->stream;
     const bool bt64 = b->members[0]->bt64;  // members share their precision mode
     for (const BatchOp &op : b->prog) {
+        if (!batch_runs(op, resident)) continue;
         switch (op.kind) {
+            case Kind::BT_LOOP: {
+                unsigned long long from = 0;
+                for (const sse_state *s : b->members) from = std::max(from, s->bt_count);
+                const int scheme = b->members[0]->p.scheme;
+                hipError_t e;
+                if (bt64) e = launch_bt_resident_batch<double>(bl<BtResident<double>>(b, op), scheme, b->tight, from, st);
+                else e = launch_bt_resident_batch<float>(bl<BtResident<float>>(b, op), scheme, b->tight, from, st);
+                for (sse_state *s : b->members) s->bt_count = from + (unsigned long long)op.substeps;
+                if (e != hipSuccess) b->launch_error = e;
+                break;
+            }
             case Kind::FE_CELL: launch_fe_cell_batch<R>(bl<FECellArgs<R>>(b, op), op.nk, op.add, g, st); break;
             case Kind::FE_VERTEX: launch_fe_vertex_batch<R>(bl<FEVertexArgs<R>>(b, op), op.nk, op.add, g, st); break;
             case Kind::FE_EDGE: launch_fe_edge_batch<R>(bl<FEEdgeArgs<R>>(b, op), op.nk, op.add, op.var, g, st); break;
@@ -1803,11 +2016,11 @@ void batch_enqueue(const sse_batch *b) {
     }
 }
 
-void batch_enqueue_any(const sse_batch *b) {
+void batch_enqueue_any(sse_batch *b, bool resident) {
     if (b->members[0]->rs == 4)
-        batch_enqueue<float>(b);
+        batch_enqueue<float>(b, resident);
     else
-        batch_enqueue<double>(b);
+        batch_enqueue<double>(b, resident);
 }
 
 }  // namespace
@@ -1916,15 +2129,19 @@ extern "C" int sse_batch_step_async(sse_batch *b, int32_t n) {
     if (!b) { set_error("NULL batch"); return SSE_EINVAL; }
     if (n < 0) { set_error("n must be >= 0"); return SSE_EINVAL; }
     if (!b->compiled) { set_error("batch program not compiled (sse_batch_compile)"); return SSE_ESTATE; }
-    if (b->use_graph) {
+    const bool resident = b->resident && !stream_capturing(b->stream);
+    if (b->use_graph && !resident) {
         if (!b->graph_exec) {
-            int rc = capture(b->stream, [&] { batch_enqueue_any(b); }, &b->graph_exec);
+            int rc = capture(b->stream, [&] { batch_enqueue_any(b, false); }, &b->graph_exec);
             if (rc) return rc;
         }
         for (int i = 0; i < n; ++i) SSE_HIP(hipGraphLaunch(b->graph_exec, b->stream));
         return SSE_OK;
     }
-    for (int i = 0; i < n; ++i) batch_enqueue_any(b);
+    for (int i = 0; i < n; ++i) batch_enqueue_any(b, resident);
+    const hipError_t le = b->launch_error;
+    b->launch_error = hipSuccess;
+    if (le != hipSuccess) return hip_fail(le, "hipLaunchCooperativeKernel");
     SSE_HIP(hipGetLastError());
     return SSE_OK;
 }

@@ -120,6 +120,7 @@ namespace sse {
 // level by level, so a level-k set is a prefix of the region lists.  The
 // evaluation that produces level k reads level k + 1.
 constexpr int kBtThreads = 512;    // threads per workgroup
+constexpr int kFactSmall = 256;    // the same, factored weights, where every region fits them
 // Workgroups of a CU at once (4 waves per SIMD, 128 VGPRs): two, so one
 // workgroup's table loads overlap the other's evaluations.
 constexpr int kBtWavesPerSimd = 4;
@@ -133,7 +134,42 @@ constexpr int kBtWavesPerSimd = 4;
 // 5.68 ms per C1 step in FP64 against 2.92.
 constexpr int kBtPatch = 176;
 constexpr int kBtEdgeSlots = 2;    // edges of level 2 per thread (at most)
-constexpr int kBtRec = 12;         // ints per patch record
+constexpr int kBtPatchMin = 64;
+// Cells per patch of a mesh of C cells run on its own: what spreads it evenly
+// over the 256 CUs (up to kBtPatch per patch; a few percent more than the
+// even share, since the breadth-first cut leaves some patches short), down to
+// kBtPatchMin, below which the halo outweighs what a smaller patch saves.  A
+// mesh whose edges fit one workgroup is one patch and needs no exchange.
+// Resident loop, ms per step of 60 or 90 substeps in FP64, 176 cells per patch
+// against this rule: 64 x 64 0.44 / 0.33, 128 x 128 0.44 / 0.37, 256 x 256 0.54
+// / 0.48, level-5 sphere 0.63 / 0.48.
+constexpr int kCus = 256;
+inline int bt_patch_cells(int C) {
+    if (3 * C <= kBtEdgeSlots * kBtThreads) return C;
+    const int per_cu = (C + kCus * kBtPatch - 1) / (kCus * kBtPatch);
+    const int even = (int)(1.06 * C / (kCus * per_cu)) + 1;
+    return even < kBtPatchMin ? kBtPatchMin : even < kBtPatch ? even : kBtPatch;
+}
+constexpr int kBtRec = 16;         // ints per patch record
+
+// Factored TRiSK weights.  Around one cell with edges 0 .. n-1 in
+// counter-clockwise order, the reconstruction weights are differences of one
+// prefix sum S of the cell's kite fractions (Thuburn et al. 2009):
+//   W_{a,b} = s_a s_b (l_b / d_a) (1/2 - (S_b - S_a)),  b > a,
+//   W_{a,b} = s_a s_b (l_b / d_a) (1/2 - (S_n - S_a + S_b)),  b < a.
+// With x_b = s_b l_b u_b, the sum over a cell's edges is then, for every one
+// of them, a combination of X = sum x, Y = sum S x and the running sum
+// P_a = sum_{b<a} x_b: six numbers per cell (S_1 .. S_5, S_n) in the place of
+// ten weights per edge.  A mesh takes this form when its weights reproduce it
+// to a few units in the last place (sse_mesh.cpp); any other mesh keeps the
+// weight tables.
+constexpr int kFactEdges = 3;      // region edges per thread, level 3
+constexpr int kFactNbrs = 64;      // neighbour patches one wavefront polls
+struct DevFact {
+    const double *lh = nullptr, *fh = nullptr;      // [E] l_e / 2, f_e / 2
+    const double *S = nullptr, *ia = nullptr;       // [6][C] 2 S_1 .. 2 S_5, 2 S_n; [C] 1 / A
+    const float *lh_f = nullptr, *fh_f = nullptr, *S_f = nullptr, *ia_f = nullptr;
+};
 struct DevBtTiles {
     int nP = 0;                    // patches (0: tiling not available)
     int ks = 0;                    // edge slots per thread needed (1 or 2)
@@ -159,6 +195,26 @@ struct DevBtTiles {
     const double *ccd = nullptr;      // [6][..] s l / A
     const float *ccd_f = nullptr;
     const uint8_t *cwet = nullptr;    // [..]
+    // Factored form (fact == 1): these in the place of enb, ew, cen, ccd and
+    // cwet.  Edges at e0 + le over all region edges; cells at c0 + lc over all
+    // region cells; the slot-major cell tables at J c0 + j nc3 + lc.
+    int fact = 0;
+    int nt = 0;                       // threads per workgroup
+    int nA = 0;                       // patches with an ocean cell (listed first in order)
+    int resident = 0;                 // 1: every patch has at most kFactNbrs neighbours
+    // patch record words 12..14: offset and count of its neighbours, ocean flag
+    const int32_t *order = nullptr;   // [nP] patches with ocean cells, then the others
+    const int32_t *nbr = nullptr;     // patches whose values a patch reads or that read its values
+    const uint32_t *fec = nullptr;    // [sum ne3] local c1 | c2 << 15 | wet << 30 | read by another patch << 31
+    const double *elh = nullptr, *efh = nullptr;    // [sum ne3] l_e / 2, f_e / 2
+    const float *elh_f = nullptr, *efh_f = nullptr;
+    const double *fidc = nullptr;     // [sum ne3] 1 / d_e
+    const float *fidc_f = nullptr;
+    const uint32_t *fcen = nullptr;   // [3][..] local edges, 16 bits each: index | (edge points inwards) << 15
+    const double *cS = nullptr, *cia = nullptr;     // [6][..], [..]
+    const float *cS_f = nullptr, *cia_f = nullptr;
+    const uint8_t *cflag = nullptr;   // [sum nc3] wet | read by another patch << 1
+    DevFact g;                        // the same numbers per mesh entity (one launch per evaluation)
 };
 }  // namespace sse
 
@@ -183,6 +239,7 @@ struct sse_mesh {
     std::mutex tile_mu;
     std::unique_ptr<sse::PermutedDesc> host_desc;  // internal numbering, for building the lists
     sse::DevBtTiles bt;                       // patches of the tiled barotropic substeps
+    sse::DevBtTiles bt_batch;                 // patches for batch members (kBtPatch cells, kBtThreads threads)
     void *dev_buf = nullptr;
     size_t dev_bytes = 0;
 };
@@ -219,7 +276,13 @@ struct HostMeshTables {
     int n_ocean_cells = 0;
     // [E][kChainWords] vertex chains of canonical stencils (empty: generic)
     std::vector<int32_t> chain;
+    // factored weights (see DevFact; empty: the weights are not of that form)
+    std::vector<double> fS, fia, flh, ffh;
 };
+// Fills t.fS .. t.ffh if every weight of d (canonical stencils) is within
+// kFactTol of the factored form.
+constexpr double kFactTol = 4.0e-15;
+void factor_weights(const sse_mesh_desc *d, HostMeshTables &t);
 void build_tables(const sse_mesh_desc *d, HostMeshTables &t);
 
 struct HostTiles {
@@ -265,7 +328,7 @@ bool canonical_stencils(PermutedDesc &p, std::vector<int32_t> &chain);
 // breadth-first order) until every patch's level-2 region fits the
 // workgroup (kBtEdgeSlots edges and one cell per thread).  pid[c] = patch of
 // cell c.  Returns false if no such partition exists.
-bool bt_partition(const sse_mesh_desc *d, std::vector<int32_t> &pid, int &nP);
+bool bt_partition(const sse_mesh_desc *d, int target, std::vector<int32_t> &pid, int &nP);
 
 struct HostBtTiles {
     int nP = 0, ks = 0;
@@ -275,16 +338,39 @@ struct HostBtTiles {
     std::vector<float> cH_f, ew_f, eidc_f, ccd_f;
     std::vector<uint32_t> ec, enb, cen;
     std::vector<uint8_t> cwet;
+    // factored form
+    bool fact = false;
+    int nt = 0, nA = 0, resident = 0;
+    std::vector<int32_t> order, nbr;
+    std::vector<uint32_t> fec, fcen;
+    std::vector<double> elh, efh, fidc, cS, cia;
+    std::vector<uint8_t> cflag;
 };
+// A partition of a mesh with the device bytes of its tables.
+struct BtPartition {
+    bool ok = false;
+    int nP = 0;
+    std::vector<int32_t> pid;
+    size_t bytes = 0;
+};
+// Device bytes of the factored tables over TE region edges and TC region cells
+// in nP patches (global tables of E edges and C cells included).
+size_t fact_tiles_bytes(size_t nP, size_t TE, size_t TC, size_t E, size_t C);
 // Region lists and tables of the partition pid (numbering of d, the same
 // numbering as the tables t).  With t == nullptr only the sizes are filled
 // (patch records, list lengths), which is what the device-bytes query needs.
 bool build_bt_tiles(const sse_mesh_desc *d, const std::vector<int32_t> &pid, int nP, const HostMeshTables *t,
                     HostBtTiles &bt);
+// The same partition in the factored form; false if a region does not fit it.
+// min_nt: kFactSmall or kBtThreads, the fewest threads to take.
+bool build_fact_tiles(const sse_mesh_desc *d, const std::vector<int32_t> &pid, int nP, const HostMeshTables &t,
+                      int min_nt, HostBtTiles &bt);
 // Device bytes of the tiled barotropic tables of d (0 if d cannot be tiled),
-// and the partition itself; both come from a cache keyed by the topology.
+// and its partitions; both come from a cache keyed by the topology.  The first
+// has patches of kBtPatch cells (its tables in either form fit its bytes), the
+// second, where it differs, bt_patch_cells (factored form only).
 size_t bt_tiles_bytes(const sse_mesh_desc *d);
-bool bt_cached_partition(const sse_mesh_desc *d, std::vector<int32_t> &pid, int &nP);
+void bt_cached_partitions(const sse_mesh_desc *d, BtPartition &coarse, BtPartition &fine);
 // Range checks of the topology tables the size queries read.
 int check_topology(const sse_mesh_desc *d, std::string &err);
 

@@ -149,6 +149,8 @@ struct BTEvalArgs {
     int zeroF;                // overwrite F instead of accumulating
     int comb;
     double tau, g;
+    DevFact fk;               // factored weights (fact != 0)
+    int fact;
 };
 
 // One whole barotropic substep of every patch (tiled kernel): input (ua, za)
@@ -177,6 +179,22 @@ struct BtLoop {
     int *err;                 // set when a barrier wait runs out
     unsigned spins;           // polls before a barrier wait runs out
 };
+
+// The whole loop of one state with its patches resident (factored weights):
+// one workgroup per patch keeps its tables and state on chip for all M
+// substeps and exchanges the halo with its neighbours through the buffers.
+template <typename R>
+struct BtResident {
+    BTTileArgs<R> a;          // tables, G, F, tau, g and flux weights
+    int M;
+    const R *u_in, *z_in;     // loop input (not modified)
+    R *bu0, *bu1, *bz0, *bz1; // outputs of the substeps before the last, alternating
+    R *u_out, *z_out;         // the last substep's output
+    unsigned long long *done; // [patch * kDoneStride] substeps finished, counted on from base
+    int *err;                 // set when a wait runs out
+    unsigned spins;           // polls before a wait runs out
+};
+constexpr int kDoneStride = 8;  // one 64-byte line per patch
 
 // Thickness stage with the z-star distribution of a 2D total flux.
 struct THArgs {
@@ -309,10 +327,20 @@ template <typename R> void launch_bt_substep(const BTTileArgs<R> &a, int scheme,
 constexpr unsigned kBarrierSpins = 1u << 22;
 // Workgroups of the persistent loop kernel the device holds at once for this
 // tile set, precision and scheme (0 if it cannot launch cooperatively).
-template <typename R> int bt_loop_capacity(const DevBtTiles &t, int scheme);
+template <typename R> int bt_loop_capacity(const DevBtTiles &t, int scheme, int tight = 0);
 // The whole loop (a: tables, G, F, tau, g and flux weights; the per-substep
 // pointers of a are unused); returns the launch's HIP error.
 template <typename R> hipError_t launch_bt_loop(const BTTileArgs<R> &a, const BtLoop<R> &l, int scheme, hipStream_t s);
+// The resident loop in one cooperative launch; base is at least every value
+// any of its counters holds.  tight: which of the kResidentForms forms, those
+// holding more workgroups per CU coming later (the capacity queries take the
+// same number).
+constexpr int kResidentForms = 3;
+template <typename R>
+hipError_t launch_bt_resident(const BtResident<R> &a, int scheme, int tight, unsigned long long base, hipStream_t s);
+// The same over the patches of several states (table entries: member, place
+// in its patch order), which must all be resident at once.
+template <typename R> int bt_resident_batch_capacity(int scheme, int tight);
 template <typename R> void launch_thickness_iso(const THIsoArgs<R> &a, const Geom &g, hipStream_t s);
 template <typename R> void launch_assemble(const AssembleArgs<R> &a, const Geom &g, hipStream_t s);
 template <typename R>
@@ -358,8 +386,13 @@ int fe_edge_variant(const DevMesh &m, int L, int vmix, bool del4);
 template <typename R> void launch_fe_edge_batch(const BatchLaunch<FEEdgeArgs<R>> &b, int nk, bool add, int var, const Geom &g, hipStream_t s);
 template <typename R> void launch_bt_eval_batch(const BatchLaunch<BTEvalArgs<R>> &b, bool delta16, const Geom &g, hipStream_t s);
 // table entries (member, patch); ks and lds: the largest over the members
+// (ks with kFactVar set: factored weights)
+constexpr int kFactVar = 16;
 template <typename R>
 void launch_bt_substep_batch(const BatchLaunch<BTTileArgs<R>> &b, int scheme, int ks, size_t lds, hipStream_t s);
+template <typename R>
+hipError_t launch_bt_resident_batch(const BatchLaunch<BtResident<R>> &b, int scheme, int tight,
+                                    unsigned long long base, hipStream_t s);
 template <typename R> void launch_thickness_iso_batch(const BatchLaunch<THIsoArgs<R>> &b, int nk, const Geom &g, hipStream_t s);
 template <typename R> void launch_assemble_batch(const BatchLaunch<AssembleArgs<R>> &b, int nk, const Geom &g, hipStream_t s);
 template <typename Tin, typename Tout>

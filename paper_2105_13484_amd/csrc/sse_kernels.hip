@@ -1724,6 +1724,488 @@ __device__ __forceinline__ void bt_substep_body(const BTTileArgs<R> &a, int p) {
 
 
 // ---------------------------------------------------------------------------
+// Barotropic substeps with factored weights (see DevFact).
+//
+// What the weight tables cost: they are streamed once per substep, 80 bytes
+// of FP64 weights and 20 of indices per region edge, 270 MB per substep of a
+// 262,144-cell mesh, and that traffic bounds the substep (46.9 us).  The
+// factored form reads six numbers per cell and three per edge instead, 145 MB
+// (39.9 us; its loads alone take 27, the rest is the barriers and evaluations
+// that two workgroups per CU do not hide), and small enough tables stay on
+// chip for a whole loop (the resident form).  It works on a cell's six edges
+// at once and leaves the edges two half sums to subtract.  One evaluation is two phases with a barrier between them:
+//   edges  finish the velocity of the previous stage, publish x = l u / 2 and
+//          the flux x (h_c1 + h_c2), keep zeta_c2 - zeta_c1;
+//   cells  read the six x, f and fluxes, write six half sums and the new zeta.
+// Every fused multiply-add is spelled out and nothing else contracts, so the
+// forms of the loop (one launch per evaluation, per substep or per loop)
+// give the same bits.
+// ---------------------------------------------------------------------------
+
+// v with its sign flipped when bit 15 of w is set (an inward edge normal)
+__device__ __forceinline__ double flip(double v, uint32_t w) {
+    return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^
+                                          ((unsigned long long)(w & 0x8000u) << 48));
+}
+__device__ __forceinline__ float flip(float v, uint32_t w) {
+    return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) ^ ((w & 0x8000u) << 16));
+}
+
+// v with its sign flipped where an edge's byte offset w names the second of its
+// two half sums (see bt_fact_body)
+template <typename R>
+__device__ __forceinline__ R flip_side(R v, uint32_t w) {
+    if constexpr (sizeof(R) == 8)
+        return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, v) ^ ((unsigned long long)(w << 28) << 32));
+    else
+        return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) ^ (w << 29));
+}
+
+// Half sums of one cell, from x_b = s_b l_b u_b / 2, f_b / 2 and S = 2 S_1 ..
+// 2 S_5, 2 S_n: s_a h_a is edge a's share of d_a times the reconstructed
+// Coriolis term.  With y_b = (f_b / 2) x_b and the sums X, Y (Y weighted by S)
+// and P_a (before a) of x, X', Y' and P'_a of y,
+//   h_a = S_a (f_a X + X') + f_a (X - Y) + (X' - Y') - S_n (f_a P_a + P'_a) - 2 y_a
+// (f_a, S in the halved and doubled units above): six operations per edge.
+// store(a, h_a) receives them one by one.
+template <typename R, typename F>
+__device__ __forceinline__ void half_sums(const R (&x)[6], const R (&f)[6], const R (&S)[6], F &&store) {
+#pragma clang fp contract(off)
+    R X = x[0], Xy = f[0] * x[0], Y = R(0), Yy = R(0);
+#pragma unroll
+    for (int j = 1; j < 6; ++j) {
+        const R y = f[j] * x[j];
+        Y = j == 1 ? S[0] * x[1] : fmadd(S[j - 1], x[j], Y);
+        Yy = j == 1 ? S[0] * y : fmadd(S[j - 1], y, Yy);
+        X += x[j];
+        Xy += y;
+    }
+    const R D = X - Y, Dy = Xy - Yy;
+    R P = x[0], Py = f[0] * x[0];
+    store(0, fmadd(R(-2), Py, fmadd(f[0], D, Dy)));
+#pragma unroll
+    for (int j = 1; j < 6; ++j) {
+        const R y = f[j] * x[j];
+        const R B = fmadd(R(-2), y, fmadd(f[j], D, Dy));
+        const R h = fmadd(-S[5], fmadd(f[j], P, Py), B);
+        store(j, fmadd(S[j - 1], fmadd(f[j], X, Xy), h));
+        P += x[j];
+        Py += y;
+    }
+}
+// New velocity and zeta of one evaluation (hs: the half sum of c1 less that of
+// c2; dv: sum of x (h_c1 + h_c2), the cell's outward fluxes).
+template <typename R>
+__device__ __forceinline__ R fact_velocity(R u, R base, R hs, R dz, R idc, R G, R g, R tau, int comb) {
+#pragma clang fp contract(off)
+    const R ru = fmadd(fmadd(-g, dz, hs), idc, G);
+    return combine<R>(comb, base, fmadd(tau, ru, u));
+}
+template <typename R>
+__device__ __forceinline__ R fact_zeta(R z, R base, R dv, R ia, R tau, int comb) {
+#pragma clang fp contract(off)
+    return combine<R>(comb, base, fmadd(tau, -(dv * ia), z));
+}
+template <typename R>
+__device__ __forceinline__ double fact_transport(R u, R z1, R z2, double H1, double H2) {
+#pragma clang fp contract(off)
+    return (double)u * (0.5 * (((double)z1 + H1) + ((double)z2 + H2)));
+}
+
+template <typename R>
+struct FactTab;
+template <>
+struct FactTab<double> {
+    __device__ static const double *lh(const DevBtTiles &t) { return t.elh; }
+    __device__ static const double *fh(const DevBtTiles &t) { return t.efh; }
+    __device__ static const double *idc(const DevBtTiles &t) { return t.fidc; }
+    __device__ static const double *S(const DevBtTiles &t) { return t.cS; }
+    __device__ static const double *ia(const DevBtTiles &t) { return t.cia; }
+    __device__ static const double *lh(const DevFact &t) { return t.lh; }
+    __device__ static const double *fh(const DevFact &t) { return t.fh; }
+    __device__ static const double *S(const DevFact &t) { return t.S; }
+    __device__ static const double *ia(const DevFact &t) { return t.ia; }
+};
+template <>
+struct FactTab<float> {
+    __device__ static const float *lh(const DevBtTiles &t) { return t.elh_f; }
+    __device__ static const float *fh(const DevBtTiles &t) { return t.efh_f; }
+    __device__ static const float *idc(const DevBtTiles &t) { return t.fidc_f; }
+    __device__ static const float *S(const DevBtTiles &t) { return t.cS_f; }
+    __device__ static const float *ia(const DevBtTiles &t) { return t.cia_f; }
+    __device__ static const float *lh(const DevFact &t) { return t.lh_f; }
+    __device__ static const float *fh(const DevFact &t) { return t.fh_f; }
+    __device__ static const float *S(const DevFact &t) { return t.S_f; }
+    __device__ static const float *ia(const DevFact &t) { return t.ia_f; }
+};
+
+// One evaluation, one thread per edge or cell (the per-evaluation form).  The
+// edge forms both of its cells' half sums for itself.
+template <typename R>
+__device__ __forceinline__ void bt_eval_fact(const BTEvalArgs<R> &a, bool edge_part, int lb) {
+#pragma clang fp contract(off)
+    const DevMesh &m = a.m;
+    const R tau = (R)a.tau, g = (R)a.g;
+    const R *__restrict__ Ht = BTTables<R>::H(m);
+    const R *__restrict__ lh = FactTab<R>::lh(a.fk);
+    if (edge_part) {
+        const int e = lb * blockDim.x + threadIdx.x;
+        if (e >= m.E) return;
+        if (!m.emask[e]) {
+            a.uo[e] = R(0);
+            if (a.F && a.zeroF) a.F[e] = 0.0;
+            return;
+        }
+        const R *__restrict__ fh = FactTab<R>::fh(a.fk);
+        const R *__restrict__ St = FactTab<R>::S(a.fk);
+        const int c[2] = {m.edge_cells[2 * e], m.edge_cells[2 * e + 1]};
+        R hs[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int n = m.cell_nedges[c[s]];
+            R x[6], f[6], S[6];
+#pragma unroll
+            for (int j = 0; j < 6; ++j) {
+                const int ej = m.cell_edges_t[(size_t)j * m.C + c[s]];
+                const uint32_t w = m.edge_cells[2 * ej] == c[s] ? 0u : 0x8000u;
+                const R v = flip(lh[ej] * a.ua[ej], w);
+                x[j] = j < n ? v : R(0);
+                f[j] = j < n ? fh[ej] : R(0);
+                S[j] = St[(size_t)j * m.C + c[s]];
+            }
+            hs[s] = R(0);
+            half_sums<R>(x, f, S, [&](int j, R h) {
+                if (j < n && m.cell_edges_t[(size_t)j * m.C + c[s]] == e) hs[s] = h;
+            });
+        }
+        const R ua = a.ua[e];
+        const R z1 = a.za[c[0]], z2 = a.za[c[1]];
+        const R base = a.comb != COMB_NONE ? a.ub[e] : R(0);
+        a.uo[e] = fact_velocity<R>(ua, base, hs[0] - hs[1], z2 - z1, BTTables<R>::inv_dc(m)[e], (R)a.G[e], g, tau, a.comb);
+        if (a.F) a.F[e] = fmadd(a.wF, fact_transport<R>(ua, z1, z2, m.H[c[0]], m.H[c[1]]), a.zeroF ? 0.0 : a.F[e]);
+    } else {
+        const int i = lb * blockDim.x + threadIdx.x;
+        if (i >= m.C) return;
+        if (!m.cmask[i]) { a.zo[i] = R(0); return; }
+        const int n = m.cell_nedges[i];
+        const R zi = a.za[i] + Ht[i];
+        R dv = R(0);
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            const int e = m.cell_edges_t[(size_t)j * m.C + i], nb = m.cell_nbrs_t[(size_t)j * m.C + i];
+            const uint32_t w = m.edge_cells[2 * e] == i ? 0u : 0x8000u;
+            const R x = flip(lh[e] * a.ua[e], w);
+            if (j < n) dv = fmadd(x, zi + (a.za[nb] + Ht[nb]), dv);
+        }
+        const R base = a.comb != COMB_NONE ? a.zb[i] : R(0);
+        a.zo[i] = fact_zeta<R>(a.za[i], base, dv, FactTab<R>::ia(a.fk)[i], tau, a.comb);
+    }
+}
+
+// Waits until every neighbour of patch p has finished `target` substeps
+// (counted on from the launch's base), one lane per neighbour.  The wait is
+// bounded: if it runs out, or another workgroup's did, the workgroup goes on
+// without waiting and *err makes the host refuse the results.
+__device__ __forceinline__ void wait_neighbours(const unsigned long long *done, const int32_t *nbr, int n,
+                                                unsigned long long target, int *err, unsigned max_spins) {
+    const int lane = threadIdx.x;
+    if (lane < n) {
+        const unsigned long long *f = done + (size_t)nbr[lane] * kDoneStride;
+        unsigned spins = 0;
+        while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+            if (++spins > max_spins) {
+                __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            if ((spins & 255u) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+        }
+    }
+}
+
+// One substep of patch p (kLoop false: the input a.ua, a.za, the output a.uo,
+// a.zo), or all l->M substeps of the loop (kLoop true).
+//
+// In the loop form the tables, the forcing, the transport sums and the
+// patch's own state stay on chip, and a substep ends with an exchange: the
+// values other patches read go out with device-scope stores (through to the
+// memory all XCDs share; no cache is written back or dropped), the workgroup
+// counts its substep, waits for its neighbours' counts and reads its halo
+// with device-scope loads.  Two buffers alternate: a neighbour overwrites
+// the one of substep s only after this workgroup's count for s + 1 tells it
+// that its values have been read.
+//
+// LDS, fixed places so that one address register serves several arrays (NT
+// threads hold at most kFactEdges NT region edges and NT region cells):
+//   XF  (x, f / 2) of an edge     HS  the half sums of its two cells
+//   ZS  h_c1 + h_c2 of an edge    ZH  (zeta, H) of a cell
+template <typename R>
+struct alignas(2 * sizeof(R)) Pair {
+    R a, b;
+};
+template <typename R>
+struct alignas(16) ZetaDepth {
+    double H;
+    R z;
+};
+template <typename R, int NT>
+struct FactLds {
+    Pair<R> XF[kFactEdges * NT];
+    Pair<R> HS[kFactEdges * NT];
+    ZetaDepth<R> ZH[NT];
+    R ZS[kFactEdges * NT];
+};
+
+template <typename R, int kScheme, bool kLoop, int NT>
+__device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtResident<R> *l, int p,
+                                             unsigned long long base_count) {
+#pragma clang fp contract(off)
+    __shared__ FactLds<R, NT> lds;
+    const DevBtTiles &T = a.t;
+    const int tid = threadIdx.x;
+    const int32_t *rec = T.patch + (size_t)p * kBtRec;
+    const int e0 = rec[0], c0 = rec[2];
+    int ne[4], nc[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        ne[k] = rec[4 + k];
+        nc[k] = rec[8 + k];
+    }
+    constexpr int kIn = kScheme == 3 ? 3 : 2;  // level of the substep input
+    constexpr int KS = kBtEdgeSlots;
+    if (!kLoop && !rec[14]) {  // no ocean cell: velocity, zeta and transport are zero
+        for (int le = tid; le < ne[0]; le += NT) {
+            const int e = T.eid[e0 + le];
+            a.uo[e] = R(0);
+            if (a.F && a.zeroF) a.F[e] = 0.0;
+        }
+        if (tid < nc[0]) a.zo[T.cid[c0 + tid]] = R(0);
+        return;
+    }
+    const int nEin = ne[kIn], nCin = nc[kIn];
+
+    // this thread's edges le = s NT + tid and cell lc = tid
+    R lhv[kFactEdges], u[KS], u0[KS], idc[KS], Gv[KS], dz[KS];
+    double Fa[KS];
+    uint32_t ec[kFactEdges];
+    int ge[kFactEdges];
+    const R *ua = kLoop ? l->u_in : a.ua, *za = kLoop ? l->z_in : a.za;
+#pragma unroll
+    for (int s = 0; s < kFactEdges; ++s) {
+        const int le = s * NT + tid;
+        const bool on = le < nEin;
+        const int q = e0 + (on ? le : 0);
+        ge[s] = T.eid[q];
+        lhv[s] = FactTab<R>::lh(T)[q];
+        ec[s] = T.fec[q];
+        const R v = ua[ge[s]];
+        if (s < KS) {
+            idc[s < KS ? s : 0] = FactTab<R>::idc(T)[q];
+            Gv[s < KS ? s : 0] = (R)a.G[ge[s]];
+            u[s < KS ? s : 0] = v;
+            Fa[s < KS ? s : 0] = (a.F && le < ne[0] && !(kLoop || a.zeroF)) ? a.F[ge[s]] : 0.0;
+        }
+        if (on) lds.XF[le] = Pair<R>{lhv[s] * v, FactTab<R>::fh(T)[q]};
+    }
+    const bool con = tid < nCin;
+    const int qc = con ? tid : 0;
+    const int gc = T.cid[c0 + qc];
+    const uint32_t cfl = T.cflag[c0 + qc];
+    const bool cwet = con && (cfl & 1u) != 0;
+    // byte offset of the cell's half sum on each of its edges: the edge's pair,
+    // the second of it where the cell is c2.  The edge's (x, f) pair is the
+    // same offset with that bit cleared, and the bit, shifted to the top, the
+    // sign s_j.
+    constexpr uint32_t kSide = sizeof(R);
+    uint32_t w[6];
+    R S[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const uint32_t c = T.fcen[(size_t)3 * c0 + (size_t)(j >> 1) * nc[3] + qc] >> (16 * (j & 1));
+        w[j] = (c & 0x7fffu) * 2 * kSide + ((c & 0x8000u) ? kSide : 0u);
+        S[j] = FactTab<R>::S(T)[(size_t)6 * c0 + (size_t)j * nc[3] + qc];
+    }
+    const R ia = FactTab<R>::ia(T)[c0 + qc];
+    R z = za[gc], z0;
+    if (con) lds.ZH[tid] = ZetaDepth<R>{T.cH[c0 + tid], z};
+    if (tid == 0) {  // the entry that missing edge slots read
+        lds.XF[ne[3]] = Pair<R>{R(0), R(0)};
+        lds.ZS[ne[3]] = R(0);
+    }
+    const R tau = (R)a.tau, g = (R)a.g;
+
+    // Publishes h_c1 + h_c2 of the edges the evaluation of level lvl sums over
+    // (at level 0 those of level 1: some edges of the patch's cells are owned
+    // by the neighbour) and adds the owned edges' transport.
+    auto prepare = [&](int lvl, double wF) {
+#pragma clang fp contract(off)
+        const int n = ne[lvl < 1 ? 1 : lvl];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int le = s * NT + tid;
+            if (le < n) {
+                const ZetaDepth<R> a1 = lds.ZH[ec[s] & 0x7fffu], a2 = lds.ZH[(ec[s] >> 15) & 0x7fffu];
+                lds.ZS[le] = (a1.z + (R)a1.H) + (a2.z + (R)a2.H);
+                dz[s] = a2.z - a1.z;
+                if (a.F && le < ne[0] && ((ec[s] >> 30) & 1u))
+                    Fa[s] = fmadd(wF, fact_transport<R>(u[s], a1.z, a2.z, a1.H, a2.H), Fa[s]);
+            }
+        }
+    };
+    // Cell phase of the evaluation that produces level lvl.
+    auto cells = [&](int lvl, int comb, R *zout) {
+#pragma clang fp contract(off)
+        if (tid < nc[lvl + 1] && cwet) {
+            const char *const xf = reinterpret_cast<const char *>(lds.XF);
+            const char *const zs = reinterpret_cast<const char *>(lds.ZS);
+            char *const hs = reinterpret_cast<char *>(lds.HS);
+            R x[6], f[6];
+#pragma unroll
+            for (int j = 0; j < 6; ++j) {
+                const Pair<R> v = *reinterpret_cast<const Pair<R> *>(xf + (w[j] & ~kSide));
+                x[j] = flip_side<R>(v.a, w[j]);
+                f[j] = v.b;
+            }
+            if (tid < nc[lvl]) {
+                R dv = R(0);
+#pragma unroll
+                for (int j = 0; j < 6; ++j)
+                    dv = fmadd(x[j], *reinterpret_cast<const R *>(zs + ((w[j] >> 1) & ~(kSide - 1))), dv);
+                z = fact_zeta<R>(z, comb != COMB_NONE ? z0 : R(0), dv, ia, tau, comb);
+            }
+            // the fluxes' registers are free before the half sums begin
+            __builtin_amdgcn_sched_barrier(0);
+            half_sums<R>(x, f, S, [&](int j, R h) { *reinterpret_cast<R *>(hs + w[j]) = h; });
+        } else {
+            z = R(0);  // land
+        }
+        if (tid < nc[lvl]) {
+            lds.ZH[tid].z = z;
+            if (zout) zout[gc] = z;
+        }
+    };
+    // Edge phase after it: the new velocity of level lvl.
+    auto edges = [&](int lvl, int comb, R *uout) {
+#pragma clang fp contract(off)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int le = s * NT + tid;
+            if (le < ne[lvl]) {
+                R out = R(0);
+                if ((ec[s] >> 30) & 1u) {
+                    const Pair<R> h = lds.HS[le];
+                    out = fact_velocity<R>(u[s], comb != COMB_NONE ? u0[s] : R(0), h.a - h.b, dz[s], idc[s], Gv[s], g, tau, comb);
+                }
+                u[s] = out;
+                if (uout) uout[ge[s]] = out;
+                else lds.XF[le].a = lhv[s] * out;
+            }
+        }
+    };
+
+    const int nsub = kLoop ? l->M : 1;
+#pragma unroll 1
+    for (int sub = 0; sub < nsub; ++sub) {
+        const bool last = sub == nsub - 1;
+        R *uo = kLoop ? (last ? l->u_out : nullptr) : a.uo;
+        R *zo = kLoop ? (last ? l->z_out : nullptr) : a.zo;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) u0[s] = u[s];
+        z0 = z;
+        __syncthreads();
+        if constexpr (kScheme == 3) {
+            prepare(2, a.w1);
+            __syncthreads();
+            cells(2, COMB_NONE, nullptr);
+            __syncthreads();
+            edges(2, COMB_NONE, nullptr);
+            prepare(1, a.w1);
+            __syncthreads();
+            cells(1, COMB_34, nullptr);
+            __syncthreads();
+            edges(1, COMB_34, nullptr);
+            prepare(0, a.w3);
+            __syncthreads();
+            cells(0, COMB_THIRD, zo);
+            __syncthreads();
+            edges(0, COMB_THIRD, uo);
+        } else {
+            prepare(1, a.w1);
+            __syncthreads();
+            cells(1, COMB_NONE, nullptr);
+            __syncthreads();
+            edges(1, COMB_NONE, nullptr);
+            prepare(0, a.w1);
+            __syncthreads();
+            cells(0, COMB_HALF, zo);
+            __syncthreads();
+            edges(0, COMB_HALF, uo);
+        }
+        if constexpr (kLoop) {
+            if (last) break;
+            R *bu = (sub & 1) ? l->bu1 : l->bu0, *bz = (sub & 1) ? l->bz1 : l->bz0;
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                if (s * NT + tid < ne[0] && (ec[s] >> 31))
+                    __hip_atomic_store(bu + ge[s], u[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid < nc[0] && (cfl & 2u)) __hip_atomic_store(bz + gc, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // every wavefront's stores have reached the shared memory before
+            // the substep is counted
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            const unsigned long long target = base_count + (unsigned long long)(sub + 1);
+            if (tid == 0)
+                __hip_atomic_store(l->done + (size_t)p * kDoneStride, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wait_neighbours(l->done, T.nbr + rec[12], rec[13], target, l->err, l->spins);
+            asm volatile("" ::: "memory");
+            __syncthreads();
+            // the halo: dry edges and land cells stay zero
+#pragma unroll
+            for (int s = 0; s < kFactEdges; ++s) {
+                const int le = s * NT + tid;
+                if (le < nEin) {
+                    R v = R(0);
+                    if (le < ne[0]) v = u[s < KS ? s : 0];
+                    else if ((ec[s] >> 30) & 1u) v = __hip_atomic_load(bu + ge[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (s < KS) u[s < KS ? s : 0] = v;
+                    lds.XF[le].a = lhv[s] * v;
+                }
+            }
+            if (con && tid >= nc[0]) {
+                z = cwet ? __hip_atomic_load(bz + gc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : R(0);
+                lds.ZH[tid].z = z;
+            }
+        }
+    }
+    if constexpr (kLoop) {
+        // after a wait that ran out the results are worthless: they come out
+        // as NaN where nobody reads the error word
+        if (__hip_atomic_load(l->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 && tid < nc[0]) l->z_out[gc] = R(NAN);
+    }
+    if (a.F) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            if (s * NT + tid < ne[0]) a.F[ge[s]] = Fa[s];
+    }
+}
+
+// The resident loop of the patch that workgroup lb of the launch owns (patches
+// without ocean cells have no workgroup: their zeros are written by others).
+template <typename R, int kScheme, int NT>
+__device__ __forceinline__ void bt_resident_body(const BtResident<R> &l, int lb, unsigned long long base) {
+    const DevBtTiles &T = l.a.t;
+    for (int i = T.nA + lb; i < T.nP; i += T.nA) {
+        const int32_t *rec = T.patch + (size_t)T.order[i] * kBtRec;
+        for (int le = threadIdx.x; le < rec[4]; le += NT) {
+            const int e = T.eid[rec[0] + le];
+            l.u_out[e] = R(0);
+            if (l.a.F) l.a.F[e] = 0.0;
+        }
+        for (int lc = threadIdx.x; lc < rec[8]; lc += NT) l.z_out[T.cid[rec[2] + lc]] = R(0);
+    }
+    bt_fact_body<R, kScheme, true, NT>(l.a, &l, T.order[lb], base);
+}
+
+// ---------------------------------------------------------------------------
 // Thickness stage (z-star): h_out = comb(h_n, h_in + dt T^h), zeta = sum h - H
 // ---------------------------------------------------------------------------
 template <int NK, int Q>
@@ -2230,10 +2712,16 @@ __global__ void __launch_bounds__(1024) bt_eval_kernel(BTEvalArgs<R> a, int nEdg
     const int x = blockIdx.x % kXcd, local = blockIdx.x / kXcd;
     if (local < pe) {
         const int lb = x * pe + local;
-        if (lb < nEdgeBlocks) bt_eval_body<R, kD16>(a, true, lb);
+        if (lb < nEdgeBlocks) {
+            if (a.fact) bt_eval_fact<R>(a, true, lb);
+            else bt_eval_body<R, kD16>(a, true, lb);
+        }
     } else {
         const int lb = x * pc + (local - pe);
-        if (lb < nCellBlocks) bt_eval_body<R, kD16>(a, false, lb);
+        if (lb < nCellBlocks) {
+            if (a.fact) bt_eval_fact<R>(a, false, lb);
+            else bt_eval_body<R, kD16>(a, false, lb);
+        }
     }
 }
 template <typename R, bool kD16>
@@ -2242,10 +2730,10 @@ __global__ void __launch_bounds__(1024) bt_eval_batch(BatchLaunch<BTEvalArgs<R>>
     if (!batch_entry(b.table, b.blocks, t)) return;
     const BTEvalArgs<R> &a = b.args[t.x];
     const int nEB = (a.m.E + (int)blockDim.x - 1) / (int)blockDim.x;
-    if (t.y < nEB)
-        bt_eval_body<R, kD16>(a, true, t.y);
-    else
-        bt_eval_body<R, kD16>(a, false, t.y - nEB);
+    const bool edge_part = t.y < nEB;
+    const int lb = edge_part ? t.y : t.y - nEB;
+    if (a.fact) bt_eval_fact<R>(a, edge_part, lb);
+    else bt_eval_body<R, kD16>(a, edge_part, lb);
 }
 
 template <typename R, int kScheme, int KS, bool kDry = false>
@@ -2266,6 +2754,37 @@ __global__ void __launch_bounds__(kBtThreads, kBtWavesPerSimd) bt_substep_batch(
 template <typename R, int kScheme, int KS>
 __global__ void __launch_bounds__(kBtThreads, kBtWavesPerSimd) bt_loop_kernel(BTTileArgs<R> a, BtLoop<R> l) {
     bt_loop_body<R, kScheme, KS>(a, l, xcd_block(a.t.nP));
+}
+
+// Factored substep and resident loop.  Waves per SIMD (kW): the substep's FP64
+// body takes 128 VGPRs (two workgroups of kBtThreads per CU), its FP32 body 88.
+// The loop comes in forms that hold one, two or (FP32) three such workgroups
+// per CU, and runs in the roomiest that holds the mesh: at two it keeps to 128
+// VGPRs and in FP64 spills 16 of them, at three to 80 and spills 18, which
+// makes a substep 35% slower (0.39 -> 0.53 ms per step of 60 substeps on a 256
+// x 256 mesh) but still halves the time of one launch per substep (level-7
+// sphere: 0.88 ms per step of 90 substeps against 1.85).
+template <typename R>
+constexpr int fact_waves() { return sizeof(R) == 8 ? 4 : 5; }
+template <typename R, int kScheme, int NT>
+__global__ void __launch_bounds__(NT, fact_waves<R>()) bt_fact_kernel(BTTileArgs<R> a) {
+    const int p = xcd_block(a.t.nP);
+    if (p >= 0) bt_fact_body<R, kScheme, false, NT>(a, nullptr, p, 0);
+}
+template <typename R, int kScheme>
+__global__ void __launch_bounds__(kBtThreads, fact_waves<R>()) bt_fact_batch(BatchLaunch<BTTileArgs<R>> b) {
+    int2 t;
+    if (batch_entry(b.table, b.blocks, t)) bt_fact_body<R, kScheme, false, kBtThreads>(b.args[t.x], nullptr, t.y, 0);
+}
+template <typename R, int kScheme, int NT, int kW>
+__global__ void __launch_bounds__(NT, kW) bt_resident_kernel(BtResident<R> l, unsigned long long base) {
+    const int lb = xcd_block(l.a.t.nA);
+    if (lb >= 0) bt_resident_body<R, kScheme, NT>(l, lb, base);
+}
+template <typename R, int kScheme, int kW>
+__global__ void __launch_bounds__(kBtThreads, kW) bt_resident_batch(BatchLaunch<BtResident<R>> b, unsigned long long base) {
+    int2 t;
+    if (batch_entry(b.table, b.blocks, t)) bt_resident_body<R, kScheme, kBtThreads>(b.args[t.x], t.y, base);
 }
 
 __global__ void __launch_bounds__(64) bt_loop_reset_kernel(unsigned *bar, unsigned *gen) {
@@ -2468,6 +2987,25 @@ static const void *bt_loop_select(int scheme, int ks) {
     return ks == 1 ? bt_loop_fn<R, 2, 1>() : bt_loop_fn<R, 2, 2>();
 }
 
+// The resident loop kernel for nt threads in the form of `tight` (see
+// kResidentForms), alone or over a batch.
+template <typename R, int kScheme, int kW>
+static const void *bt_resident_of(int nt, bool batch) {
+    if (batch) return reinterpret_cast<const void *>(bt_resident_batch<R, kScheme, kW>);
+    if (nt == kBtThreads) return reinterpret_cast<const void *>(bt_resident_kernel<R, kScheme, kBtThreads, kW>);
+    return reinterpret_cast<const void *>(bt_resident_kernel<R, kScheme, kFactSmall, kW>);
+}
+template <typename R, int kScheme>
+static const void *bt_resident_form(int nt, int tight, bool batch) {
+    if constexpr (sizeof(R) == 4)
+        if (tight >= 2) return bt_resident_of<R, kScheme, 6>(nt, batch);
+    return tight ? bt_resident_of<R, kScheme, 4>(nt, batch) : bt_resident_of<R, kScheme, 2>(nt, batch);
+}
+template <typename R>
+static const void *bt_resident_fn(int scheme, int nt, int tight, bool batch = false) {
+    return scheme == 3 ? bt_resident_form<R, 3>(nt, tight, batch) : bt_resident_form<R, 2>(nt, tight, batch);
+}
+
 // Allow the tiled kernels the device's full LDS per workgroup.
 void set_tiled_lds_limit(size_t bytes) {
 #define SSE_TILED_FN(NK_, R_, ADD_, MIX_) reinterpret_cast<const void *>(fe_edge_tiled_kernel<NK_, R_, ADD_, MIX_>)
@@ -2511,6 +3049,16 @@ template <typename R>
 void launch_bt_substep(const BTTileArgs<R> &a, int scheme, hipStream_t s) {
     const dim3 grid = xcd_grid(a.t.nP), block(kBtThreads);
     const size_t lds = sizeof(R) == 8 ? a.t.lds_d : a.t.lds_f;
+    if (a.t.fact) {
+        if (a.t.nt == kBtThreads) {
+            if (scheme == 3) bt_fact_kernel<R, 3, kBtThreads><<<grid, kBtThreads, 0, s>>>(a);
+            else bt_fact_kernel<R, 2, kBtThreads><<<grid, kBtThreads, 0, s>>>(a);
+        } else {
+            if (scheme == 3) bt_fact_kernel<R, 3, kFactSmall><<<grid, kFactSmall, 0, s>>>(a);
+            else bt_fact_kernel<R, 2, kFactSmall><<<grid, kFactSmall, 0, s>>>(a);
+        }
+        return;
+    }
     if (sizeof(R) == 8 && a.t.dry) {
         if (scheme == 3) {
             if (a.t.ks == 1) bt_substep_kernel<R, 3, 1, true><<<grid, block, lds, s>>>(a);
@@ -2528,18 +3076,21 @@ void launch_bt_substep(const BTTileArgs<R> &a, int scheme, hipStream_t s) {
     }
 }
 
-template <typename R>
-int bt_loop_capacity(const DevBtTiles &t, int scheme) {
-    if (t.nP <= 0) return 0;
+// Workgroups of a cooperative kernel the device holds at once.
+static int coop_capacity(const void *fn, int threads, size_t lds) {
     int dev = 0, coop = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    const size_t lds = sizeof(R) == 8 ? t.lds_d : t.lds_f;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, bt_loop_select<R>(scheme, t.ks), kBtThreads, lds) !=
-        hipSuccess)
-        return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess) return 0;
     return per_cu * cus;
+}
+
+template <typename R>
+int bt_loop_capacity(const DevBtTiles &t, int scheme, int tight) {
+    if (t.nP <= 0) return 0;
+    if (t.fact) return coop_capacity(bt_resident_fn<R>(scheme, t.nt, tight), t.nt, 0);
+    return coop_capacity(bt_loop_select<R>(scheme, t.ks), kBtThreads, sizeof(R) == 8 ? t.lds_d : t.lds_f);
 }
 
 template <typename R>
@@ -2554,8 +3105,38 @@ hipError_t launch_bt_loop(const BTTileArgs<R> &a, const BtLoop<R> &l, int scheme
 }
 
 template <typename R>
+hipError_t launch_bt_resident(const BtResident<R> &l, int scheme, int tight, unsigned long long base, hipStream_t s) {
+    BtResident<R> ll = l;
+    const int nA = l.a.t.nA, nt = l.a.t.nt, blocks = (int)xcd_grid(nA).x;
+    void *args[] = {&ll, &base};
+    const void *fn = bt_resident_fn<R>(scheme, nt, tight);
+    // one patch waits for nobody: an ordinary launch
+    if (nA == 1) return hipLaunchKernel(fn, xcd_grid(1), dim3(nt), args, 0, s);
+    return hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(nt), args, 0, s);
+}
+
+template <typename R>
+int bt_resident_batch_capacity(int scheme, int tight) {
+    return coop_capacity(bt_resident_fn<R>(scheme, kBtThreads, tight, true), kBtThreads, 0);
+}
+
+template <typename R>
+hipError_t launch_bt_resident_batch(const BatchLaunch<BtResident<R>> &b, int scheme, int tight,
+                                    unsigned long long base, hipStream_t s) {
+    BatchLaunch<BtResident<R>> bb = b;
+    const int blocks = (int)xcd_grid(b.blocks).x;
+    void *args[] = {&bb, &base};
+    return hipLaunchCooperativeKernel(bt_resident_fn<R>(scheme, kBtThreads, tight, true), dim3(blocks), dim3(kBtThreads), args, 0, s);
+}
+
+template <typename R>
 void launch_bt_substep_batch(const BatchLaunch<BTTileArgs<R>> &b, int scheme, int ks, size_t lds, hipStream_t s) {
     const dim3 grid = xcd_grid(b.blocks), block(kBtThreads);
+    if (ks & kFactVar) {
+        if (scheme == 3) bt_fact_batch<R, 3><<<grid, kBtThreads, 0, s>>>(b);
+        else bt_fact_batch<R, 2><<<grid, kBtThreads, 0, s>>>(b);
+        return;
+    }
     if (scheme == 3) {
         if (ks == 1) bt_substep_batch<R, 3, 1><<<grid, block, lds, s>>>(b);
         else bt_substep_batch<R, 3, 2><<<grid, block, lds, s>>>(b);
@@ -2673,8 +3254,11 @@ void launch_convert_batch(const BatchLaunch<ConvArgs<Tin, Tout>> &b, const Geom 
     template void launch_edge_gathers<R>(const FEEdgeArgs<R> &, const Geom &, hipStream_t);                \
     template void launch_bt_eval<R>(const BTEvalArgs<R> &, const Geom &, hipStream_t);                     \
     template void launch_bt_substep<R>(const BTTileArgs<R> &, int, hipStream_t);                           \
-    template int bt_loop_capacity<R>(const DevBtTiles &, int);                                             \
+    template int bt_loop_capacity<R>(const DevBtTiles &, int, int);                                        \
     template hipError_t launch_bt_loop<R>(const BTTileArgs<R> &, const BtLoop<R> &, int, hipStream_t);       \
+    template hipError_t launch_bt_resident<R>(const BtResident<R> &, int, int, unsigned long long, hipStream_t); \
+    template int bt_resident_batch_capacity<R>(int, int);                                                         \
+    template hipError_t launch_bt_resident_batch<R>(const BatchLaunch<BtResident<R>> &, int, int, unsigned long long, hipStream_t); \
     template void launch_bt_substep_batch<R>(const BatchLaunch<BTTileArgs<R>> &, int, int, size_t, hipStream_t); \
     template void launch_bt_eval_batch<R>(const BatchLaunch<BTEvalArgs<R>> &, bool, const Geom &, hipStream_t); \
     template void launch_thickness_iso<R>(const THIsoArgs<R> &, const Geom &, hipStream_t);                \

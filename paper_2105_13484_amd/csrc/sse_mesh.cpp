@@ -284,6 +284,49 @@ void build_tables(const sse_mesh_desc *d, HostMeshTables &t) {
     to_f32(t.wpair, t.wpair_f);
 }
 
+void factor_weights(const sse_mesh_desc *d, HostMeshTables &t) {
+    t.fS.clear();
+    const int C = d->n_cells, E = d->n_edges, me = d->max_edges;
+    if (t.chain.empty()) return;
+    std::vector<double> S((size_t)6 * C, 0.0);
+    for (int c = 0; c < C; ++c) {
+        const int n = d->n_edges_on_cell[c];
+        const int32_t *ec = d->edges_on_cell + (size_t)c * me;
+        // om(a, b) = W_{a,b} s_a s_b d_a / l_b; the canonical stencil of edge a
+        // lists the cell's other edges counter-clockwise after a
+        double om[6][6] = {};
+        for (int a = 0; a < n; ++a) {
+            const int e = ec[a], side = d->cells_on_edge[2 * (size_t)e] == c ? 0 : 1;
+            for (int k = 0; k < n - 1; ++k) {
+                const int b = (a + 1 + k) % n, eb = ec[b];
+                if (t.eoe[(size_t)(5 * side + k) * E + e] != eb) return;
+                const double sb = d->cells_on_edge[2 * (size_t)eb] == c ? 1.0 : -1.0;
+                om[a][b] = (side ? -sb : sb) * t.w[(size_t)(5 * side + k) * E + e] * d->dc_edge[e] / d->dv_edge[eb];
+            }
+        }
+        double s[6] = {};
+        for (int b = 1; b < n; ++b) s[b] = 0.5 - om[0][b];
+        const double total = 0.5 + s[1] - om[1][0];
+        for (int a = 0; a < n; ++a)
+            for (int b = 0; b < n; ++b) {
+                if (a == b) continue;
+                const double want = b > a ? 0.5 - (s[b] - s[a]) : 0.5 - (total - s[a] + s[b]);
+                if (!(std::fabs(om[a][b] - want) <= kFactTol)) return;
+            }
+        for (int j = 1; j < 6; ++j) S[(size_t)(j - 1) * C + c] = j < n ? 2.0 * s[j] : 0.0;
+        S[(size_t)5 * C + c] = 2.0 * total;
+    }
+    t.fS.swap(S);
+    t.fia.resize(C);
+    for (int c = 0; c < C; ++c) t.fia[c] = 1.0 / d->area_cell[c];
+    t.flh.resize(E);
+    t.ffh.resize(E);
+    for (int e = 0; e < E; ++e) {
+        t.flh[e] = 0.5 * d->dv_edge[e];
+        t.ffh[e] = 0.5 * d->f_edge[e];
+    }
+}
+
 bool build_tiles(const sse_mesh_desc *d, int T, HostTiles &t) {
     const int E = d->n_edges, me2 = d->max_edges2;
     t.T = T;
@@ -675,6 +718,11 @@ struct RegionBuilder {
             ne[k] = (int)edges.size();
         }
     }
+    // The region fits the factored kernels with nt threads (one entry past the
+    // region edges stays free for missing edge slots).
+    bool fits_fact(int nt) const {
+        return ne[2] <= kBtEdgeSlots * nt && ne[3] < kFactEdges * nt && nc[3] <= nt;
+    }
     bool fits() const {
         return ne[2] <= kBtEdgeSlots * kBtThreads && nc[2] <= kBtThreads && nc[3] < (1 << 15) && ne[3] < (1 << 16);
     }
@@ -692,7 +740,7 @@ constexpr size_t kBtLdsMax = 160 * 1024;
 
 }  // namespace
 
-bool bt_partition(const sse_mesh_desc *d, std::vector<int32_t> &pid, int &nP) {
+bool bt_partition(const sse_mesh_desc *d, int target, std::vector<int32_t> &pid, int &nP) {
     const int C = d->n_cells;
     pid.assign(C, -1);
     std::vector<std::vector<int32_t>> patches;
@@ -721,7 +769,7 @@ bool bt_partition(const sse_mesh_desc *d, std::vector<int32_t> &pid, int &nP) {
             cells.push_back(c);
             for_each_neighbour(d, c, [&](int nb) {
                 if (taken[nb]) return;
-                if ((int)(cells.size() + q.size()) < kBtPatch) {
+                if ((int)(cells.size() + q.size()) < target) {
                     taken[nb] = 1;
                     q.push_back(nb);
                 } else {
@@ -835,6 +883,117 @@ bool build_bt_tiles(const sse_mesh_desc *d, const std::vector<int32_t> &pid, int
     return bt.ks >= 1 && bt.ks <= kBtEdgeSlots;
 }
 
+size_t fact_tiles_bytes(size_t nP, size_t TE, size_t TC, size_t E, size_t C) {
+    auto al = [](size_t x) { return (x + kAlign - 1) / kAlign * kAlign; };
+    size_t n = al(nP * kBtRec * 4) + al(nP * 4) + al(nP * kFactNbrs * 4);
+    n += 2 * al(TE * 4) + al(TC * 4) + al(TC * 8) + al(3 * TC * 4) + al(TC);
+    for (size_t rs : {sizeof(double), sizeof(float)})
+        n += 3 * al(TE * rs) + al(6 * TC * rs) + al(TC * rs) + 2 * al(E * rs) + al(6 * C * rs) + al(C * rs);
+    return n;
+}
+
+bool build_fact_tiles(const sse_mesh_desc *d, const std::vector<int32_t> &pid, int nP, const HostMeshTables &t,
+                      int min_nt, HostBtTiles &bt) {
+    const int C = d->n_cells, E = d->n_edges;
+    if (t.fS.empty()) return false;
+    std::vector<std::vector<int32_t>> own(nP);
+    for (int c = 0; c < C; ++c) own[pid[c]].push_back(c);
+    RegionBuilder rb(d);
+    bt = HostBtTiles();
+    bt.fact = true;
+    bt.nP = nP;
+    bt.patch.assign((size_t)nP * kBtRec, 0);
+    std::vector<uint8_t> out_e(E, 0), out_c(C, 0);       // read by another patch
+    std::vector<std::vector<int32_t>> reads(nP);
+    bt.nt = min_nt;
+    for (int p = 0; p < nP; ++p) {
+        rb.build(own[p], pid, p);
+        const int ne2 = rb.ne[2], ne3 = rb.ne[3], nc3 = rb.nc[3];
+        for (; !rb.fits_fact(bt.nt); bt.nt = kBtThreads)
+            if (bt.nt == kBtThreads) return false;
+        int32_t *r = &bt.patch[(size_t)p * kBtRec];
+        const size_t e0 = bt.eid.size(), c0 = bt.cid.size();
+        r[0] = (int)e0; r[1] = (int)e0; r[2] = (int)c0; r[3] = (int)c0;
+        for (int k = 0; k < 4; ++k) { r[4 + k] = rb.ne[k]; r[8 + k] = rb.nc[k]; }
+        for (int c : own[p]) r[14] |= t.cmask[c] ? 1 : 0;
+        bt.eid.insert(bt.eid.end(), rb.edges.begin(), rb.edges.end());
+        bt.cid.insert(bt.cid.end(), rb.cells.begin(), rb.cells.end());
+        auto in_c = [&](int c) { return c >= 0 && rb.cst[c] == rb.stamp; };
+        auto in_e = [&](int e) { return e >= 0 && rb.est[e] == rb.stamp; };
+        auto read = [&](int q) {
+            if (q != p && r[14]) reads[p].push_back(q);
+        };
+        for (int le = 0; le < ne3; ++le) {
+            const int e = rb.edges[le];
+            const int g1 = t.edge_cells[2 * (size_t)e], g2 = t.edge_cells[2 * (size_t)e + 1];
+            if (le < ne2 && (!in_c(g1) || !in_c(g2))) return false;
+            // the cells of the outermost edges may lie outside the region; nothing reads them
+            const uint32_t c1 = le < ne2 ? rb.cloc[g1] : 0, c2 = le < ne2 ? rb.cloc[g2] : 0;
+            bt.fec.push_back(c1 | (c2 << 15) | ((uint32_t)(t.emask[e] ? 1 : 0) << 30));
+            bt.elh.push_back(t.flh[e]);
+            bt.efh.push_back(t.ffh[e]);
+            bt.fidc.push_back(t.inv_dc[e]);
+            if (le >= rb.ne[0] && t.emask[e] && r[14]) {
+                out_e[e] = 1;
+                read(pid[g1]);
+            }
+        }
+        const size_t cb = bt.cflag.size();
+        bt.cflag.resize(cb + nc3);
+        bt.fcen.resize(3 * (cb + nc3));
+        bt.cS.resize(6 * (cb + nc3));
+        bt.cia.resize(cb + nc3);
+        for (int lc = 0; lc < nc3; ++lc) {
+            const int i = rb.cells[lc], n = t.cell_nedges[i];
+            bt.cH.push_back(t.H[i]);
+            bt.cflag[cb + lc] = t.cmask[i] ? 1 : 0;
+            bt.cia[cb + lc] = t.fia[i];
+            for (int j = 0; j < 6; ++j) bt.cS[6 * cb + (size_t)j * nc3 + lc] = t.fS[(size_t)j * C + i];
+            uint32_t w[6];
+            for (int j = 0; j < 6; ++j) {
+                // missing slots name the zero entry past the region edges
+                const int e = t.cell_edges_t[(size_t)j * C + i];
+                if (j < n && !in_e(e)) return false;
+                w[j] = j < n ? (uint32_t)rb.eloc[e] | (t.edge_cells[2 * (size_t)e] == i ? 0u : 0x8000u) : (uint32_t)ne3;
+            }
+            for (int j = 0; j < 3; ++j) bt.fcen[3 * cb + (size_t)j * nc3 + lc] = w[2 * j] | (w[2 * j + 1] << 16);
+            if (lc >= rb.nc[0] && t.cmask[i] && r[14]) {
+                out_c[i] = 1;
+                read(pid[i]);
+            }
+        }
+    }
+    // a patch waits for the patches it reads and for those that read it, so
+    // that no buffer is overwritten while a neighbour still reads it
+    std::vector<std::vector<int32_t>> nbr(reads);
+    for (int p = 0; p < nP; ++p)
+        for (int q : reads[p]) nbr[q].push_back(p);
+    bt.resident = 1;
+    for (int p = 0; p < nP; ++p) {
+        auto &v = nbr[p];
+        std::sort(v.begin(), v.end());
+        v.erase(std::unique(v.begin(), v.end()), v.end());
+        int32_t *r = &bt.patch[(size_t)p * kBtRec];
+        r[12] = (int)bt.nbr.size();
+        r[13] = (int)v.size();
+        if (v.size() > (size_t)kFactNbrs) {  // more than one wavefront polls: one launch per substep
+            bt.resident = 0;
+            v.resize(kFactNbrs);
+            r[13] = kFactNbrs;
+        }
+        bt.nbr.insert(bt.nbr.end(), v.begin(), v.end());
+        for (int le = 0; le < r[4]; ++le)
+            if (out_e[bt.eid[r[0] + le]]) bt.fec[r[0] + le] |= 0x80000000u;
+        for (int lc = 0; lc < r[8]; ++lc)
+            if (out_c[bt.cid[r[2] + lc]]) bt.cflag[r[2] + lc] |= 2;
+    }
+    for (int active = 1; active >= 0; --active)
+        for (int p = 0; p < nP; ++p)
+            if ((bt.patch[(size_t)p * kBtRec + 14] != 0) == (active != 0)) bt.order.push_back(p), bt.nA += active;
+    if (!bt.nA) bt.resident = 0;
+    return true;
+}
+
 namespace {
 
 // The partition depends on the cell-edge topology only; meshes that share it
@@ -857,10 +1016,7 @@ uint64_t topology_hash(const sse_mesh_desc *d) {
 
 struct PartitionEntry {
     uint64_t key;
-    bool ok;
-    int nP;
-    std::vector<int32_t> pid;
-    size_t bytes;
+    BtPartition coarse, fine;
 };
 std::mutex g_part_mu;
 std::deque<PartitionEntry> g_part_cache;  // most recent first
@@ -887,14 +1043,17 @@ PartitionEntry cached_partition(const sse_mesh_desc *d) {
                 return e;
             }
     }
-    PartitionEntry e{key, false, 0, {}, 0};
-    if (bt_partition(d, e.pid, e.nP)) {
+    PartitionEntry e{key, {}, {}};
+    const size_t E = d->n_edges, C = d->n_cells;
+    auto cut = [&](int target, BtPartition &q, bool general) {
         HostBtTiles bt;
-        if (build_bt_tiles(d, e.pid, e.nP, nullptr, bt)) {
-            e.ok = true;
-            e.bytes = bt_bytes_of(bt);
-        }
-    }
+        if (!bt_partition(d, target, q.pid, q.nP) || !build_bt_tiles(d, q.pid, q.nP, nullptr, bt)) return;
+        q.ok = true;
+        q.bytes = fact_tiles_bytes(q.nP, bt.eid.size(), bt.cid.size(), E, C);
+        if (general) q.bytes = std::max(q.bytes, bt_bytes_of(bt));
+    };
+    cut(kBtPatch, e.coarse, true);
+    if (e.coarse.ok && bt_patch_cells((int)C) != kBtPatch) cut(bt_patch_cells((int)C), e.fine, false);
     std::lock_guard<std::mutex> g(g_part_mu);
     g_part_cache.push_front(e);
     if (g_part_cache.size() > kPartCache) g_part_cache.pop_back();
@@ -903,14 +1062,15 @@ PartitionEntry cached_partition(const sse_mesh_desc *d) {
 
 }  // namespace
 
-size_t bt_tiles_bytes(const sse_mesh_desc *d) { return cached_partition(d).bytes; }
+size_t bt_tiles_bytes(const sse_mesh_desc *d) {
+    const PartitionEntry e = cached_partition(d);
+    return e.coarse.bytes + e.fine.bytes;
+}
 
-bool bt_cached_partition(const sse_mesh_desc *d, std::vector<int32_t> &pid, int &nP) {
+void bt_cached_partitions(const sse_mesh_desc *d, BtPartition &coarse, BtPartition &fine) {
     PartitionEntry e = cached_partition(d);
-    if (!e.ok) return false;
-    pid.swap(e.pid);
-    nP = e.nP;
-    return true;
+    coarse = std::move(e.coarse);
+    fine = std::move(e.fine);
 }
 
 int check_topology(const sse_mesh_desc *d, std::string &err) {

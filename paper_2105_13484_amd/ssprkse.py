@@ -331,7 +331,7 @@ class DeviceState:
 
     @property
     def bt_variant(self) -> int:
-        """Barotropic loop kernels: 0 one launch per evaluation, 1 one per substep."""
+        """Barotropic loop kernels: 0 one launch per evaluation, 1 one per substep, 2 one per loop."""
         v = c_int(0)
         _check(load().sse_state_get_bt_variant(self.handle, ctypes.byref(v)))
         return int(v.value)

@@ -1,0 +1,148 @@
+"""Barotropic loops with factored reconstruction weights, and the resident
+loop (all substeps in one launch, halo exchange between neighbouring patches).
+
+The forms of the loop agree bit for bit; against the oracle one loop stays
+within 1e-12 (a substep rounds a few dozen times, so M substeps stay within
+about M x 50 x 1.1e-16 relative to the fields, 1.1e-13 for M = 20, with a
+factor 10 for the growth of rounding in zeta).  A mesh whose weights are off
+the factored form by more than rounding keeps the weight tables.
+"""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from oracle import ssprk_se as S
+from oracle.layered import Setup
+from synthetic import cases
+
+pytestmark = pytest.mark.gpu
+
+MESHES = {
+    "one_patch_hex16": lambda: cases.c1(n=16, L=2, steps=1),       # 768 edges: one workgroup, no exchange
+    "two_patches_hex20": lambda: cases.c1(n=20, L=2, steps=1),     # just past one workgroup's edges
+    "hex64": lambda: cases.c1(n=64, L=2, steps=1),                 # small patches
+    "pentagons_sphere2": lambda: cases.sphere_case(2, 2, 5, substeps=5, dt_btr=300.0),
+    "land_sphere5": lambda: cases.sphere_case(5, 2, 7, substeps=5, dt_btr=60.0),
+}
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_13484_amd import ssprkse
+    ssprkse.load()
+    return ssprkse
+
+
+def _inputs(case, seed):
+    rng = np.random.default_rng(seed)
+    c = case.mesh.cellsOnEdge
+    cm = case.cell_mask.astype(bool)
+    em = cm[c[:, 0]] & cm[c[:, 1]]
+    return (np.where(em, rng.normal(0, 0.05, case.mesh.nEdges), 0.0), np.where(cm, rng.normal(0, 0.05, case.mesh.nCells), 0.0),
+            np.where(em, rng.normal(0, 1e-5, case.mesh.nEdges), 0.0))
+
+
+def _loops(dev, case, scheme, M, inputs, variants=(0, 1, 2)):
+    out = {}
+    for v in variants:
+        _, st = dev.state_from_case(case)
+        assert st.try_bt_variant(v), dev.last_error()
+        out[v] = st.debug_barotropic_substep(scheme, M, case.params.dt / case.params.substeps * M, *inputs)
+    return out
+
+
+@pytest.mark.parametrize("name", sorted(MESHES))
+@pytest.mark.parametrize("scheme,M", [(2, 1), (3, 2), (3, 21), (2, 12)])
+def test_loop_forms_agree_and_match_the_oracle(dev, name, scheme, M):
+    case = MESHES[name]()
+    inputs = _inputs(case, 3)
+    out = _loops(dev, case, scheme, M, inputs)
+    for v in (1, 2):
+        for a, b in zip(out[0], out[v]):
+            assert np.array_equal(a, b), v
+    sub = S.barotropic_ssprk2_substep if scheme == 2 else S.barotropic_ssprk3_substep
+    want = sub(*inputs, case.params.dt / case.params.substeps * M, M, Setup.from_case(case))
+    for a, b in zip(out[2], want):
+        assert np.linalg.norm(a - b) <= 1e-12 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("scale", [1.0, 1.0 + 1e-9])
+def test_weights_off_the_factored_form_keep_their_tables(dev, scale):
+    """Some weight pairs scaled by 1 + 1e-9: every form still uses the caller's
+    weights (the oracle with the same weights, 1e-12), which the factored form
+    of the other pairs would miss by about 1e-9 x f dt."""
+    case = MESHES["hex64"]()
+    w, eoe = case.mesh.weightsOnEdge.copy(), case.mesh.edgesOnEdge
+    w[(eoe + np.arange(len(eoe))[:, None]) % 7 == 0] *= scale
+    case = replace(case, mesh=replace(case.mesh, weightsOnEdge=w, fEdge=case.mesh.fEdge * 50))
+    inputs = _inputs(case, 4)
+    # the persistent loop of such a mesh holds the weight tables: it fits here too
+    out = _loops(dev, case, 3, 10, inputs)
+    want = S.barotropic_ssprk3_substep(*inputs, case.params.dt / case.params.substeps * 10, 10, Setup.from_case(case))
+    for v in (0, 1, 2):
+        for a, b in zip(out[v], want):
+            assert np.linalg.norm(a - b) <= 1e-12 * np.linalg.norm(b), v
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_resident_batch_equals_alone(dev, precision):
+    """Members of uneven size and M share one launch per loop (few launches a
+    step), and step to the bits they reach alone with any form."""
+    import torch
+    stream = torch.cuda.Stream()
+    specs = [(12, 5, 12), (24, 66, 25), (40, 3, 17), (16, 9, 2)]
+    cs = [cases.with_params(cases.c1(n=n, L=L, substeps=M, dt_btr=10.0, member=i, steps=2), precision=precision)
+          for i, (n, L, M) in enumerate(specs)]
+    keep, b = [], dev.Batch(stream=stream)
+    for c in cs:
+        keep.append(dev.state_from_case(c, stream=stream))
+        b.add(keep[-1][1])
+    b.compile()
+    assert b.launches_per_step() < 80          # a launch per substep would make at least 75 more
+    for _ in range(2):
+        assert b.step(1) == 0
+    for v in (1, 2):
+        for c, (_, st) in zip(cs, keep):
+            _, alone = dev.state_from_case(c, stream=stream)
+            assert alone.try_bt_variant(v)
+            assert alone.step(2) == 0
+            got, want = st.read(), alone.read()
+            for k in want:
+                assert np.array_equal(got[k], want[k]), (v, k)
+    # a member set to the other form by its caller: the whole batch follows
+    b.remove(keep[0][1])
+    assert keep[0][1].try_bt_variant(1)
+    b.add(keep[0][1])
+    b.compile()
+    assert b.launches_per_step() > 75
+
+
+def test_captured_call_equals_resident_loop(dev):
+    """A stream under graph capture takes one launch per substep; replays agree
+    with the resident loop, also after eager calls in between."""
+    import torch
+    case = MESHES["land_sphere5"]()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        _, st = dev.state_from_case(case, stream=stream)
+        assert st.try_bt_variant(2), dev.last_error()
+        ins = [torch.from_numpy(a).cuda() for a in _inputs(case, 6)]
+        eager, replay = [[torch.empty_like(t) for t in ins] for _ in range(2)]
+        st.barotropic_substep_noalloc(3, 12, 600.0, *ins, *eager)
+        stream.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            st.barotropic_substep_noalloc(3, 12, 600.0, *ins, *replay)
+        for _ in range(3):
+            for t in replay:
+                t.zero_()
+            g.replay()
+            stream.synchronize()
+            for a, b in zip(eager, replay):
+                assert torch.equal(a, b)
+            st.barotropic_substep_noalloc(3, 12, 600.0, *ins, *eager)
+            stream.synchronize()

@@ -19,9 +19,12 @@
 #include <atomic>
 #include <map>
 #include <cmath>
+#include <condition_variable>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -918,6 +921,250 @@ int download_real(const sse_state *s, double *dst, const void *src, size_t n) {
     return SSE_OK;
 }
 
+// ---- state read-out --------------------------------------------------------
+// Reading a state moves hundreds of MB to host arrays that are usually fresh
+// memory.  Copied the plain way (a pageable device copy into a temporary, then
+// row by row into the caller's order) that is one thread's work, page faults
+// included: 150 ms for the 630 MB of a 262,144-cell, 60-layer state, as long
+// as 20 of its steps.  Here pinned slots are filled by the copy engine while
+// several threads take the rows of the previous slots to their places, widened
+// from FP32 on the way.
+//
+// The slots come from a bounded pool shared by all states of the process and
+// freed with the last of them.
+class PinnedPool {
+  public:
+    static constexpr size_t kSlot = size_t(4) << 20;
+    static constexpr size_t kKept = 8;
+    static PinnedPool &get() {
+        static PinnedPool *pool = new PinnedPool;  // outlives every state, also those destroyed at exit
+        return *pool;
+    }
+    void *take() {
+        {
+            std::lock_guard<std::mutex> g(mu_);
+            if (!free_.empty()) {
+                void *p = free_.back();
+                free_.pop_back();
+                return p;
+            }
+        }
+        void *p = nullptr;
+        if (hipHostMalloc(&p, kSlot, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        return p;
+    }
+    void give(void *p) {
+        {
+            std::lock_guard<std::mutex> g(mu_);
+            if (states_ > 0 && free_.size() < kKept) {
+                free_.push_back(p);
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+    void state_made() {
+        std::lock_guard<std::mutex> g(mu_);
+        ++states_;
+    }
+    void state_gone() {
+        std::vector<void *> drop;
+        {
+            std::lock_guard<std::mutex> g(mu_);
+            if (--states_ == 0) drop.swap(free_);
+        }
+        for (void *p : drop) (void)hipHostFree(p);
+    }
+
+  private:
+    PinnedPool() { free_.reserve(kKept); }
+    std::mutex mu_;
+    std::vector<void *> free_;
+    long states_ = 0;
+};
+
+// One array to read: rows of `row` values (FP64, or FP32 when size is 4), row
+// i of the device array going to row old[i] (or i) of dst.
+struct Piece {
+    const void *dev;
+    size_t size;
+    double *dst;
+    const std::vector<int32_t> *old;
+    size_t row;
+    size_t rows() const { return old->size(); }
+};
+
+// Rows [a, b) of a piece from `src`, which holds them from row a0 on.
+void place_rows(const Piece &p, const char *src, size_t a0, size_t a, size_t b, bool identity) {
+    const size_t row = p.row;
+    if (p.size == 8) {
+        const double *s = reinterpret_cast<const double *>(src) + (a - a0) * row;
+        if (identity) {
+            std::memcpy(p.dst + a * row, s, (b - a) * row * 8);
+        } else if (row == 1) {
+            for (size_t i = a; i < b; ++i) p.dst[(*p.old)[i]] = *s++;
+        } else {
+            for (size_t i = a; i < b; ++i, s += row) std::memcpy(p.dst + (size_t)(*p.old)[i] * row, s, row * 8);
+        }
+    } else {
+        const float *s = reinterpret_cast<const float *>(src) + (a - a0) * row;
+        for (size_t i = a; i < b; ++i, s += row) {
+            double *d = p.dst + (size_t)(*p.old)[i] * row;
+            for (size_t k = 0; k < row; ++k) d[k] = s[k];
+        }
+    }
+}
+
+// No C++ exception leaves a C entry point.
+template <typename F>
+int guarded(F &&f) {
+    try {
+        return f();
+    } catch (const std::exception &e) {
+        set_error(std::string("out of host resources: ") + e.what());
+        return SSE_ENOMEM;
+    }
+}
+
+constexpr size_t kReadSlots = 4;                   // pinned slots in flight
+constexpr size_t kReadThreaded = size_t(4) << 20;  // bytes per thread that places rows
+constexpr int kReadThreads = 8;
+
+// Copies the pieces to the host behind the work enqueued on st; returns when
+// they are in place.
+int read_pieces(const std::vector<Piece> &pieces, bool identity, hipStream_t st) {
+    struct Item {
+        size_t piece, a, b, off;
+    };
+    struct Slot {
+        void *mem = nullptr;
+        hipEvent_t ev = nullptr;
+    };
+    struct Slots {
+        Slot v[kReadSlots];
+        ~Slots() {
+            for (Slot &q : v) {
+                if (q.ev) (void)hipEventDestroy(q.ev);
+                if (q.mem) PinnedPool::get().give(q.mem);
+            }
+        }
+    } slots;
+    // what goes into each slot's fill
+    std::vector<std::vector<Item>> fills;
+    size_t used = PinnedPool::kSlot, total = 0;
+    for (size_t q = 0; q < pieces.size(); ++q) {
+        const Piece &p = pieces[q];
+        const size_t rb = p.row * p.size;
+        total += p.rows() * rb;
+        for (size_t a = 0; a < p.rows();) {
+            size_t n = used < PinnedPool::kSlot ? (PinnedPool::kSlot - used) / rb : 0;
+            if (n == 0) {
+                fills.emplace_back();
+                used = 0;
+                n = PinnedPool::kSlot / rb;
+            }
+            const size_t b = std::min(p.rows(), a + n);
+            fills.back().push_back({q, a, b, used});
+            used = (used + (b - a) * rb + 7) / 8 * 8;
+            a = b;
+        }
+    }
+    const size_t nfill = fills.size(), nslot = std::min(kReadSlots, nfill);
+    for (size_t k = 0; k < nslot; ++k) {
+        slots.v[k].mem = PinnedPool::get().take();
+        if (!slots.v[k].mem) { set_error("no pinned host memory for the read-out"); return SSE_ENOMEM; }
+        SSE_HIP(hipEventCreateWithFlags(&slots.v[k].ev, hipEventDisableTiming));
+    }
+    auto fill = [&](size_t f) -> hipError_t {
+        Slot &q = slots.v[f % kReadSlots];
+        for (const Item &it : fills[f]) {
+            const Piece &p = pieces[it.piece];
+            const size_t rb = p.row * p.size;
+            const hipError_t e = hipMemcpyAsync(static_cast<char *>(q.mem) + it.off, static_cast<const char *>(p.dev) + it.a * rb,
+                                                (it.b - it.a) * rb, hipMemcpyDeviceToHost, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipEventRecord(q.ev, st);
+    };
+    // thread t of n places its share of every item of fill f
+    auto place = [&](size_t f, size_t t, size_t n) {
+        const char *mem = static_cast<const char *>(slots.v[f % kReadSlots].mem);
+        for (const Item &it : fills[f]) {
+            const size_t a = it.a + (it.b - it.a) * t / n, b = it.a + (it.b - it.a) * (t + 1) / n;
+            if (a < b) place_rows(pieces[it.piece], mem + it.off, it.a, a, b, identity);
+        }
+    };
+    hipError_t err = hipSuccess;
+    for (size_t f = 0; f < nslot && err == hipSuccess; ++f) err = fill(f);
+    // The crew sleeps while it waits: threads that spin would take the CPUs
+    // from the caller's own (an ensemble's read-outs between OpenMP loops took
+    // 13 ms longer that way).
+    std::mutex mu;
+    std::condition_variable arrived, freed;
+    size_t ready = 0;                 // fills that have arrived; SIZE_MAX: stop
+    size_t placed[kReadSlots] = {};   // threads that are done with the slot's fill
+    auto announce = [&](size_t n) {
+        {
+            std::lock_guard<std::mutex> g(mu);
+            ready = n;
+        }
+        arrived.notify_all();
+    };
+    std::vector<std::thread> crew;
+    if (total >= kReadThreaded && err == hipSuccess) {
+        const size_t want = std::min<size_t>({(size_t)kReadThreads, 1 + total / kReadThreaded,
+                                              (size_t)std::max(1u, std::thread::hardware_concurrency())});
+        try {
+            crew.reserve(want);
+            for (size_t t = 0; t < want; ++t)
+                crew.emplace_back([&, t, want] {
+                    for (size_t f = 0; f < nfill; ++f) {
+                        {
+                            std::unique_lock<std::mutex> g(mu);
+                            arrived.wait(g, [&] { return ready > f; });
+                            if (ready == SIZE_MAX) return;
+                        }
+                        place(f, t, want);
+                        std::lock_guard<std::mutex> g(mu);
+                        if (++placed[f % kReadSlots] == want) freed.notify_one();
+                    }
+                });
+        } catch (...) {  // not enough threads: this one does it all
+            announce(SIZE_MAX);
+            for (auto &th : crew) th.join();
+            crew.clear();
+        }
+    }
+    for (size_t f = 0; f < nfill && err == hipSuccess; ++f) {
+        err = hipEventSynchronize(slots.v[f % kReadSlots].ev);
+        if (err != hipSuccess) break;
+        if (crew.empty()) place(f, 0, 1);
+        else announce(f + 1);
+        // the slot of an earlier fill is filled again once its rows are placed;
+        // meanwhile the next copies stay in flight
+        const size_t back = crew.empty() ? 0 : kReadSlots / 2;
+        if (f >= back && f - back + nslot < nfill) {
+            if (!crew.empty()) {
+                size_t &done = placed[(f - back) % kReadSlots];
+                std::unique_lock<std::mutex> g(mu);
+                freed.wait(g, [&] { return done == crew.size(); });
+                done = 0;
+            }
+            err = fill(f - back + nslot);
+        }
+    }
+    if (err != hipSuccess) announce(SIZE_MAX);
+    for (auto &th : crew) th.join();
+    if (err != hipSuccess) {
+        (void)hipStreamSynchronize(st);  // no copy into a slot that is given back
+        return hip_fail(err, "read-out");
+    }
+    return SSE_OK;
+}
+
 #define SSE_TRY(call)               \
     do {                            \
         int _rc = (call);           \
@@ -1005,7 +1252,8 @@ extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t byt
     const sse_mesh_desc *d0 = d;  // the caller's numbering
     MeshOrder ord;
     locality_order(d, kPatchCells, ord);
-    if (local_share(d, nullptr) >= local_share(d, &ord)) identity_order(d, ord);
+    const bool identity = local_share(d, nullptr) >= local_share(d, &ord);
+    if (identity) identity_order(d, ord);
     PermutedDesc pd;
     permute_desc(d, ord, pd);
     // Reconstruction stencils in canonical two-cell order when the mesh
@@ -1095,6 +1343,7 @@ extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t byt
     m->cells_on_edge = t.edge_cells;
     m->cell_old = ord.cell_old;
     m->edge_old = ord.edge_old;
+    m->identity = identity;
     // Gather lists of the LDS-staged edge pass for tiles of 8, 16 and 32
     // edges: space is reserved here, the lists are built when a state first
     // selects the variant (most runs never do).
@@ -1306,6 +1555,7 @@ extern "C" int sse_state_create(const sse_mesh *m, const sse_params *p, void *de
         delete s;
         return hip_fail(hipGetLastError(), "clearing the substep counters");
     }
+    PinnedPool::get().state_made();
     *out = s;
     return SSE_OK;
 }
@@ -1377,6 +1627,7 @@ extern "C" int sse_state_destroy(sse_state *s) {
     if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
     for (auto e : s->events) (void)hipEventDestroy(e);
     delete s;
+    PinnedPool::get().state_gone();
     return SSE_OK;
 }
 
@@ -1498,11 +1749,7 @@ extern "C" int sse_read_tracer(const sse_state *s, double *T) {
     if (!s->p.tracer || !s->tracer_set) { set_error("the state carries no temperature"); return SSE_ESTATE; }
     const sse_mesh *m = s->mesh;
     const size_t L = s->p.n_layers;
-    std::vector<double> ti((size_t)m->C * L);
-    SSE_HIP(hipMemcpyAsync(ti.data(), s->w.Tn, ti.size() * 8, hipMemcpyDeviceToHost, s->stream));
-    SSE_HIP(hipStreamSynchronize(s->stream));
-    rows_to_user(ti.data(), T, m->cell_old, L);
-    return SSE_OK;
+    return guarded([&] { return read_pieces({{s->w.Tn, 8, T, &m->cell_old, L}}, m->identity, s->stream); });
 }
 
 extern "C" int sse_step_async(sse_state *s, int32_t n) {
@@ -1570,18 +1817,14 @@ extern "C" int sse_read_state(const sse_state *cs, double *h, double *u, double 
     const sse_mesh *m = cs->mesh;
     const size_t L = cs->p.n_layers;
     const Work &w = cs->w;
-    hipStream_t st = cs->stream;
-    std::vector<double> hi(h ? m->C * L : 0), ui(u ? m->E * L : 0), zi(zeta ? m->C : 0), bi(ubar ? m->E : 0);
-    if (h) SSE_HIP(hipMemcpyAsync(hi.data(), w.Hs, hi.size() * 8, hipMemcpyDeviceToHost, st));
-    if (u) SSE_TRY(download_real(cs, ui.data(), w.U, ui.size()));
-    if (zeta) SSE_HIP(hipMemcpyAsync(zi.data(), w.zeta_n, zi.size() * 8, hipMemcpyDeviceToHost, st));
-    if (ubar) SSE_HIP(hipMemcpyAsync(bi.data(), w.ubar_n, bi.size() * 8, hipMemcpyDeviceToHost, st));
-    SSE_HIP(hipStreamSynchronize(st));
-    if (h) rows_to_user(hi.data(), h, m->cell_old, L);
-    if (u) rows_to_user(ui.data(), u, m->edge_old, L);
-    if (zeta) rows_to_user(zi.data(), zeta, m->cell_old, 1);
-    if (ubar) rows_to_user(bi.data(), ubar, m->edge_old, 1);
-    return SSE_OK;
+    return guarded([&] {
+        std::vector<Piece> v;
+        if (u) v.push_back({w.U, cs->rs, u, &m->edge_old, L});
+        if (h) v.push_back({w.Hs, 8, h, &m->cell_old, L});
+        if (zeta) v.push_back({w.zeta_n, 8, zeta, &m->cell_old, 1});
+        if (ubar) v.push_back({w.ubar_n, 8, ubar, &m->edge_old, 1});
+        return read_pieces(v, m->identity, cs->stream);
+    });
 }
 
 extern "C" int sse_profile_enable(sse_state *s, int class_mask) {

@@ -229,6 +229,7 @@ struct sse_mesh {
     // Internal (locality) numbering: entity i of the device arrays is entity
     // cell_old[i] / edge_old[i] of the caller's numbering.
     std::vector<int32_t> cell_old, edge_old;
+    bool identity = false;                  // both are the identity
     std::vector<int32_t> cells_on_edge;     // host copy (for debug helpers)
     // Gather lists of the LDS-staged edge pass (T = 8, 16, 32 edges per
     // tile), built and uploaded into their reserved part of the mesh buffer

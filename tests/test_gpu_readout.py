@@ -1,0 +1,49 @@
+"""State read-out: what was set comes back in the caller's order, bit for bit,
+for read-outs of one pinned slot and of many, with and without renumbering."""
+import numpy as np
+import pytest
+
+from synthetic import cases
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_13484_amd import ssprkse
+    ssprkse.load()
+    return ssprkse
+
+
+@pytest.mark.parametrize("name,make", [
+    ("hex8, one layer", lambda L: cases.c1(n=8, L=L, steps=1)),                                    # a few kB
+    ("sphere4", lambda L: cases.sphere_case(4, L, 5, substeps=5, dt_btr=60.0)),                    # renumbered
+    ("sphere6", lambda L: cases.sphere_case(6, L, 5, substeps=5, dt_btr=60.0, land_fraction=0.0)),  # many slots
+    ("hex200", lambda L: cases.c1(n=200, L=L, steps=1)),                                           # many, as numbered
+])
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("L", [1, 41])
+def test_read_returns_what_was_set(dev, name, make, precision, L):
+    case = cases.with_params(make(L), precision=precision, tracer=1)
+    rng = np.random.default_rng(1)
+    c, sea = case.mesh.cellsOnEdge, case.cell_mask.astype(bool)
+    wet = sea[c[:, 0]] & sea[c[:, 1]]
+    u = np.where(wet[:, None], rng.normal(0, 0.1, case.u.shape), 0.0)
+    h = case.h * (1 + 1e-4 * rng.random(case.h.shape))
+    T = np.where(sea[:, None], rng.normal(10, 1, case.h.shape), 0.0)
+    dm = dev.DeviceMesh(case.mesh, case.H, case.cell_mask)
+    st = dev.DeviceState(dm, case.params)
+    st.init(h, u, case.rho, case.h_ref)
+    st.set_tracer(T)
+    for _ in range(2):
+        got = st.read()
+        assert np.array_equal(got["h"], h)
+        assert np.array_equal(got["u"], u if precision == 0 else u.astype(np.float32).astype(np.float64))
+        assert np.array_equal(st.read_tracer(), T)
+        assert np.allclose(got["zeta"], np.where(sea, h.sum(1) - case.H, 0.0), rtol=0, atol=1e-9)
+        he = 0.5 * (h[c[:, 0]] + h[c[:, 1]])
+        want = np.where(wet, (he * got["u"]).sum(1) / np.where(wet, he.sum(1), 1.0), 0.0)
+        assert np.allclose(got["ubar"], want, rtol=0, atol=1e-12)

@@ -80,10 +80,10 @@ def kernel_bytes(cls, C, E, V, L, b=8.0, bt_tiled=True):
 
 def intermediate_bytes(cls, C, E, V, L, b=8.0):
     """Bytes a launch moves beyond the ideal-fusion count: for the edge pass
-    the intermediates that the cell and vertex passes write for it (K - nu
-    div u and w at cells, the relative vorticity at vertices), read back."""
+    the intermediates that the cell part writes for it (the shares of both
+    cells at edges, w at cells), read back."""
     if cls == "fe_edge":
-        return b * L * (2 * C + V)
+        return b * L * (2 * E + C)
     return 0.0
 
 
@@ -153,9 +153,10 @@ def cpu_baseline(n=128, steps=4):
 
 
 def gather_only(torch, st, E, L, reps=10):
-    """The direct edge pass's 30 column gathers per edge without its
-    arithmetic (sse_debug_edge_gathers), timed with HIP events on the state's
-    stream: the time its memory accesses alone take at its access pattern."""
+    """The edge pass's 10 column gathers per edge (its split form, which this
+    mesh's factored weights take) without its arithmetic
+    (sse_debug_edge_gathers), timed with HIP events on the state's stream:
+    the time its memory accesses alone take at its access pattern."""
     stream = torch.cuda.current_stream()
     ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     st.debug_edge_gathers()
@@ -167,10 +168,10 @@ def gather_only(torch, st, E, L, reps=10):
     torch.cuda.synchronize()
     ms = ev0.elapsed_time(ev1) / reps
     rs = 8 if int(st.params.precision) == 0 else 4
-    # u, u^n, K - nu div u, w, the 10 stencil edges and 10 vertices in the
-    # state's real type; h and rho at both cells in FP64
-    nbytes = float(E) * L * (26 * rs + 4 * 8)
-    return {"gather_only_launch_ms": ms, "columns_gathered_per_edge": 30,
+    # u, u^n, the shares of both cells and their w in the state's real type;
+    # h and rho at both cells in FP64
+    nbytes = float(E) * L * (6 * rs + 4 * 8)
+    return {"gather_only_launch_ms": ms, "columns_gathered_per_edge": 10,
             "gathered_bytes_per_launch": nbytes, "gathered_gbs": nbytes / (ms * 1e-3) / 1e9}
 
 

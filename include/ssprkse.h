@@ -237,7 +237,11 @@ int sse_profile_read(sse_state *s, int32_t *launches, double *milliseconds);
  * 0, 1, 2: the operands of tiles of 8, 16 or 32 consecutive edges are
  * first staged in LDS.  SSE_EINVAL if the variant is unknown or does not fit
  * this mesh (a tile list longer than 255 columns) or the device's LDS for the
- * state's layer count and precision.  The default is -1.  The first
+ * state's layer count and precision.  The default is -1.  On meshes whose
+ * tangential weights factor by cell (the TRiSK weights of any area split) the
+ * pass runs as a cell part that writes each edge's two shares and an edge
+ * part that joins them, which sums in another order than the stencil; there
+ * 0, 1 and 2 are accepted and refused as elsewhere and run as -1.  The first
  * selection of a tiled variant on a mesh builds its gather lists on the host
  * and uploads them (on the state's stream, synchronously) into space the
  * mesh buffer reserves for them.  Applies to subsequent steps; the autotuner
@@ -360,7 +364,8 @@ int sse_debug_barotropic_substep(sse_state *s, int32_t scheme, int32_t M, double
  * returns without waiting) one launch that gathers, for every edge, the same
  * layer columns the direct edge pass reads (u and u^n at the edge, h, rho,
  * K - nu_h div u and w at its two cells, its 10 stencil edges and the
- * vorticity of the 10 vertices of their chains; Algorithm 1's operands) from
+ * vorticity of the 10 vertices of their chains; where the pass is split, the
+ * edge's two shares in place of the last three; Algorithm 1's operands) from
  * the state's current arrays and writes their sum into a stage buffer that
  * every step overwrites before reading.  The state steps on unchanged.
  * SSE_EINVAL without canonical stencils, above 64 layers or with arrays of

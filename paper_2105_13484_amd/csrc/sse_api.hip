@@ -72,8 +72,11 @@ void *scratch_address(int dev) {
 // Device workspace of one state.  Arrays marked R hold the mode's real type.
 struct Work {
     void *U, *T1, *T2;                       // R [E][L]: u^n and two stage buffers
-    void *B, *Wt;                            // R [C][L]: K - nu_h div u, w at layer tops
+    void *Wt, *B;                            // R [C][L]: w at layer tops, K - nu_h div u
     void *Z;                                 // R [V][L]: relative vorticity
+    void *GB;                                // R [E][L]: the second cells' shares of the split pass; they
+                                             // take the place of B and Z (an array of their own in
+                                             // biharmonic runs, which need Z)
     void *bt_u1, *bt_uh, *bt_ua, *bt_uo;     // [E] substep stages, loop input / output, in the loop's type
     void *bt_z1, *bt_zh, *bt_za, *bt_zo;     // [C]
     double *Hs, *H1, *H2, *frac, *rho;       // [C][L]
@@ -113,7 +116,7 @@ size_t workspace_bytes(int C, int E, int V, int L, size_t rs, size_t bs, int hdi
     if (tracer) b += 3 * align_up((size_t)C * L * 8);
     b += align_up((size_t)E * rs);  // ubar_r, last
     if (hdiff == SSE_HDIFF_DEL4)
-        b += align_up((size_t)E * L * rs) + 2 * align_up((size_t)C * L * rs) + align_up((size_t)V * L * rs);
+        b += 2 * align_up((size_t)E * L * rs) + 2 * align_up((size_t)C * L * rs) + align_up((size_t)V * L * rs);
     b += kR3E * align_up((size_t)E * L * rs);
     b += kR3C * align_up((size_t)C * L * rs);
     b += kR3V * align_up((size_t)V * L * rs);
@@ -137,9 +140,10 @@ Work carve(void *buf, int C, int E, int V, int L, size_t rs, size_t bs, int hdif
     Work w{};
     void **r3e[] = {&w.U, &w.T1, &w.T2};
     for (auto q : r3e) *q = take((size_t)E * L * rs);
-    void **r3c[] = {&w.B, &w.Wt};
+    void **r3c[] = {&w.Wt, &w.B};
     for (auto q : r3c) *q = take((size_t)C * L * rs);
     w.Z = take((size_t)V * L * rs);
+    w.GB = w.B;
     void **r2e[] = {&w.bt_u1, &w.bt_uh, &w.bt_ua, &w.bt_uo};
     for (auto q : r2e) *q = take((size_t)E * bs);
     void **r2c[] = {&w.bt_z1, &w.bt_zh, &w.bt_za, &w.bt_zo};
@@ -159,6 +163,7 @@ Work carve(void *buf, int C, int E, int V, int L, size_t rs, size_t bs, int hdif
         w.L1 = take((size_t)E * L * rs);
         w.D2 = take((size_t)C * L * rs);
         w.Z2 = take((size_t)V * L * rs);
+        w.GB = take((size_t)E * L * rs);
     }
     w.Tn = w.T1s = w.Th = nullptr;
     if (tracer) {
@@ -238,7 +243,7 @@ bool all_finite(const double *x, size_t n) {
 // key (seq = launch site in step order; j = substep evaluation inside a
 // barotropic loop), so that the same launch of every member can be merged
 // into one batched launch.
-enum class Kind : int { FE_CELL, FE_VERTEX, FE_EDGE, BT_EVAL, BT_LOOP, BT_TILE, THICK, THICK_ISO, RECON, ASSEMBLE, CONV_DF, CONV_FD, LAP, DIV, TRACER };
+enum class Kind : int { FE_CELL, FE_SPLIT, FE_VERTEX, FE_EDGE, BT_EVAL, BT_LOOP, BT_TILE, THICK, THICK_ISO, RECON, ASSEMBLE, CONV_DF, CONV_FD, LAP, DIV, TRACER };
 
 struct RecEntry {
     Kind kind;
@@ -384,6 +389,21 @@ bool stream_capturing(hipStream_t st) {
     return c != hipStreamCaptureStatusNone;
 }
 
+// The forward-Euler pass is split by cells: the mesh has the records, and B and
+// Z together hold the second cells' shares (V + C >= E on the closed surfaces
+// TRiSK meshes cover).
+bool split_pass(const sse_state *s) {
+    const sse_mesh *m = s->mesh;
+    return m->cell_rec && (s->p.hdiff == SSE_HDIFF_DEL4 || (size_t)m->V + m->C >= (size_t)m->E);
+}
+
+template <typename R>
+const CellRec<R> *cell_rec_of(const sse_mesh *m);
+template <>
+const CellRec<double> *cell_rec_of<double>(const sse_mesh *m) { return m->cell_rec; }
+template <>
+const CellRec<float> *cell_rec_of<float>(const sse_mesh *m) { return m->cell_rec_f; }
+
 // ---- building blocks -------------------------------------------------------
 template <typename Tin, typename Tout>
 void convert(sse_state *s, const Tin *src, Tout *dst, size_t n);
@@ -397,18 +417,31 @@ void fe_pass(sse_state *s, const R *X, const double *add, const double *sub, con
     Work &w = s->w;
     const bool zstar = p.vcoord == SSE_ZSTAR;
     const int nk = nk_of(p.n_layers);
-    const bool del4 = p.hdiff == SSE_HDIFF_DEL4;
+    const bool del4 = p.hdiff == SSE_HDIFF_DEL4, split = split_pass(s);
+    const int evar = fe_edge_variant(m, p.n_layers, p.vmix, del4, split) | (s->edge_variant == -2 ? 8 : 0);
     // the FP32 edge pass reads the barotropic velocity of every stencil edge:
     // rounded to FP32 once here instead of in every gather
-    if constexpr (sizeof(R) == 4) convert<double, float>(s, add ? add : sub, rp<float>(w.ubar_r), (size_t)m.E);
-    {
+    if constexpr (sizeof(R) == 4) {
+        if (!split) convert<double, float>(s, add ? add : sub, rp<float>(w.ubar_r), (size_t)m.E);
+        else if (s->rec) s->rec->seq++;
+    }
+    if (split) {
+        ProfScope ps(s, SSE_PROF_FE_CELL);
+        FESplitArgs<R> a{m.C, p.n_layers, cell_rec_of<R>(s->mesh), m.cmask, X, add, add ? nullptr : sub, h,
+                         zstar ? w.frac : nullptr, del4 ? 0.0 : p.nu_h, out, rp<R>(w.GB), del4 ? rp<R>(w.D1) : nullptr,
+                         rp<R>(w.Wt), w.Kbot};
+        if (s->rec) record(s, Kind::FE_SPLIT, a, nk, add != nullptr, col_blocks(m.C, edge_geom(s->geom, nk)), -1, evar & 8);
+        else launch_fe_split<R>(a, (evar & 8) != 0, s->geom, s->stream);
+    } else {
         ProfScope ps(s, SSE_PROF_FE_CELL);
         FECellArgs<R> a{m, p.n_layers, X, add, h, zstar ? w.frac : nullptr, del4 ? 0.0 : p.nu_h, rp<R>(w.B),
                         del4 ? rp<R>(w.D1) : nullptr, rp<R>(w.Wt), w.Kbot};
         if (s->rec) record(s, Kind::FE_CELL, a, nk, add != nullptr, col_blocks(m.C, s->geom));
         else launch_fe_cell<R>(a, s->geom, s->stream);
     }
-    {
+    if (split && !del4) {
+        if (s->rec) s->rec->seq++;
+    } else {
         ProfScope ps(s, SSE_PROF_FE_VERTEX);
         FEVertexArgs<R> a{m, p.n_layers, X, add, rp<R>(w.Z)};
         if (s->rec) record(s, Kind::FE_VERTEX, a, nk, add != nullptr, col_blocks(wave_groups<kVertexCols>(m.V), s->geom));
@@ -442,7 +475,7 @@ void fe_pass(sse_state *s, const R *X, const double *add, const double *sub, con
         if constexpr (sizeof(R) == 4) a.ubar_r = rp<R>(w.ubar_r);
         a.h = h;
         a.rho = w.rho;
-        a.B = rp<R>(w.B);
+        a.B = split ? rp<R>(w.GB) : rp<R>(w.B);
         a.Wtop = rp<R>(w.Wt);
         a.Kbot = w.Kbot;
         a.Z = rp<R>(w.Z);
@@ -475,12 +508,11 @@ void fe_pass(sse_state *s, const R *X, const double *add, const double *sub, con
             a.Z2 = rp<R>(w.Z2);
         }
         if (s->rec)
-            record(s, Kind::FE_EDGE, a, nk, add != nullptr, col_blocks(m.E, edge_geom(s->geom, nk)), -1,
-                   fe_edge_variant(m, p.n_layers, p.vmix, del4) | (s->edge_variant == -2 ? 8 : 0));
-        else if (s->edge_variant >= 0)
+            record(s, Kind::FE_EDGE, a, nk, add != nullptr, col_blocks(m.E, edge_geom(s->geom, nk)), -1, evar);
+        else if (s->edge_variant >= 0 && !split)
             launch_fe_edge_tiled<R>(a, s->mesh->tiles[s->edge_variant], s->stream);
         else
-            launch_fe_edge<R>(a, s->geom, s->stream, s->edge_variant == -2);
+            launch_fe_edge<R>(a, evar, s->geom, s->stream);
     }
 }
 
@@ -1178,6 +1210,26 @@ int read_pieces(const std::vector<Piece> &pieces, bool identity, hipStream_t st)
 // ===========================================================================
 namespace {
 
+CellRec<float> narrow(const CellRec<double> &q) {
+    CellRec<float> f{};
+    auto copy = [](const double *from, float *to, int n) {
+        for (int i = 0; i < n; ++i) to[i] = (float)from[i];
+    };
+    copy(q.lhs, f.lhs, 6);
+    copy(q.fh, f.fh, 6);
+    copy(q.S, f.S, 6);
+    copy(q.curl, f.curl, 18);
+    copy(q.ke, f.ke, 6);
+    copy(q.rk, f.rk, 6);
+    copy(&q.ia, &f.ia, 1);
+    std::memcpy(f.own, q.own, sizeof(f.own));
+    std::memcpy(f.out, q.out, sizeof(f.out));
+    std::memcpy(f.nbr, q.nbr, sizeof(f.nbr));
+    f.n = q.n;
+    f.side = q.side;
+    return f;
+}
+
 std::vector<float> to_float(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
 
 // Uploads one set of patches in the factored form; the tables per mesh entity
@@ -1354,6 +1406,25 @@ extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t byt
         m->tiles[q].T = 0;
         cursor += tiles_bytes(d, kTileSizes[q]);
     }
+    // With factored weights no such list is ever needed: their space holds the
+    // cell records of the split pass.
+    std::vector<CellRec<double>> recs;
+    if (build_cell_recs(d, t, recs)) {
+        std::vector<CellRec<float>> recs_f(recs.size());
+        for (size_t i = 0; i < recs.size(); ++i) recs_f[i] = narrow(recs[i]);
+        const size_t n8 = recs.size() * sizeof(recs[0]), n4 = recs.size() * sizeof(recs_f[0]), at = m->tile_off[0];
+        if (at + align_up(n8) + n4 <= cursor) {
+            hipError_t e = hipMemcpyAsync(base + at, recs.data(), n8, hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = hipMemcpyAsync(base + at + align_up(n8), recs_f.data(), n4, hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e != hipSuccess) {
+                delete m;
+                return hip_fail(e, "upload of the cell records");
+            }
+            m->cell_rec = reinterpret_cast<const CellRec<double> *>(base + at);
+            m->cell_rec_f = reinterpret_cast<const CellRec<float> *>(base + at + align_up(n8));
+        }
+    }
     const size_t bt_off = cursor;
     // Patches of the tiled barotropic substeps (partitioned in the caller's
     // numbering, the same partition the device-bytes query sizes).
@@ -1445,6 +1516,16 @@ int ensure_tiles(const sse_mesh *cm, int q, hipStream_t s) {
     const sse_mesh_desc *d = &m->host_desc->d;
     if (!build_tiles(d, kTileSizes[q], ht)) {
         m->tile_state[q] = -1;
+        return SSE_OK;
+    }
+    if (m->cell_rec) {  // the split pass runs in their place: only the lists' sizes decide what is accepted
+        DevTiles &dt = m->tiles[q];
+        dt.nT = ht.nT;
+        dt.max_ue = ht.max_ue;
+        dt.max_uv = ht.max_uv;
+        dt.max_uc = ht.max_uc;
+        dt.T = ht.T;
+        m->tile_state[q] = 1;
         return SSE_OK;
     }
     char *base = static_cast<char *>(m->dev_buf);
@@ -1891,7 +1972,7 @@ extern "C" int sse_debug_edge_gathers(sse_state *s) {
     if (!s->initialized) { set_error("state not initialised"); return SSE_ESTATE; }
     const DevMesh &m = s->mesh->d;
     const int L = s->p.n_layers;
-    if (!m.chain || L > kWave || (fe_edge_variant(m, L, 0, false) & 8)) {
+    if (!m.chain || L > kWave || (fe_edge_variant(m, L, 0, false, false) & 8)) {
         set_error("the gather-only edge pass needs canonical stencils, at most 64 layers and arrays below 4 GiB");
         return SSE_EINVAL;
     }
@@ -1905,11 +1986,12 @@ extern "C" int sse_debug_edge_gathers(sse_state *s) {
         a.Un = rp<R>(w.U);
         a.h = w.Hs;
         a.rho = w.rho;
-        a.B = rp<R>(w.B);
+        const bool split = split_pass(s);
+        a.B = split ? rp<R>(w.GB) : rp<R>(w.B);
         a.Wtop = rp<R>(w.Wt);
         a.Z = rp<R>(w.Z);
         a.out = rp<R>(w.T2);
-        launch_edge_gathers<R>(a, s->geom, s->stream);
+        launch_edge_gathers<R>(a, split, s->geom, s->stream);
     };
     if (s->rs == 4) go(0.0f);
     else go(0.0);
@@ -2232,6 +2314,7 @@ void batch_enqueue(sse_batch *b, bool resident) {
                 break;
             }
             case Kind::FE_CELL: launch_fe_cell_batch<R>(bl<FECellArgs<R>>(b, op), op.nk, op.add, g, st); break;
+            case Kind::FE_SPLIT: launch_fe_split_batch<R>(bl<FESplitArgs<R>>(b, op), op.nk, op.add, op.var != 0, g, st); break;
             case Kind::FE_VERTEX: launch_fe_vertex_batch<R>(bl<FEVertexArgs<R>>(b, op), op.nk, op.add, g, st); break;
             case Kind::FE_EDGE: launch_fe_edge_batch<R>(bl<FEEdgeArgs<R>>(b, op), op.nk, op.add, op.var, g, st); break;
             case Kind::BT_EVAL:

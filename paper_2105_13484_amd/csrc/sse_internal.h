@@ -84,6 +84,26 @@ struct DevMesh {
     const int32_t *edge_old = nullptr;      // [E]
 };
 
+// Per-cell record of the split forward-Euler pass (meshes with factored
+// weights, see DevFact): what one wavefront needs for its cell's column, read
+// with scalar loads from one place.  Slots past the cell's last edge repeat its
+// first edge with zero coefficients.
+template <typename R>
+struct alignas(64) CellRec {
+    R lhs[6];       // s_b l_b / 2
+    R fh[6];        // f_b / 2
+    R S[6];         // 2 S_1 .. 2 S_5, 2 S_n
+    R curl[18];     // a quarter of the curl weights at vertex m (between edges m and m + 1): edge m,
+                    // edge m + 1, and the edge that leaves the cell there
+    R ke[6];        // l d / (4 A)
+    R rk[6];        // 2 d / l
+    R ia;           // 1 / A
+    R pad;
+    int32_t own[6], out[6], nbr[6];   // its edges, the outgoing edges at its vertices, its neighbours
+    int32_t n;
+    uint32_t side;  // bit b: the cell is the second cell of edge b
+};
+
 // Fixed-point base of the 16-bit offsets (see DevMesh).
 __host__ __device__ inline int delta_base(int x, uint32_t ratio) {
     return (int)(((unsigned long long)x * ratio) >> 16);
@@ -237,6 +257,10 @@ struct sse_mesh {
     sse::DevTiles tiles[sse::kTileVariants];
     size_t tile_off[sse::kTileVariants] = {};
     int tile_state[sse::kTileVariants] = {};  // 0 not built, 1 built, -1 not possible
+    // Records of the split forward-Euler pass, in the lists' reserved part
+    // (null: the weights do not factor; the lists are then built on demand).
+    const sse::CellRec<double> *cell_rec = nullptr;
+    const sse::CellRec<float> *cell_rec_f = nullptr;
     std::mutex tile_mu;
     std::unique_ptr<sse::PermutedDesc> host_desc;  // internal numbering, for building the lists
     sse::DevBtTiles bt;                       // patches of the tiled barotropic substeps
@@ -284,6 +308,9 @@ struct HostMeshTables {
 // kFactTol of the factored form.
 constexpr double kFactTol = 4.0e-15;
 void factor_weights(const sse_mesh_desc *d, HostMeshTables &t);
+// The cell records of a mesh with factored weights; false if some vertex has
+// no third edge.
+bool build_cell_recs(const sse_mesh_desc *d, const HostMeshTables &t, std::vector<CellRec<double>> &v);
 void build_tables(const sse_mesh_desc *d, HostMeshTables &t);
 
 struct HostTiles {

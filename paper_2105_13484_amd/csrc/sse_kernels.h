@@ -34,6 +34,26 @@ struct FECellArgs {
     double *Kbot;            // [C]
 };
 
+// Baroclinic forward Euler split by cells (factored weights): per cell and
+// layer z-star w, bottom-layer K, and for each of its edges the cell's share g
+// of the edge tendency, such that (g of c1 - g of c2) / d_e is
+// - grad(K - nu_h div u) + the vorticity flux + Coriolis - nu_h k x grad curl.
+template <typename R>
+struct FESplitArgs {
+    int C, L;
+    const CellRec<R> *rec;
+    const uint8_t *cmask;
+    const R *X;
+    const double *ubar_add, *ubar_sub;  // one of them: u = X + ubar_add, or ut = X - ubar_sub
+    const double *h;
+    const double *frac;      // z-star; null for isopycnal
+    double nu_h;
+    R *GA, *GB;              // [E][L] g of c1 and of c2
+    R *D1;                   // [C][L] div u (biharmonic runs), nullable
+    R *Wtop;                 // [C][L]
+    double *Kbot;            // [C]
+};
+
 // Baroclinic forward Euler, vertex pass: relative vorticity of u = X + ubar_add.
 template <typename R>
 struct FEVertexArgs {
@@ -309,16 +329,17 @@ int bt_blocks(int E, int C, const Geom &g);
 // Single-state launches.  The column kernels take NK from a.L and the velocity
 // form from whether ubar_add is non-null.
 template <typename R> void launch_fe_cell(const FECellArgs<R> &a, const Geom &g, hipStream_t s);
+template <typename R> void launch_fe_split(const FESplitArgs<R> &a, bool wide, const Geom &g, hipStream_t s);
 template <typename R> void launch_fe_vertex(const FEVertexArgs<R> &a, const Geom &g, hipStream_t s);
 template <typename R> void launch_lap(const LapArgs<R> &a, const Geom &g, hipStream_t s);
 template <typename R> void launch_tracer(const TracerArgs<R> &a, const Geom &g, hipStream_t s);
 template <typename R> void launch_div(const DivArgs<R> &a, const Geom &g, hipStream_t s);
-// wide: 64-bit column addressing whatever the array sizes (edge variant -2)
-template <typename R> void launch_fe_edge(const FEEdgeArgs<R> &a, const Geom &g, hipStream_t s, bool wide = false);
+// var: fe_edge_variant, with bit 3 also set for edge variant -2
+template <typename R> void launch_fe_edge(const FEEdgeArgs<R> &a, int var, const Geom &g, hipStream_t s);
 // LDS bytes the tiled edge pass needs for tile set t, L layers and type R.
 template <typename R> size_t fe_edge_tiled_lds(const DevTiles &t, int L);
 template <typename R> void launch_fe_edge_tiled(const FEEdgeArgs<R> &a, const DevTiles &t, hipStream_t s);
-template <typename R> void launch_edge_gathers(const FEEdgeArgs<R> &a, const Geom &g, hipStream_t s);
+template <typename R> void launch_edge_gathers(const FEEdgeArgs<R> &a, bool split, const Geom &g, hipStream_t s);
 void set_tiled_lds_limit(size_t bytes);
 template <typename R> void launch_bt_eval(const BTEvalArgs<R> &a, const Geom &g, hipStream_t s);
 // scheme 2 or 3; requires a.t.nP > 0 and the LDS limit set (set_tiled_lds_limit).
@@ -368,6 +389,7 @@ struct BatchLaunch {
     int blocks;
 };
 template <typename R> void launch_fe_cell_batch(const BatchLaunch<FECellArgs<R>> &b, int nk, bool add, const Geom &g, hipStream_t s);
+template <typename R> void launch_fe_split_batch(const BatchLaunch<FESplitArgs<R>> &b, int nk, bool add, bool wide, const Geom &g, hipStream_t s);
 template <typename R> void launch_fe_vertex_batch(const BatchLaunch<FEVertexArgs<R>> &b, int nk, bool add, const Geom &g, hipStream_t s);
 template <typename R> void launch_lap_batch(const BatchLaunch<LapArgs<R>> &b, int nk, const Geom &g, hipStream_t s);
 template <typename R> void launch_tracer_batch(const BatchLaunch<TracerArgs<R>> &b, int nk, const Geom &g, hipStream_t s);
@@ -381,8 +403,9 @@ Geom edge_geom(const Geom &g, int nk);
 // Template variant of the edge pass: bit 0 canonical stencils with vertex
 // chains (mesh), bit 1 implicit vertical mixing, bit 2 biharmonic viscosity
 // (parameters), bit 3 64-bit column addressing (some array of L layers per
-// entity reaches 4 GiB).
-int fe_edge_variant(const DevMesh &m, int L, int vmix, bool del4);
+// entity reaches 4 GiB), bit 4 the edge part of the split pass (then g of c1
+// is read from the output array and g of c2 from B, and Z is not used).
+int fe_edge_variant(const DevMesh &m, int L, int vmix, bool del4, bool split);
 template <typename R> void launch_fe_edge_batch(const BatchLaunch<FEEdgeArgs<R>> &b, int nk, bool add, int var, const Geom &g, hipStream_t s);
 template <typename R> void launch_bt_eval_batch(const BatchLaunch<BTEvalArgs<R>> &b, bool delta16, const Geom &g, hipStream_t s);
 // table entries (member, patch); ks and lds: the largest over the members

@@ -511,6 +511,213 @@ __device__ __forceinline__ void fe_cell_body(const FECellArgs<R> &a, int col) {
 }
 
 // ---------------------------------------------------------------------------
+// Baroclinic forward Euler split by cells (meshes with factored weights).
+//
+// The direct edge pass gathers 30 layer columns per edge, 11 GB per launch of
+// a 512 x 512 x 60 mesh, and those gathers bound it (0.87 of its 1.07 ms).
+// With factored weights the 20 columns of the reconstruction belong to the two
+// cells: one wavefront per cell loads its 6 edges, the 6 edges that leave its
+// vertices, h of itself and its neighbours (20 columns for 6 half edges, and
+// no vorticity array in between), and writes the cell's share of each edge's
+// horizontal terms.  The edge pass then reads the two shares.  On that mesh in
+// FP64 the cell, vertex and edge passes took 0.22 + 0.12 + 1.07 ms; the split
+// takes 0.55 (cells) + 0.59 (edges), in FP32 0.14 + 0.09 + 0.76 against 0.28 +
+// 0.52.  Both parts are now near the rate of HBM: 2.34 and 2.5 GB per launch
+// by the counters, 4.3 TB/s where a copy reaches 5.1.
+//
+// With x = s l u / 2, t the same of ut, f / 2, q = zeta_e / 2 (zeta_e the mean
+// of the edge's two vertex vorticities) and y = f t + q x, edge a's share of
+// d_a (Coriolis on ut + vorticity flux of u) is, as in half_sums,
+//   S_a (f_a T + q_a X + Y') + f_a (T - Yt) + q_a (X - Yx) + (Y' - Yy) - 2 y_a
+//     - S_n (f_a Pt_a + q_a Px_a + Py_a),
+// capitals the sums over the cell (Y weighted by S), P the sums before a.
+// ---------------------------------------------------------------------------
+// Layer k of the column that starts off elements into arr, through the array's
+// base and a 32-bit lane offset (arrays below 4 GiB), or (kWide) the column's
+// 64-bit base.
+template <bool kWide, typename T>
+__device__ __forceinline__ T col_ldo(const T *arr, size_t off, int k) {
+    if constexpr (kWide) return col_ld(arr + off, k);
+    const unsigned vo = (unsigned)(off * sizeof(T)) + (unsigned)k * (unsigned)sizeof(T);
+    return *(const __attribute__((address_space(1))) T *)((const global_char *)(unsigned long long)arr + vo);
+}
+template <bool kWide, typename T>
+__device__ __forceinline__ void col_sto(T *arr, size_t off, int k, T v) {
+    if constexpr (kWide) {
+        col_st(arr + off, k, v);
+    } else {
+        const unsigned vo = (unsigned)(off * sizeof(T)) + (unsigned)k * (unsigned)sizeof(T);
+        *(__attribute__((address_space(1))) T *)((global_char *)(unsigned long long)arr + vo) = v;
+    }
+}
+
+template <typename T>
+using const_ptr = const __attribute__((address_space(4))) T *;
+
+template <int NK, typename R, bool kAdd, bool kWide>
+__device__ __forceinline__ void fe_split_body(const FESplitArgs<R> &a, int i) {
+    if (i >= a.C) return;
+    const int L = a.L;
+    const size_t base = (size_t)i * L;
+    int kk[NK];
+    bool ok[NK];
+    lane_layers<NK>(L, kk, ok);
+    if (!a.cmask[i]) {
+#pragma unroll
+        for (int c = 0; c < NK; ++c)
+            if (ok[c]) {
+                a.Wtop[base + kk[c]] = R(0);
+                if (a.D1) a.D1[base + kk[c]] = R(0);
+            }
+        if (lane_id() == 0) a.Kbot[i] = 0.0;
+        return;
+    }
+    // The record through the constant address space, so that its loads stay
+    // scalar also past the stores.  They are issued in three groups, each well
+    // before its use and held there by scheduling barriers: left alone the
+    // compiler loads every coefficient where it is used, and a wavefront spends
+    // its time in a dozen scalar waits one after another.
+    const_ptr<CellRec<R>> q = (const_ptr<CellRec<R>>)(unsigned long long)(a.rec + i);
+    const double *ubar = kAdd ? a.ubar_add : a.ubar_sub;
+    int own[6];
+    const int n = q->n;
+    const unsigned side = q->side;
+    R u[6][NK], o[6][NK], hs[6][NK], fr[NK];
+    R lhs[6], ke[6], ub[6], uo[6], curl[18];
+    {
+        double hi[NK], hn[6][NK];
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            own[b] = q->own[b];
+            const size_t eb = (size_t)own[b] * L, ob = (size_t)q->out[b] * L, nb = (size_t)q->nbr[b] * L;
+#pragma unroll
+            for (int c = 0; c < NK; ++c) {
+                u[b][c] = col_ldo<kWide>(a.X, eb, kk[c]);
+                o[b][c] = col_ldo<kWide>(a.X, ob, kk[c]);
+                hn[b][c] = col_ldo<kWide>(a.h, nb, kk[c]);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NK; ++c) {
+            hi[c] = col_ldo<kWide>(a.h, base, kk[c]);
+            fr[c] = a.frac ? (R)col_ldo<kWide>(a.frac, base, kk[c]) : R(0);
+        }
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            ub[b] = (R)ubar[own[b]];
+            if constexpr (kAdd) uo[b] = (R)ubar[q->out[b]];
+        }
+#pragma unroll
+        for (int m = 0; m < 18; ++m) curl[m] = q->curl[m];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 6; ++b)
+#pragma unroll
+            for (int c = 0; c < NK; ++c) hs[b][c] = (R)(hi[c] + hn[b][c]);
+    }
+    R tot[NK], K[NK], x[6][NK], t[6][NK], z[6][NK], bern[NK], X[NK];
+#pragma unroll
+    for (int b = 0; b < 6; ++b)
+#pragma unroll
+        for (int c = 0; c < NK; ++c) {
+            t[b][c] = kAdd ? u[b][c] : u[b][c] - ub[b];
+            if constexpr (kAdd) {
+                u[b][c] += ub[b];
+                o[b][c] += uo[b];
+            }
+        }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        lhs[b] = q->lhs[b];
+        ke[b] = q->ke[b];
+    }
+    const R ia = q->ia;
+#pragma unroll
+    for (int c = 0; c < NK; ++c) {
+#pragma unroll
+        for (int m = 0; m < 6; ++m)
+            z[m][c] = curl[3 * m] * u[m][c] + curl[3 * m + 1] * u[(m + 1) % 6][c] + curl[3 * m + 2] * o[m][c];
+        if (n < 6) z[5][c] = z[4][c];   // the vertex before edge 0 of a pentagon
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    R fh[6], S[6], nr[6];
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        fh[b] = q->fh[b];
+        S[b] = q->S[b];
+        nr[b] = q->rk[b];
+    }
+#pragma unroll
+    for (int c = 0; c < NK; ++c) {
+        tot[c] = K[c] = X[c] = R(0);
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            x[b][c] = lhs[b] * u[b][c];
+            t[b][c] = lhs[b] * t[b][c];
+            K[c] += ke[b] * (u[b][c] * u[b][c]);
+            X[c] += x[b][c];
+            tot[c] += x[b][c] * hs[b][c];
+        }
+        const R divu = R(2) * ia * X[c];
+        bern[c] = K[c] - (R)a.nu_h * divu;
+        if (a.D1 && ok[c]) col_sto<kWide>(a.D1, base, kk[c], divu);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // z-star: T^h_k = -frac_k sum_l div(h u)_l, and w_k - w_{k+1} = -div_k - T^h_k
+    R w[NK];
+    if (a.frac) {
+        R src[NK];
+#pragma unroll
+        for (int c = 0; c < NK; ++c) tot[c] = ok[c] ? ia * tot[c] : R(0);
+        const R sum = col_sum<NK, kDppFor<R>>(tot);
+#pragma unroll
+        for (int c = 0; c < NK; ++c) src[c] = ok[c] ? fr[c] * sum - tot[c] : R(0);
+        col_incl_suffix<NK, kDppFor<R>>(src, w);
+    } else {
+#pragma unroll
+        for (int c = 0; c < NK; ++c) w[c] = R(0);
+    }
+#pragma unroll
+    for (int c = 0; c < NK; ++c)
+        if (ok[c]) {
+            col_sto<kWide>(a.Wtop, base, kk[c], w[c]);
+            if (kk[c] == L - 1) a.Kbot[i] = (double)K[c];
+        }
+#pragma unroll
+    for (int c = 0; c < NK; ++c) {
+        R T = R(0), Y = R(0), Yx = R(0), Yt = R(0), Yy = R(0), y[6];
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            const R qb = z[(b + 5) % 6][c] + z[b][c];
+            y[b] = fh[b] * t[b][c] + qb * x[b][c];
+            T += t[b][c];
+            Y += y[b];
+            if (b > 0) {
+                Yx += S[b - 1] * x[b][c];
+                Yt += S[b - 1] * t[b][c];
+                Yy += S[b - 1] * y[b];
+            }
+        }
+        const R Dx = X[c] - Yx, Dt = T - Yt, Dy = Y - Yy;
+        R Px = R(0), Pt = R(0), Py = R(0);
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            const R zp = z[(b + 5) % 6][c], f = fh[b], qb = zp + z[b][c];
+            R g = bern[c] + (f * Dt + (qb * Dx + Dy)) - R(2) * y[b] - ((R)a.nu_h * nr[b]) * (z[b][c] - zp);
+            if (b > 0) g += S[b - 1] * (f * T + (qb * X[c] + Y)) - S[5] * (f * Pt + (qb * Px + Py));
+            Px += x[b][c];
+            Pt += t[b][c];
+            Py += y[b];
+            if (b < n && ok[c]) {
+                R *const G = ((side >> b) & 1u) ? a.GB : a.GA;
+                col_sto<kWide>(G, (size_t)own[b] * L, kk[c], g);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Baroclinic forward Euler: vertex pass (relative vorticity of X + ubar_add)
 // ---------------------------------------------------------------------------
 template <int NK, typename R, bool kAdd, int Q>
@@ -664,7 +871,7 @@ struct EdgeOperands {
 
 // kMix: D^u is left out of the tendency and applied by the implicit column
 // solve of Algorithm 2 (the vertical-mixing form of the stage).
-template <int NK, typename R, bool kMix, bool kWide>
+template <int NK, typename R, bool kMix, bool kWide, bool kSplit = false>
 __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, int c1, int c2, double idc, double idv,
                                                const EdgeOperands<NK, R> &o) {
     const int lane = lane_id();
@@ -738,12 +945,19 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
         const int k = lane + c * kWave;
         if (k < L) {
             if (k == L - 1) taun[c] = c_drag * speed * o.u[c];
-            const R gradB = (o.B2[c] - o.B1[c]) * ridc;
-            const R curlp = (o.zb[c] - o.za[c]) * ridv;
             const R vadv = R(0.5) * (at[c] + atn[c]);
-            const R tu = -gradB + o.vor[c] - vadv + (R)pgf[c] - nu_h * curlp - (R)a.nu4 * o.lap2[c];
             const R du = kMix ? R(0) : (tau[c] - taun[c]) * (R(1) / he[c]);
-            ut1[c] = o.ut[c] + dt * (o.cor[c] + tu + du + gz);
+            if constexpr (kSplit) {
+                // B1, B2: the two cells' shares of the horizontal terms
+                const R hor = (o.B1[c] - o.B2[c]) * ridc;
+                const R tu = hor - vadv + (R)pgf[c] - (R)a.nu4 * o.lap2[c];
+                ut1[c] = o.ut[c] + dt * (tu + du + gz);
+            } else {
+                const R gradB = (o.B2[c] - o.B1[c]) * ridc;
+                const R curlp = (o.zb[c] - o.za[c]) * ridv;
+                const R tu = -gradB + o.vor[c] - vadv + (R)pgf[c] - nu_h * curlp - (R)a.nu4 * o.lap2[c];
+                ut1[c] = o.ut[c] + dt * (o.cor[c] + tu + du + gz);
+            }
         } else {
             ut1[c] = R(0);
         }
@@ -973,15 +1187,67 @@ __device__ __forceinline__ void fe_edge_body(const FEEdgeArgs<R> &a, int col) {
     fe_edge_finish<NK, R, kMix, kWide>(a, e, c1, c2, idc, idv, o);
 }
 
+// The edge part of the split pass: per edge the two shares g, h, rho and w at
+// both cells, the edge itself and u^n, ten columns in the place of thirty.
+template <int NK, typename R, bool kAdd, int kVar>
+__device__ __forceinline__ void fe_edge_split_body(const FEEdgeArgs<R> &a, int e) {
+    constexpr bool kMix = (kVar & 2) != 0;
+    constexpr bool kDel4 = (kVar & 4) != 0;
+    constexpr bool kWide = (kVar & 8) != 0;
+    const DevMesh &m = a.m;
+    if (e >= m.E) return;
+    const int L = a.L;
+    const size_t base = (size_t)e * L;
+    if (!m.emask[e]) {
+        fe_edge_dry<NK, R>(a, e);
+        return;
+    }
+    int kk[NK];
+    bool ok[NK];
+    lane_layers<NK>(L, kk, ok);
+    const int c1 = m.edge_cells[2 * e], c2 = m.edge_cells[2 * e + 1];
+    const double idc = m.inv_dc[e], idv = kDel4 ? m.inv_dv[e] : 0.0;
+    const R ub = (R)(kAdd ? a.ubar_add : a.ubar_sub)[e];
+    const size_t b1 = (size_t)c1 * L, b2 = (size_t)c2 * L;
+    EdgeOperands<NK, R> o;
+#pragma unroll
+    for (int c = 0; c < NK; ++c) {
+        const int k = kk[c];
+        const R x = col_ldv<kWide>(a.X, base, k);
+        o.u[c] = kAdd ? x + ub : x;
+        o.ut[c] = kAdd ? x : x - ub;
+        o.B1[c] = col_ldv<kWide>(a.out, base, k);
+        o.B2[c] = col_ldv<kWide>(a.B, base, k);
+        o.h1[c] = col_ldv<kWide>(a.h, b1, k);
+        o.h2[c] = col_ldv<kWide>(a.h, b2, k);
+        o.r1[c] = col_ldv<kWide>(a.rho, b1, k);
+        o.r2[c] = col_ldv<kWide>(a.rho, b2, k);
+        o.W1[c] = col_ldv<kWide>(a.Wtop, b1, k);
+        o.W2[c] = col_ldv<kWide>(a.Wtop, b2, k);
+        o.lap2[c] = R(0);
+    }
+    if constexpr (kDel4) {
+        const size_t w1 = (size_t)m.edge_verts[2 * e] * L, w2 = (size_t)m.edge_verts[2 * e + 1] * L;
+#pragma unroll
+        for (int c = 0; c < NK; ++c) {
+            const int k = kk[c];
+            const R d1 = col_ldv<kWide>(a.D2, b1, k), d2 = col_ldv<kWide>(a.D2, b2, k);
+            const R z1 = col_ldv<kWide>(a.Z2, w1, k), z2 = col_ldv<kWide>(a.Z2, w2, k);
+            o.lap2[c] = (d2 - d1) * (R)idc - (z2 - z1) * (R)idv;
+        }
+    }
+    fe_edge_finish<NK, R, kMix, kWide, true>(a, e, c1, c2, idc, idv, o);
+}
+
 // ---------------------------------------------------------------------------
 // Measurement aid: the edge pass's column loads without its arithmetic.
 // Each wavefront gathers the columns the direct edge pass reads for its edge
 // (canonical stencils, one register chunk): u and u^n at the edge, h, rho,
 // K - nu div u and w at both cells, the 10 stencil edges and the 10 chain
 // vertices, and writes their sum; a launch takes the pass's gather time at
-// its access pattern.
+// its access pattern.  kSplit: the ten columns of the split pass's edge part.
 // ---------------------------------------------------------------------------
-template <typename R>
+template <typename R, bool kSplit>
 __global__ void __launch_bounds__(1024, 8) edge_gather_kernel(FEEdgeArgs<R> a) {
     const DevMesh &m = a.m;
     const int e = column_id(m.E);
@@ -1004,18 +1270,18 @@ __global__ void __launch_bounds__(1024, 8) edge_gather_kernel(FEEdgeArgs<R> a) {
     v[3] = (R)col_ldv<false>(a.h, b2, k);
     v[4] = (R)col_ldv<false>(a.rho, b1, k);
     v[5] = (R)col_ldv<false>(a.rho, b2, k);
-    v[6] = col_ldv<false>(a.B, b1, k);
-    v[7] = col_ldv<false>(a.B, b2, k);
+    v[6] = kSplit ? col_ldv<false>(a.B, (size_t)e * L, k) : col_ldv<false>(a.B, b1, k);
+    v[7] = kSplit ? col_ldv<false>(a.out, (size_t)e * L, k) : col_ldv<false>(a.B, b2, k);
     v[8] = col_ldv<false>(a.Wtop, b1, k);
     v[9] = col_ldv<false>(a.Wtop, b2, k);
 #pragma unroll
-    for (int j = 0; j < 10; ++j) {
+    for (int j = 0; j < (kSplit ? 0 : 10); ++j) {
         v[10 + j] = col_ldv<false>(a.X, (size_t)rec[j] * L, k);
         v[20 + j] = col_ldv<false>(a.Z, (size_t)rec[10 + j] * L, k);
     }
     R sum = R(0);
 #pragma unroll
-    for (int j = 0; j < 30; ++j) sum += v[j];
+    for (int j = 0; j < (kSplit ? 10 : 30); ++j) sum += v[j];
     if (ok[0]) col_st(a.out + (size_t)e * L, k, sum);
 }
 
@@ -2609,6 +2875,21 @@ __global__ void __launch_bounds__(1024) fe_cell_batch(BatchLaunch<FECellArgs<R>>
     if (batch_entry(b.table, b.blocks, t)) fe_cell_body<NK, R, kAdd>(b.args[t.x], batch_column(t.y));
 }
 
+// Waves per SIMD of the split cell pass.  One register chunk, FP64: at 5 (96
+// VGPRs) it spills 14 registers and takes 0.78 ms per launch (512 x 512 x 60),
+// at 6 1.09, at 4 and at 3 0.55.  FP32: 0.28 at 6 and 7, 0.32 at 8.
+template <int NK, typename R>
+constexpr int split_min_waves() { return NK != 1 ? kEdge2Waves : sizeof(R) == 8 ? 4 : 6; }
+template <int NK, typename R, bool kAdd, bool kWide>
+__global__ void __launch_bounds__((NK == 1 ? 1024 : kEdge2MaxCols * kWave), (split_min_waves<NK, R>())) fe_split_kernel(FESplitArgs<R> a) {
+    fe_split_body<NK, R, kAdd, kWide>(a, column_id(a.C));
+}
+template <int NK, typename R, bool kAdd, bool kWide>
+__global__ void __launch_bounds__((NK == 1 ? 1024 : kEdge2MaxCols * kWave), (split_min_waves<NK, R>())) fe_split_batch(BatchLaunch<FESplitArgs<R>> b) {
+    int2 t;
+    if (batch_entry(b.table, b.blocks, t)) fe_split_body<NK, R, kAdd, kWide>(b.args[t.x], batch_column(t.y));
+}
+
 template <int NK, typename R, bool kAdd>
 __global__ void __launch_bounds__(1024) fe_vertex_kernel(FEVertexArgs<R> a) {
     fe_vertex_body<NK, R, kAdd, kVertexCols>(a, kVertexCols * column_id(wave_groups<kVertexCols>(a.m.V)));
@@ -2667,12 +2948,15 @@ __global__ void __launch_bounds__(1024) div_batch(BatchLaunch<DivArgs<R>> b) {
 
 template <int NK, typename R, bool kAdd, int kVar>
 __global__ void __launch_bounds__(edge_max_threads<NK>(), (edge_min_waves<NK, R, kVar>())) fe_edge_kernel(FEEdgeArgs<R> a) {
-    fe_edge_body<NK, R, kAdd, kVar>(a, column_id(a.m.E));
+    if constexpr (kVar & 16) fe_edge_split_body<NK, R, kAdd, kVar>(a, column_id(a.m.E));
+    else fe_edge_body<NK, R, kAdd, kVar>(a, column_id(a.m.E));
 }
 template <int NK, typename R, bool kAdd, int kVar>
 __global__ void __launch_bounds__(edge_max_threads<NK>(), (edge_min_waves<NK, R, kVar>())) fe_edge_batch(BatchLaunch<FEEdgeArgs<R>> b) {
     int2 t;
-    if (batch_entry(b.table, b.blocks, t)) fe_edge_body<NK, R, kAdd, kVar>(b.args[t.x], batch_column(t.y));
+    if (!batch_entry(b.table, b.blocks, t)) return;
+    if constexpr (kVar & 16) fe_edge_split_body<NK, R, kAdd, kVar>(b.args[t.x], batch_column(t.y));
+    else fe_edge_body<NK, R, kAdd, kVar>(b.args[t.x], batch_column(t.y));
 }
 
 template <int NK>
@@ -2885,9 +3169,31 @@ void launch_fe_vertex(const FEVertexArgs<R> &a, const Geom &g, hipStream_t s) {
             case 12: SSE_NK_ADD_V(NK2, ADD, 12, KERNEL, GRID, BLOCK, ARG); break;      \
             case 13: SSE_NK_ADD_V(NK2, ADD, 13, KERNEL, GRID, BLOCK, ARG); break;      \
             case 14: SSE_NK_ADD_V(NK2, ADD, 14, KERNEL, GRID, BLOCK, ARG); break;      \
-            default: SSE_NK_ADD_V(NK2, ADD, 15, KERNEL, GRID, BLOCK, ARG); break;      \
+            case 15: SSE_NK_ADD_V(NK2, ADD, 15, KERNEL, GRID, BLOCK, ARG); break;      \
+            case 16: SSE_NK_ADD_V(NK2, ADD, 16, KERNEL, GRID, BLOCK, ARG); break;      \
+            case 18: SSE_NK_ADD_V(NK2, ADD, 18, KERNEL, GRID, BLOCK, ARG); break;      \
+            case 20: SSE_NK_ADD_V(NK2, ADD, 20, KERNEL, GRID, BLOCK, ARG); break;      \
+            case 22: SSE_NK_ADD_V(NK2, ADD, 22, KERNEL, GRID, BLOCK, ARG); break;      \
+            case 24: SSE_NK_ADD_V(NK2, ADD, 24, KERNEL, GRID, BLOCK, ARG); break;      \
+            case 26: SSE_NK_ADD_V(NK2, ADD, 26, KERNEL, GRID, BLOCK, ARG); break;      \
+            case 28: SSE_NK_ADD_V(NK2, ADD, 28, KERNEL, GRID, BLOCK, ARG); break;      \
+            default: SSE_NK_ADD_V(NK2, ADD, 30, KERNEL, GRID, BLOCK, ARG); break;      \
         }                                                                              \
     } while (0)
+
+template <typename R>
+void launch_fe_split(const FESplitArgs<R> &a, bool wide, const Geom &g0, hipStream_t s) {
+    const Geom g = edge_geom(g0, a.L > kWave ? 2 : 1);
+    const dim3 grid = xcd_grid(col_blocks(a.C, g)), block = col_block(g);
+    if (wide) SSE_NK_ADD_V(a.L > kWave, a.ubar_add != nullptr, true, fe_split_kernel, grid, block, a);
+    else SSE_NK_ADD_V(a.L > kWave, a.ubar_add != nullptr, false, fe_split_kernel, grid, block, a);
+}
+template <typename R>
+void launch_fe_split_batch(const BatchLaunch<FESplitArgs<R>> &b, int nk, bool add, bool wide, const Geom &g, hipStream_t s) {
+    const dim3 grid = xcd_grid(b.blocks), block = col_block(edge_geom(g, nk));
+    if (wide) SSE_NK_ADD_V(nk == 2, add, true, fe_split_batch, grid, block, b);
+    else SSE_NK_ADD_V(nk == 2, add, false, fe_split_batch, grid, block, b);
+}
 
 template <typename R>
 void launch_tracer(const TracerArgs<R> &a, const Geom &g, hipStream_t s) {
@@ -2924,18 +3230,17 @@ void launch_div_batch(const BatchLaunch<DivArgs<R>> &b, int nk, const Geom &g, h
     else div_batch<2, R><<<xcd_grid(b.blocks), col_block(g), 0, s>>>(b);
 }
 
-int fe_edge_variant(const DevMesh &m, int L, int vmix, bool del4) {
+int fe_edge_variant(const DevMesh &m, int L, int vmix, bool del4, bool split) {
     // 32-bit column offsets cover every array the pass reads while the
     // largest (edges, vertices or cells) x L x 8 bytes stays below 4 GiB,
     // with a margin for the layer offsets
     const size_t n = (size_t)std::max(m.E, std::max(m.V, m.C));
     const bool wide = n * (size_t)L * 8 + 4096 > ((size_t)1 << 32);
-    return (m.chain ? 1 : 0) | (vmix ? 2 : 0) | (del4 ? 4 : 0) | (wide ? 8 : 0);
+    return (split ? 16 : m.chain ? 1 : 0) | (vmix ? 2 : 0) | (del4 ? 4 : 0) | (wide ? 8 : 0);
 }
 
 template <typename R>
-void launch_fe_edge(const FEEdgeArgs<R> &a, const Geom &g0, hipStream_t s, bool wide) {
-    const int var = fe_edge_variant(a.m, a.L, a.vmix, a.D2 != nullptr) | (wide ? 8 : 0);
+void launch_fe_edge(const FEEdgeArgs<R> &a, int var, const Geom &g0, hipStream_t s) {
     const Geom g = edge_geom(g0, a.L > kWave ? 2 : 1);
     SSE_NK_ADD_VAR(a.L > kWave, a.ubar_add != nullptr, var, fe_edge_kernel, xcd_grid(col_blocks(a.m.E, g)), col_block(g), a);
 }
@@ -2954,9 +3259,10 @@ void launch_fe_edge_batch(const BatchLaunch<FEEdgeArgs<R>> &b, int nk, bool add,
 }
 
 template <typename R>
-void launch_edge_gathers(const FEEdgeArgs<R> &a, const Geom &g0, hipStream_t s) {
+void launch_edge_gathers(const FEEdgeArgs<R> &a, bool split, const Geom &g0, hipStream_t s) {
     const Geom g = edge_geom(g0, 1);
-    edge_gather_kernel<R><<<xcd_grid(col_blocks(a.m.E, g)), col_block(g), 0, s>>>(a);
+    if (split) edge_gather_kernel<R, true><<<xcd_grid(col_blocks(a.m.E, g)), col_block(g), 0, s>>>(a);
+    else edge_gather_kernel<R, false><<<xcd_grid(col_blocks(a.m.E, g)), col_block(g), 0, s>>>(a);
 }
 
 template <typename R>
@@ -3235,6 +3541,8 @@ void launch_convert_batch(const BatchLaunch<ConvArgs<Tin, Tout>> &b, const Geom 
 
 #define SSE_INSTANTIATE(R)                                                                                   \
     template void launch_fe_cell<R>(const FECellArgs<R> &, const Geom &, hipStream_t);                     \
+    template void launch_fe_split<R>(const FESplitArgs<R> &, bool, const Geom &, hipStream_t);             \
+    template void launch_fe_split_batch<R>(const BatchLaunch<FESplitArgs<R>> &, int, bool, bool, const Geom &, hipStream_t); \
     template void launch_fe_vertex<R>(const FEVertexArgs<R> &, const Geom &, hipStream_t);                 \
     template void launch_lap<R>(const LapArgs<R> &, const Geom &, hipStream_t);                           \
     template void launch_tracer<R>(const TracerArgs<R> &, const Geom &, hipStream_t);                     \
@@ -3242,7 +3550,7 @@ void launch_convert_batch(const BatchLaunch<ConvArgs<Tin, Tout>> &b, const Geom 
     template void launch_div<R>(const DivArgs<R> &, const Geom &, hipStream_t);                           \
     template void launch_lap_batch<R>(const BatchLaunch<LapArgs<R>> &, int, const Geom &, hipStream_t);  \
     template void launch_div_batch<R>(const BatchLaunch<DivArgs<R>> &, int, const Geom &, hipStream_t);  \
-    template void launch_fe_edge<R>(const FEEdgeArgs<R> &, const Geom &, hipStream_t, bool);               \
+    template void launch_fe_edge<R>(const FEEdgeArgs<R> &, int, const Geom &, hipStream_t);               \
     template void launch_fe_cell_batch<R>(const BatchLaunch<FECellArgs<R>> &, int, bool, const Geom &,     \
                                           hipStream_t);                                                    \
     template void launch_fe_vertex_batch<R>(const BatchLaunch<FEVertexArgs<R>> &, int, bool, const Geom &, \
@@ -3251,7 +3559,7 @@ void launch_convert_batch(const BatchLaunch<ConvArgs<Tin, Tout>> &b, const Geom 
                                           hipStream_t);                                                    \
     template size_t fe_edge_tiled_lds<R>(const DevTiles &, int);                                           \
     template void launch_fe_edge_tiled<R>(const FEEdgeArgs<R> &, const DevTiles &, hipStream_t);           \
-    template void launch_edge_gathers<R>(const FEEdgeArgs<R> &, const Geom &, hipStream_t);                \
+    template void launch_edge_gathers<R>(const FEEdgeArgs<R> &, bool, const Geom &, hipStream_t);                \
     template void launch_bt_eval<R>(const BTEvalArgs<R> &, const Geom &, hipStream_t);                     \
     template void launch_bt_substep<R>(const BTTileArgs<R> &, int, hipStream_t);                           \
     template int bt_loop_capacity<R>(const DevBtTiles &, int, int);                                        \

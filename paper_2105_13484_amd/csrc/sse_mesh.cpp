@@ -327,6 +327,55 @@ void factor_weights(const sse_mesh_desc *d, HostMeshTables &t) {
     }
 }
 
+bool build_cell_recs(const sse_mesh_desc *d, const HostMeshTables &t, std::vector<CellRec<double>> &v) {
+    const int C = d->n_cells, me = d->max_edges;
+    if (t.fS.empty()) return false;
+    v.assign(C, CellRec<double>{});
+    for (int c = 0; c < C; ++c) {
+        CellRec<double> &q = v[c];
+        const int n = d->n_edges_on_cell[c];
+        const int32_t *ec = d->edges_on_cell + (size_t)c * me;
+        q.n = n;
+        q.ia = t.fia[c];
+        for (int b = 0; b < 6; ++b) {
+            const int e = ec[b < n ? b : 0];
+            q.own[b] = q.out[b] = e;
+            q.nbr[b] = t.cell_nbrs[(size_t)c * 6 + b];
+            q.S[b] = t.fS[(size_t)b * C + c];
+            q.ke[b] = t.cell_ke[(size_t)c * 6 + b];
+            if (b >= n) continue;
+            const bool second = d->cells_on_edge[2 * (size_t)e] != c;
+            if (second) q.side |= 1u << b;
+            q.lhs[b] = second ? -t.flh[e] : t.flh[e];
+            q.fh[b] = t.ffh[e];
+            q.rk[b] = 2.0 * d->dc_edge[e] / d->dv_edge[e];
+        }
+        for (int m = 0; m < n; ++m) {
+            const int ea = ec[m], eb = ec[(m + 1) % n];
+            int vert = -1;
+            for (int i = 0; i < 2; ++i)
+                for (int j = 0; j < 2; ++j)
+                    if (d->vertices_on_edge[2 * (size_t)ea + i] == d->vertices_on_edge[2 * (size_t)eb + j] && vert < 0)
+                        vert = d->vertices_on_edge[2 * (size_t)ea + i];
+            // the vertex between them is the end of edge m in counter-clockwise order
+            const int end = d->vertices_on_edge[2 * (size_t)ea + ((q.side >> m) & 1u ? 0 : 1)];
+            const int start = d->vertices_on_edge[2 * (size_t)eb + ((q.side >> ((m + 1) % n)) & 1u ? 1 : 0)];
+            if (vert < 0 || end != start) return false;
+            vert = end;
+            int seen = 0;
+            for (int j = 0; j < 3; ++j) {
+                const int e = t.vert_edges[(size_t)vert * 3 + j];
+                const double w = 0.25 * t.vert_curl[(size_t)vert * 3 + j];
+                if (e == ea) { q.curl[3 * m] = w; seen |= 1; }
+                else if (e == eb) { q.curl[3 * m + 1] = w; seen |= 2; }
+                else { q.curl[3 * m + 2] = w; q.out[m] = e; seen |= 4; }
+            }
+            if (seen != 7) return false;
+        }
+    }
+    return true;
+}
+
 bool build_tiles(const sse_mesh_desc *d, int T, HostTiles &t) {
     const int E = d->n_edges, me2 = d->max_edges2;
     t.T = T;

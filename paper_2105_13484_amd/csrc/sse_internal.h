@@ -354,9 +354,10 @@ bool canonical_stencils(PermutedDesc &p, std::vector<int32_t> &chain);
 // Patches of the tiled barotropic substeps, computed in the numbering of d:
 // breadth-first patches of about kBtPatch cells, split in two (in their
 // breadth-first order) until every patch's level-2 region fits the
-// workgroup (kBtEdgeSlots edges and one cell per thread).  pid[c] = patch of
-// cell c.  Returns false if no such partition exists.
-bool bt_partition(const sse_mesh_desc *d, int target, std::vector<int32_t> &pid, int &nP);
+// workgroup (kBtEdgeSlots edges and one cell per thread).  With `mask` (may be
+// NULL) no patch holds cells of both kinds.  pid[c] = patch of cell c.
+// Returns false if no such partition exists.
+bool bt_partition(const sse_mesh_desc *d, int target, const uint8_t *mask, std::vector<int32_t> &pid, int &nP);
 
 struct HostBtTiles {
     int nP = 0, ks = 0;
@@ -399,6 +400,11 @@ bool build_fact_tiles(const sse_mesh_desc *d, const std::vector<int32_t> &pid, i
 // second, where it differs, bt_patch_cells (factored form only).
 size_t bt_tiles_bytes(const sse_mesh_desc *d);
 void bt_cached_partitions(const sse_mesh_desc *d, BtPartition &coarse, BtPartition &fine);
+// The same two cut along the coast, for the factored form: ocean patches sized
+// by the ocean cells, and land patches, which take no work.  Not ok where the
+// mesh has no land, or where the cut leaves more than twice the ocean patches
+// that full ones would be (an ocean of scattered cells).
+void bt_coast_partitions(const sse_mesh_desc *d, BtPartition &coarse, BtPartition &fine);
 // Range checks of the topology tables the size queries read.
 int check_topology(const sse_mesh_desc *d, std::string &err);
 

@@ -767,6 +767,12 @@ struct RegionBuilder {
             ne[k] = (int)edges.size();
         }
     }
+    // Cut the region back to the patch itself.
+    void own_only() {
+        for (int k = 1; k <= 3; ++k) { ne[k] = ne[0]; nc[k] = nc[0]; }
+        edges.resize(ne[0]);
+        cells.resize(nc[0]);
+    }
     // The region fits the factored kernels with nt threads (one entry past the
     // region edges stays free for missing edge slots).
     bool fits_fact(int nt) const {
@@ -789,7 +795,7 @@ constexpr size_t kBtLdsMax = 160 * 1024;
 
 }  // namespace
 
-bool bt_partition(const sse_mesh_desc *d, int target, std::vector<int32_t> &pid, int &nP) {
+bool bt_partition(const sse_mesh_desc *d, int target, const uint8_t *mask, std::vector<int32_t> &pid, int &nP) {
     const int C = d->n_cells;
     pid.assign(C, -1);
     std::vector<std::vector<int32_t>> patches;
@@ -818,7 +824,7 @@ bool bt_partition(const sse_mesh_desc *d, int target, std::vector<int32_t> &pid,
             cells.push_back(c);
             for_each_neighbour(d, c, [&](int nb) {
                 if (taken[nb]) return;
-                if ((int)(cells.size() + q.size()) < target) {
+                if ((!mask || mask[nb] == mask[seed]) && (int)(cells.size() + q.size()) < target) {
                     taken[nb] = 1;
                     q.push_back(nb);
                 } else {
@@ -957,14 +963,15 @@ bool build_fact_tiles(const sse_mesh_desc *d, const std::vector<int32_t> &pid, i
     bt.nt = min_nt;
     for (int p = 0; p < nP; ++p) {
         rb.build(own[p], pid, p);
+        int32_t *r = &bt.patch[(size_t)p * kBtRec];
+        for (int c : own[p]) r[14] |= t.cmask[c] ? 1 : 0;
+        if (!r[14]) rb.own_only();  // of a land patch only the zeros of its own edges and cells are written
         const int ne2 = rb.ne[2], ne3 = rb.ne[3], nc3 = rb.nc[3];
         for (; !rb.fits_fact(bt.nt); bt.nt = kBtThreads)
             if (bt.nt == kBtThreads) return false;
-        int32_t *r = &bt.patch[(size_t)p * kBtRec];
         const size_t e0 = bt.eid.size(), c0 = bt.cid.size();
         r[0] = (int)e0; r[1] = (int)e0; r[2] = (int)c0; r[3] = (int)c0;
         for (int k = 0; k < 4; ++k) { r[4 + k] = rb.ne[k]; r[8 + k] = rb.nc[k]; }
-        for (int c : own[p]) r[14] |= t.cmask[c] ? 1 : 0;
         bt.eid.insert(bt.eid.end(), rb.edges.begin(), rb.edges.end());
         bt.cid.insert(bt.cid.end(), rb.cells.begin(), rb.cells.end());
         auto in_c = [&](int c) { return c >= 0 && rb.cst[c] == rb.stamp; };
@@ -1003,7 +1010,7 @@ bool build_fact_tiles(const sse_mesh_desc *d, const std::vector<int32_t> &pid, i
                 // missing slots name the zero entry past the region edges
                 const int e = t.cell_edges_t[(size_t)j * C + i];
                 if (j < n && !in_e(e)) return false;
-                w[j] = j < n ? (uint32_t)rb.eloc[e] | (t.edge_cells[2 * (size_t)e] == i ? 0u : 0x8000u) : (uint32_t)ne3;
+                w[j] = j < n && rb.eloc[e] < ne3 ? (uint32_t)rb.eloc[e] | (t.edge_cells[2 * (size_t)e] == i ? 0u : 0x8000u) : (uint32_t)ne3;
             }
             for (int j = 0; j < 3; ++j) bt.fcen[3 * cb + (size_t)j * nc3 + lc] = w[2 * j] | (w[2 * j + 1] << 16);
             if (lc >= rb.nc[0] && t.cmask[i] && r[14]) {
@@ -1045,12 +1052,12 @@ bool build_fact_tiles(const sse_mesh_desc *d, const std::vector<int32_t> &pid, i
 
 namespace {
 
-// The partition depends on the cell-edge topology only; meshes that share it
-// (every request on the same icosahedral level, the size query before the
-// creation of a mesh) reuse it from a small cache keyed by a hash of the
-// topology tables.
-uint64_t topology_hash(const sse_mesh_desc *d) {
-    uint64_t h = 1469598103934665603ull;
+// The partition depends on the cell-edge topology, and on the mask where it is
+// cut along the coast; meshes that share them (every request on the same
+// icosahedral level, the size query before the creation of a mesh) reuse it
+// from a small cache keyed by a hash of the tables.
+uint64_t topology_hash(const sse_mesh_desc *d, bool coast) {
+    uint64_t h = coast ? 1099511628211ull : 1469598103934665603ull;
     auto mix = [&](const void *p, size_t n) {
         const unsigned char *b = static_cast<const unsigned char *>(p);
         for (size_t i = 0; i < n; ++i) h = (h ^ b[i]) * 1099511628211ull;
@@ -1060,6 +1067,7 @@ uint64_t topology_hash(const sse_mesh_desc *d) {
     mix(d->cells_on_edge, 2 * (size_t)d->n_edges * 4);
     mix(d->edges_on_cell, (size_t)d->n_cells * d->max_edges * 4);
     mix(d->n_edges_on_cell, (size_t)d->n_cells * 4);
+    if (coast) mix(d->cell_mask, (size_t)d->n_cells);
     return h;
 }
 
@@ -1069,7 +1077,7 @@ struct PartitionEntry {
 };
 std::mutex g_part_mu;
 std::deque<PartitionEntry> g_part_cache;  // most recent first
-constexpr size_t kPartCache = 8;
+constexpr size_t kPartCache = 16;
 
 size_t bt_bytes_of(const HostBtTiles &bt) {
     auto al = [](size_t x) { return (x + kAlign - 1) / kAlign * kAlign; };
@@ -1079,9 +1087,10 @@ size_t bt_bytes_of(const HostBtTiles &bt) {
            al(SC * 6 * 8) + al(SC * 6 * 4) + al(SC);
 }
 
-// Partition of d with its table bytes (0 if d cannot be tiled), cached.
-PartitionEntry cached_partition(const sse_mesh_desc *d) {
-    const uint64_t key = topology_hash(d);
+// Partition of d with its table bytes (0 if d cannot be tiled), cached; cut
+// along the coast (whose bytes the builder of its tables counts) if asked for.
+PartitionEntry cached_partition(const sse_mesh_desc *d, bool coast) {
+    const uint64_t key = topology_hash(d, coast);
     {
         std::lock_guard<std::mutex> g(g_part_mu);
         for (auto it = g_part_cache.begin(); it != g_part_cache.end(); ++it)
@@ -1094,15 +1103,27 @@ PartitionEntry cached_partition(const sse_mesh_desc *d) {
     }
     PartitionEntry e{key, {}, {}};
     const size_t E = d->n_edges, C = d->n_cells;
+    const size_t ocean = coast ? (size_t)std::count_if(d->cell_mask, d->cell_mask + C, [](uint8_t x) { return x != 0; }) : C;
+    std::vector<uint8_t> wet;
+    if (coast)
+        for (size_t c = 0; c < C; ++c) wet.push_back(d->cell_mask[c] ? 1 : 0);
     auto cut = [&](int target, BtPartition &q, bool general) {
         HostBtTiles bt;
-        if (!bt_partition(d, target, q.pid, q.nP) || !build_bt_tiles(d, q.pid, q.nP, nullptr, bt)) return;
+        if (!bt_partition(d, target, coast ? wet.data() : nullptr, q.pid, q.nP)) return;
+        if (coast) {
+            std::vector<char> sea(q.nP, 0);
+            for (size_t c = 0; c < C; ++c) sea[q.pid[c]] |= wet[c];
+            q.ok = (size_t)std::count(sea.begin(), sea.end(), 1) <= 2 * (ocean / target + 1);
+            return;
+        }
+        if (!build_bt_tiles(d, q.pid, q.nP, nullptr, bt)) return;
         q.ok = true;
         q.bytes = fact_tiles_bytes(q.nP, bt.eid.size(), bt.cid.size(), E, C);
         if (general) q.bytes = std::max(q.bytes, bt_bytes_of(bt));
     };
     cut(kBtPatch, e.coarse, true);
-    if (e.coarse.ok && bt_patch_cells((int)C) != kBtPatch) cut(bt_patch_cells((int)C), e.fine, false);
+    const int target = bt_patch_cells((int)ocean);
+    if (e.coarse.ok && target != kBtPatch) cut(target, e.fine, false);
     std::lock_guard<std::mutex> g(g_part_mu);
     g_part_cache.push_front(e);
     if (g_part_cache.size() > kPartCache) g_part_cache.pop_back();
@@ -1112,12 +1133,21 @@ PartitionEntry cached_partition(const sse_mesh_desc *d) {
 }  // namespace
 
 size_t bt_tiles_bytes(const sse_mesh_desc *d) {
-    const PartitionEntry e = cached_partition(d);
+    const PartitionEntry e = cached_partition(d, false);
     return e.coarse.bytes + e.fine.bytes;
 }
 
 void bt_cached_partitions(const sse_mesh_desc *d, BtPartition &coarse, BtPartition &fine) {
-    PartitionEntry e = cached_partition(d);
+    PartitionEntry e = cached_partition(d, false);
+    coarse = std::move(e.coarse);
+    fine = std::move(e.fine);
+}
+
+void bt_coast_partitions(const sse_mesh_desc *d, BtPartition &coarse, BtPartition &fine) {
+    coarse = fine = BtPartition();
+    const size_t C = d->n_cells, ocean = std::count_if(d->cell_mask, d->cell_mask + C, [](uint8_t x) { return x != 0; });
+    if (ocean == 0 || ocean == C) return;
+    PartitionEntry e = cached_partition(d, true);
     coarse = std::move(e.coarse);
     fine = std::move(e.fine);
 }

@@ -207,12 +207,13 @@ template <typename R>
 struct BtResident {
     BTTileArgs<R> a;          // tables, G, F, tau, g and flux weights
     int M;
-    const R *u_in, *z_in;     // loop input (not modified)
+    const double *u_in, *z_in; // loop input (not modified); an FP32 loop rounds it as it reads it
     R *bu0, *bu1, *bz0, *bz1; // outputs of the substeps before the last, alternating
-    R *u_out, *z_out;         // the last substep's output
+    double *u_out, *z_out;    // the last substep's output
     unsigned long long *done; // [patch * kDoneStride] substeps finished, counted on from base
     int *err;                 // set when a wait runs out
     unsigned spins;           // polls before a wait runs out
+    const int32_t *eold, *cold; // the fields' numbering of the mesh's edges and cells (null: the mesh's own)
 };
 constexpr int kDoneStride = 8;  // one 64-byte line per patch
 

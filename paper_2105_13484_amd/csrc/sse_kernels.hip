@@ -2254,16 +2254,27 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
     double Fa[KS];
     uint32_t ec[kFactEdges];
     int ge[kFactEdges];
-    const R *ua = kLoop ? l->u_in : a.ua, *za = kLoop ? l->z_in : a.za;
+    // the resident loop reads and writes the step's FP64 fields (an FP32 loop
+    // rounds and widens them here: two launches each way less, 4 us apiece)
+    using IO = std::conditional_t<kLoop, double, R>;
+    const IO *ua, *za;
+    if constexpr (kLoop) {
+        ua = l->u_in;
+        za = l->z_in;
+    } else {
+        ua = a.ua;
+        za = a.za;
+    }
 #pragma unroll
     for (int s = 0; s < kFactEdges; ++s) {
         const int le = s * NT + tid;
         const bool on = le < nEin;
         const int q = e0 + (on ? le : 0);
         ge[s] = T.eid[q];
+        if (kLoop && l->eold) ge[s] = l->eold[ge[s]];
         lhv[s] = FactTab<R>::lh(T)[q];
         ec[s] = T.fec[q];
-        const R v = ua[ge[s]];
+        const R v = (R)ua[ge[s]];
         if (s < KS) {
             idc[s < KS ? s : 0] = FactTab<R>::idc(T)[q];
             Gv[s < KS ? s : 0] = (R)a.G[ge[s]];
@@ -2274,7 +2285,8 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
     }
     const bool con = tid < nCin;
     const int qc = con ? tid : 0;
-    const int gc = T.cid[c0 + qc];
+    int gc = T.cid[c0 + qc];
+    if (kLoop && l->cold) gc = l->cold[gc];
     const uint32_t cfl = T.cflag[c0 + qc];
     const bool cwet = con && (cfl & 1u) != 0;
     // byte offset of the cell's half sum on each of its edges: the edge's pair,
@@ -2291,7 +2303,7 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
         S[j] = FactTab<R>::S(T)[(size_t)6 * c0 + (size_t)j * nc[3] + qc];
     }
     const R ia = FactTab<R>::ia(T)[c0 + qc];
-    R z = za[gc], z0;
+    R z = (R)za[gc], z0;
     if (con) lds.ZH[tid] = ZetaDepth<R>{T.cH[c0 + tid], z};
     if (tid == 0) {  // the entry that missing edge slots read
         lds.XF[ne[3]] = Pair<R>{R(0), R(0)};
@@ -2318,7 +2330,7 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
         }
     };
     // Cell phase of the evaluation that produces level lvl.
-    auto cells = [&](int lvl, int comb, R *zout) {
+    auto cells = [&](int lvl, int comb, IO *zout) {
 #pragma clang fp contract(off)
         if (tid < nc[lvl + 1] && cwet) {
             const char *const xf = reinterpret_cast<const char *>(lds.XF);
@@ -2350,7 +2362,7 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
         }
     };
     // Edge phase after it: the new velocity of level lvl.
-    auto edges = [&](int lvl, int comb, R *uout) {
+    auto edges = [&](int lvl, int comb, IO *uout) {
 #pragma clang fp contract(off)
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
@@ -2372,8 +2384,14 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
 #pragma unroll 1
     for (int sub = 0; sub < nsub; ++sub) {
         const bool last = sub == nsub - 1;
-        R *uo = kLoop ? (last ? l->u_out : nullptr) : a.uo;
-        R *zo = kLoop ? (last ? l->z_out : nullptr) : a.zo;
+        IO *uo = nullptr, *zo = nullptr;
+        if constexpr (!kLoop) {
+            uo = a.uo;
+            zo = a.zo;
+        } else if (last) {
+            uo = l->u_out;
+            zo = l->z_out;
+        }
 #pragma unroll
         for (int s = 0; s < KS; ++s) u0[s] = u[s];
         z0 = z;
@@ -2445,7 +2463,7 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
     if constexpr (kLoop) {
         // after a wait that ran out the results are worthless: they come out
         // as NaN where nobody reads the error word
-        if (__hip_atomic_load(l->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 && tid < nc[0]) l->z_out[gc] = R(NAN);
+        if (__hip_atomic_load(l->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 && tid < nc[0]) l->z_out[gc] = NAN;
     }
     if (a.F) {
 #pragma unroll
@@ -2462,11 +2480,15 @@ __device__ __forceinline__ void bt_resident_body(const BtResident<R> &l, int lb,
     for (int i = T.nA + lb; i < T.nP; i += T.nA) {
         const int32_t *rec = T.patch + (size_t)T.order[i] * kBtRec;
         for (int le = threadIdx.x; le < rec[4]; le += NT) {
-            const int e = T.eid[rec[0] + le];
-            l.u_out[e] = R(0);
+            int e = T.eid[rec[0] + le];
+            if (l.eold) e = l.eold[e];
+            l.u_out[e] = 0.0;
             if (l.a.F) l.a.F[e] = 0.0;
         }
-        for (int lc = threadIdx.x; lc < rec[8]; lc += NT) l.z_out[T.cid[rec[2] + lc]] = R(0);
+        for (int lc = threadIdx.x; lc < rec[8]; lc += NT) {
+            const int c = T.cid[rec[2] + lc];
+            l.z_out[l.cold ? l.cold[c] : c] = 0.0;
+        }
     }
     bt_fact_body<R, kScheme, true, NT>(l.a, &l, T.order[lb], base);
 }

@@ -175,3 +175,46 @@ def test_patches_cut_along_any_coast(dev, kind, level, precision):
     want = S.barotropic_ssprk3_substep(*inputs, case.params.dt / case.params.substeps * 12, 12, Setup.from_case(case))
     for a, b in zip(out[2], want):
         assert np.linalg.norm(a - b) <= (4e-4 if precision else 1e-12) * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("name", ["one_patch_hex16", "hex64", "land_sphere5"])
+@pytest.mark.parametrize("variant", [0, 1, 2])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_device_arrays_in_place_or_through_scratch(dev, name, variant, precision):
+    """The loop on device arrays gives the same bits whether it works on the
+    caller's arrays (separate ones, the mesh renumbered or not) or through
+    scratch (an output that shares memory with an input or another output);
+    inputs that no output touches are left as they were."""
+    import torch
+    case = cases.with_params(MESHES[name](), precision=precision)
+    _, st = dev.state_from_case(case)
+    assert st.try_bt_variant(variant), dev.last_error()
+    inputs, dt = _inputs(case, 8), case.params.dt / case.params.substeps * 3
+    want = st.debug_barotropic_substep(3, 3, dt, *inputs)
+    E, C = case.mesh.nEdges, case.mesh.nCells
+
+    def check(outs, keep):
+        torch.cuda.synchronize()
+        for a, b in zip(outs, want):
+            assert np.array_equal(a.cpu().numpy(), b)
+        for a, b in keep:
+            assert np.array_equal(a.cpu().numpy(), b)
+
+    ins = [torch.from_numpy(a).cuda() for a in inputs]
+    outs = [torch.full_like(t, 5.0) for t in ins]
+    st.barotropic_substep_noalloc(3, 3, dt, *ins, *outs)
+    check(outs, zip(ins, inputs))
+    # adjacent views of one buffer share nothing
+    buf = torch.full((2 * E + C + 2 * E + C,), 5.0, dtype=torch.float64, device="cuda")
+    views = torch.split(buf, [E, C, E, E, C, E])
+    for v, t in zip(views, ins):
+        v.copy_(t)
+    st.barotropic_substep_noalloc(3, 3, dt, *views)
+    check(views[3:], zip(views[:3], inputs))
+    # the last output starts inside the forcing: one value of it is shared
+    buf = torch.full((2 * E,), 5.0, dtype=torch.float64, device="cuda")
+    buf[:E].copy_(ins[2])
+    st.barotropic_substep_noalloc(3, 3, dt, ins[0], ins[1], buf[:E], outs[0], outs[1], buf[E - 1:2 * E - 1])
+    check([outs[0], outs[1], buf[E - 1:2 * E - 1]], [])
+    st.barotropic_substep_noalloc(3, 3, dt, *ins, *ins)
+    check(ins, [])

@@ -501,7 +501,7 @@ void fe_pass(sse_state *s, const R *X, const double *add, const double *sub, con
         a.interp = interp;
         a.dt = p.dt;
         a.g = p.gravity;
-        a.rho0 = p.rho0;
+        a.irho0 = 1.0 / p.rho0;
         a.nu_h = p.nu_h;
         a.nu_v = p.nu_v;
         a.c_drag = p.c_drag;

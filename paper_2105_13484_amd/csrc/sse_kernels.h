@@ -94,7 +94,7 @@ struct FEEdgeArgs {
     int vmix;                 // 1: D^u by the implicit column solve (Algorithm 2)
     const R *D2, *Z2;         // div and curl of lap u (biharmonic runs), nullable
     double nu4;               // biharmonic coefficient (m^4/s); nu_h is 0 then
-    double dt, g, rho0, nu_h, nu_v, c_drag;
+    double dt, g, irho0, nu_h, nu_v, c_drag;   // irho0: 1 / rho0
 };
 
 // The FP32 pass also takes the barotropic velocity it uses rounded to FP32
@@ -133,7 +133,7 @@ struct FEEdgeArgs<float> {
     int vmix;                 // 1: D^u by the implicit column solve (Algorithm 2)
     const float *D2, *Z2;     // div and curl of lap u (biharmonic runs), nullable
     double nu4;               // biharmonic coefficient (m^4/s); nu_h is 0 then
-    double dt, g, rho0, nu_h, nu_v, c_drag;
+    double dt, g, irho0, nu_h, nu_v, c_drag;   // irho0: 1 / rho0
 };
 
 // Vector Laplacian of u at edges from div u at cells and curl u at vertices:

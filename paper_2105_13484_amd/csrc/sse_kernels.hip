@@ -104,6 +104,51 @@ __device__ __forceinline__ T lane_value(T x, int l) {
     }
 }
 
+// One butterfly step of two values at once, by the swap instructions: lanes
+// 0 - 31 hold a_i + a_{i+32}, lanes 32 - 63 b's; and across rows of 16, rows 0
+// and 2 a's sum over their two rows, rows 1 and 3 b's.
+template <typename T>
+__device__ __forceinline__ T merge32(T a, T b) {
+    constexpr int W = sizeof(T) / 4;
+    unsigned x[W], y[W];
+    __builtin_memcpy(x, &a, sizeof(T));
+    __builtin_memcpy(y, &b, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const auto v = __builtin_amdgcn_permlane32_swap(x[i], y[i], false, false);
+        x[i] = v[0];
+        y[i] = v[1];
+    }
+    __builtin_memcpy(&a, x, sizeof(T));
+    __builtin_memcpy(&b, y, sizeof(T));
+    return a + b;
+}
+template <typename T>
+__device__ __forceinline__ T merge16(T a, T b) {
+    constexpr int W = sizeof(T) / 4;
+    unsigned x[W], y[W];
+    __builtin_memcpy(x, &a, sizeof(T));
+    __builtin_memcpy(y, &b, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const auto v = __builtin_amdgcn_permlane16_swap(x[i], y[i], false, false);
+        x[i] = v[0];
+        y[i] = v[1];
+    }
+    __builtin_memcpy(&a, x, sizeof(T));
+    __builtin_memcpy(&b, y, sizeof(T));
+    return a + b;
+}
+// Sum over the 16 lanes of every row.
+template <typename T>
+__device__ __forceinline__ T row_sum(T x) {
+    x += dpp_z<kDppRowRor + 8>(x);
+    x += dpp_z<kDppRowRor + 4>(x);
+    x += dpp_z<kDppQuadXor2>(x);
+    x += dpp_z<kDppQuadXor1>(x);
+    return x;
+}
+
 // Sum over the 64 lanes as a butterfly: every lane adds the value of lane
 // i ^ 32, then i ^ 16, i ^ 8, i ^ 4, i ^ 2, i ^ 1; the result is the pairwise
 // halving sum, the same bits in both forms.  (DPP: after the i ^ 8 step the
@@ -118,12 +163,23 @@ __device__ __forceinline__ T wave_sum(T x) {
     } else {
         x += __shfl_xor(x, 32, kWave);
         x += __shfl_xor(x, 16, kWave);
-        x += dpp_z<kDppRowRor + 8>(x);
-        x += dpp_z<kDppRowRor + 4>(x);
-        x += dpp_z<kDppQuadXor2>(x);
-        x += dpp_z<kDppQuadXor1>(x);
-        return lane_value(x, 0);
+        return lane_value(row_sum(x), 0);
     }
+}
+
+// The sums of two columns in one butterfly, the same bits as one each.
+template <int NK, typename T>
+__device__ __forceinline__ void col_sum2(const T (&a)[NK], const T (&b)[NK], T &sa, T &sb) {
+    T x = a[0], y = b[0];
+#pragma unroll
+    for (int c = 1; c < NK; ++c) {
+        x += a[c];
+        y += b[c];
+    }
+    x = merge32(x, y);
+    x = row_sum(merge16(x, x));
+    sa = lane_value(x, 0);
+    sb = lane_value(x, 32);
 }
 
 // Inclusive scan over the lanes.  DPP: steps of 1, 2, 4, 8 inside each row,
@@ -347,8 +403,6 @@ __device__ __forceinline__ float fmadd(float a, float b, float c) { return __bui
 // precision p: 1 - 3 RN(1/3) is 2^-54 in FP64 and 2^-25 in FP32 (and RN(1/6)
 // is RN(1/3) / 2).  Valid while the quotient and the residual stay normal
 // (|x / d| above about 2^-960 in FP64, 2^-100 in FP32); x = -0 gives +0.
-// (Divisions by the run's dt and rho0 done this way, with host reciprocals,
-// made the edge pass slower, so those stay divisions.)
 template <typename T>
 __device__ __forceinline__ T div_by_near(T x, T d, T r) {
     const T q = x * r;
@@ -867,7 +921,37 @@ struct EdgeOperands {
     double h1[NK], h2[NK], r1[NK], r2[NK];
     R cor[NK], vor[NK];
     R lap2[NK];   // lap(lap u) (biharmonic runs; zero otherwise)
+    // split pass: u^n of the stage combination, and the two cells' scalars
+    R un[NK];
+    double K1, K2, z1, z2, H1, H2, ubn;
 };
+
+// 1 / x of a layer thickness: the hardware reciprocal refined to the last
+// place in three (FP64: five) instructions, where the division takes eleven.
+template <typename R>
+__device__ __forceinline__ R recip(R x) {
+    R r;
+    if constexpr (sizeof(R) == 4) {
+        r = __builtin_amdgcn_rcpf(x);
+    } else {
+        r = __builtin_amdgcn_rcp(x);
+        r = fmadd(fmadd(-x, r, R(1)), r, r);
+    }
+    return fmadd(fmadd(-x, r, R(1)), r, r);
+}
+
+// sqrt(x) rounded to R.  FP32: one Newton step from the hardware's reciprocal
+// root is good to about 1e-15 before the rounding.
+template <typename R>
+__device__ __forceinline__ R sqrt_to(double x) {
+    if constexpr (sizeof(R) == 4) {
+        const double y = __builtin_amdgcn_rsq(x), v = x * y;
+        const double w = fmadd(fmadd(-v, v, x), 0.5 * y, v);
+        return x > 1e-300 ? (R)w : (x >= 0.0 ? R(0) : R(NAN));
+    } else {
+        return sqrt(x);
+    }
+}
 
 // kMix: D^u is left out of the tendency and applied by the implicit column
 // solve of Algorithm 2 (the vertical-mixing form of the stage).
@@ -903,8 +987,8 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
         }
         col_excl_prefix<NK, kDppFor<R>>(drh, sp);
         col_excl_suffix<NK, kDppFor<R>>(dh, ss);
-        const double dH = m.H[c2] - m.H[c1];
-        const double pgf_scale = idc / a.rho0;
+        const double dH = kSplit ? o.H2 - o.H1 : m.H[c2] - m.H[c1];
+        const double pgf_scale = idc * a.irho0;
 #pragma unroll
         for (int c = 0; c < NK; ++c) {
             const double dp = a.g * (sp[c] + 0.5 * drh[c]);
@@ -922,7 +1006,7 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
     for (int c = 0; c < NK; ++c) {
         const int k = lane + c * kWave;
         if (k >= 1 && k < L) {
-            const R dzt = (uu[c] - o.u[c]) * (R(1) / (R(0.5) * (hu[c] + he[c])));
+            const R dzt = (uu[c] - o.u[c]) * recip<R>(R(0.5) * (hu[c] + he[c]));
             const R we = R(0.5) * (o.W1[c] + o.W2[c]);
             at[c] = we * dzt;
             tau[c] = nu_v * dzt;
@@ -933,41 +1017,42 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
     }
     col_down1<NK, kDppFor<R>>(at, atn);
     col_down1<NK, kDppFor<R>>(tau, taun);
-    const R speed = (R)sqrt(a.Kbot[c1] + a.Kbot[c2]);
-    const R gz = (R)(a.g * (a.zeta[c2] - a.zeta[c1]) * idc);
+    const R speed = sqrt_to<R>(kSplit ? o.K1 + o.K2 : a.Kbot[c1] + a.Kbot[c2]);
+    const R gz = (R)(a.g * (kSplit ? o.z2 - o.z1 : a.zeta[c2] - a.zeta[c1]) * idc);
     const R dt = (R)a.dt, nu_h = (R)a.nu_h, c_drag = (R)a.c_drag;
     const R ridc = (R)idc, ridv = (R)idv;
 
+    // (lanes past the last layer run along and are cleared, rather than
+    // branched around: a branch keeps their loads from starting early)
     R ut1[NK];
     double hut1[NK], hu_in[NK];
 #pragma unroll
     for (int c = 0; c < NK; ++c) {
         const int k = lane + c * kWave;
-        if (k < L) {
-            if (k == L - 1) taun[c] = c_drag * speed * o.u[c];
-            const R vadv = R(0.5) * (at[c] + atn[c]);
-            const R du = kMix ? R(0) : (tau[c] - taun[c]) * (R(1) / he[c]);
-            if constexpr (kSplit) {
-                // B1, B2: the two cells' shares of the horizontal terms
-                const R hor = (o.B1[c] - o.B2[c]) * ridc;
-                const R tu = hor - vadv + (R)pgf[c] - (R)a.nu4 * o.lap2[c];
-                ut1[c] = o.ut[c] + dt * (tu + du + gz);
-            } else {
-                const R gradB = (o.B2[c] - o.B1[c]) * ridc;
-                const R curlp = (o.zb[c] - o.za[c]) * ridv;
-                const R tu = -gradB + o.vor[c] - vadv + (R)pgf[c] - nu_h * curlp - (R)a.nu4 * o.lap2[c];
-                ut1[c] = o.ut[c] + dt * (o.cor[c] + tu + du + gz);
-            }
+        if (k == L - 1) taun[c] = c_drag * speed * o.u[c];
+        const R vadv = R(0.5) * (at[c] + atn[c]);
+        const R du = kMix ? R(0) : (tau[c] - taun[c]) * recip<R>(he[c]);
+        R next;
+        if constexpr (kSplit) {
+            // B1, B2: the two cells' shares of the horizontal terms
+            const R hor = (o.B1[c] - o.B2[c]) * ridc;
+            const R tu = hor - vadv + (R)pgf[c] - (R)a.nu4 * o.lap2[c];
+            next = o.ut[c] + dt * (tu + du + gz);
         } else {
-            ut1[c] = R(0);
+            const R gradB = (o.B2[c] - o.B1[c]) * ridc;
+            const R curlp = (o.zb[c] - o.za[c]) * ridv;
+            const R tu = -gradB + o.vor[c] - vadv + (R)pgf[c] - nu_h * curlp - (R)a.nu4 * o.lap2[c];
+            next = o.ut[c] + dt * (o.cor[c] + tu + du + gz);
         }
+        ut1[c] = k < L ? next : R(0);
         hut1[c] = hed[c] * (double)ut1[c];
         hu_in[c] = hed[c] * (double)o.u[c];
     }
     // Column sums that feed the barotropic forcing and the reconciliation are
     // formed in FP64 in both modes.
-    const double Sh = col_sum<NK, kDppFor<R>>(hed);
-    const double G = col_sum<NK, kDppFor<R>>(hut1) / Sh / a.dt;
+    double Sh, Shut;
+    col_sum2<NK>(hed, hut1, Sh, Shut);
+    const double G = Shut / (Sh * a.dt);
     const R dtG = (R)(a.dt * G);
     R x[NK];
 #pragma unroll
@@ -997,7 +1082,7 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
 #pragma unroll
         for (int c = 0; c < NK; ++c) x[c] = (lane + c * kWave < L) ? x[c] - ubin : R(0);
     }
-    const double ubn = a.Un ? a.ubar_n[e] : 0.0;
+    const double ubn = a.Un ? (kSplit ? o.ubn : a.ubar_n[e]) : 0.0;
     R outv[NK];
     double hp[NK];
 #pragma unroll
@@ -1005,7 +1090,7 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
         const int k = lane + c * kWave;
         R utn = R(0);
         if (a.Un) {
-            const double un = (double)col_ldv<kWide>(a.Un, base, kk[c]);
+            const double un = kSplit ? (double)o.un[c] : (double)col_ldv<kWide>(a.Un, base, kk[c]);
             utn = k < L ? (R)(un - ubn) : R(0);
         }
         outv[c] = (k < L) ? combine<R>(a.comb, utn, x[c]) : R(0);
@@ -1013,8 +1098,7 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
         hp[c] = hed[c] * (a.psum_a * (double)utn + a.psum_b * (double)outv[c]);
     }
     double shu = 0.0, shp = 0.0;
-    if (a.sum_hu) shu = col_sum<NK, kDppFor<R>>(hu_in);
-    if (a.sum_hp) shp = col_sum<NK, kDppFor<R>>(hp);
+    if (a.sum_hu || a.sum_hp) col_sum2<NK>(hu_in, hp, shu, shp);
     if (lane == 0) {
         a.G[e] = G;
         a.sum_h[e] = Sh;
@@ -1189,6 +1273,14 @@ __device__ __forceinline__ void fe_edge_body(const FEEdgeArgs<R> &a, int col) {
 
 // The edge part of the split pass: per edge the two shares g, h, rho and w at
 // both cells, the edge itself and u^n, ten columns in the place of thirty.
+// Between its bytes (FP64 512 x 512 x 60: 2.5 GB a call) and about 250 vector
+// instructions per edge, a wavefront has little else to wait with, so all of
+// its loads, vector and scalar, start before the first wait: left to the
+// compiler, u^n, the shares and the cells' scalars came one after the other
+// behind the scans.  With the column sums two to a butterfly and the
+// reciprocals refined rather than divided, one call on 512 x 512 x 60 went
+// from 595 to 526 us (FP64, 4.8 TB/s) and 523 to 458 (FP32), on a level-7
+// globe from 343 to 285 and 305 to 241.
 template <int NK, typename R, bool kAdd, int kVar>
 __device__ __forceinline__ void fe_edge_split_body(const FEEdgeArgs<R> &a, int e) {
     constexpr bool kMix = (kVar & 2) != 0;
@@ -1198,24 +1290,34 @@ __device__ __forceinline__ void fe_edge_split_body(const FEEdgeArgs<R> &a, int e
     if (e >= m.E) return;
     const int L = a.L;
     const size_t base = (size_t)e * L;
-    if (!m.emask[e]) {
+    // the mask's word by a scalar load, beside the edge's cells (the table is
+    // padded to whole words)
+    const uint32_t wet = reinterpret_cast<const uint32_t *>(m.emask)[e >> 2] >> (8 * (e & 3)) & 0xffu;
+    const int c1 = m.edge_cells[2 * e], c2 = m.edge_cells[2 * e + 1];
+    if (!wet || c1 < 0) {  // (c1 is a cell; read here so that its load starts with the mask's)
         fe_edge_dry<NK, R>(a, e);
         return;
     }
     int kk[NK];
     bool ok[NK];
     lane_layers<NK>(L, kk, ok);
-    const int c1 = m.edge_cells[2 * e], c2 = m.edge_cells[2 * e + 1];
     const double idc = m.inv_dc[e], idv = kDel4 ? m.inv_dv[e] : 0.0;
     const R ub = (R)(kAdd ? a.ubar_add : a.ubar_sub)[e];
     const size_t b1 = (size_t)c1 * L, b2 = (size_t)c2 * L;
     EdgeOperands<NK, R> o;
+    o.K1 = a.Kbot[c1];
+    o.K2 = a.Kbot[c2];
+    o.z1 = a.zeta[c1];
+    o.z2 = a.zeta[c2];
+    o.H1 = m.H[c1];
+    o.H2 = m.H[c2];
+    o.ubn = (a.Un ? a.ubar_n : m.inv_dc)[e];  // (used with u^n only)
+    const R *const un = a.Un ? a.Un : a.X;
+    R x[NK];
 #pragma unroll
     for (int c = 0; c < NK; ++c) {
         const int k = kk[c];
-        const R x = col_ldv<kWide>(a.X, base, k);
-        o.u[c] = kAdd ? x + ub : x;
-        o.ut[c] = kAdd ? x : x - ub;
+        x[c] = col_ldv<kWide>(a.X, base, k);
         o.B1[c] = col_ldv<kWide>(a.out, base, k);
         o.B2[c] = col_ldv<kWide>(a.B, base, k);
         o.h1[c] = col_ldv<kWide>(a.h, b1, k);
@@ -1224,7 +1326,15 @@ __device__ __forceinline__ void fe_edge_split_body(const FEEdgeArgs<R> &a, int e
         o.r2[c] = col_ldv<kWide>(a.rho, b2, k);
         o.W1[c] = col_ldv<kWide>(a.Wtop, b1, k);
         o.W2[c] = col_ldv<kWide>(a.Wtop, b2, k);
+        o.un[c] = col_ldv<kWide>(un, base, k);
         o.lap2[c] = R(0);
+    }
+    // every load has started before the first value is waited for
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < NK; ++c) {
+        o.u[c] = kAdd ? x[c] + ub : x[c];
+        o.ut[c] = kAdd ? x[c] : x[c] - ub;
     }
     if constexpr (kDel4) {
         const size_t w1 = (size_t)m.edge_verts[2 * e] * L, w2 = (size_t)m.edge_verts[2 * e + 1] * L;

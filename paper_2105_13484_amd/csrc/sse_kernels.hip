@@ -353,6 +353,38 @@ __device__ __forceinline__ void col_shift_down(const T (&v)[NK], int s, T fill, 
     }
 }
 
+// a b + c rounded once
+__device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// 1 / x (layer thicknesses, pivots): the hardware reciprocal refined to the
+// last place in three (FP64: five) instructions, where the division takes eleven.
+template <typename R>
+__device__ __forceinline__ R recip(R x) {
+    R r;
+    if constexpr (sizeof(R) == 4) {
+        r = __builtin_amdgcn_rcpf(x);
+    } else {
+        r = __builtin_amdgcn_rcp(x);
+        r = fmadd(fmadd(-x, r, R(1)), r, r);
+    }
+    return fmadd(fmadd(-x, r, R(1)), r, r);
+}
+
+// o_k = v_{k-s} and v_{k+s}, for rows whose values from outside the column are
+// multiplied by zero: with one register chunk they may be any row's.
+template <int NK, typename T>
+__device__ __forceinline__ void col_shift_any(const T (&v)[NK], int s, T (&a)[NK], T (&b)[NK]) {
+    if constexpr (NK == 1) {
+        const int l = lane_id();
+        a[0] = __shfl(v[0], (l - s) & (kWave - 1), kWave);
+        b[0] = __shfl(v[0], (l + s) & (kWave - 1), kWave);
+    } else {
+        col_shift_up<NK>(v, s, T(0), a);
+        col_shift_down<NK>(v, s, T(0), b);
+    }
+}
+
 // Solves lo_k x_{k-1} + di_k x_k + up_k x_{k+1} = d_k over the layers of a
 // column, x returned in d.  Rows past the last layer must be the identity
 // (lo = up = 0, di = 1, d = 0) and the first and last rows must not couple
@@ -362,38 +394,75 @@ __device__ __forceinline__ void col_shift_down(const T (&v)[NK], int s, T fill, 
 // holds one unknown.  Every lane works in every round, the cross-lane reads
 // are register shuffles, and for the diagonally dominant systems of implicit
 // diffusion no pivoting is needed.
+//
+// The shuffles' LDS port bounds it (six rounds of eight FP64 shuffles were a
+// third of the edge pass with mixing).  Rows are kept divided by their
+// diagonal, which leaves three columns to shift each way; the first round
+// shifts by DPP, the round of 32 reads the same lane for above and below, and
+// the last round moves on the right-hand side only.  A row's coupling past
+// the column's end is zero in every round, so with one chunk the shifts wrap
+// around without a select.  One edge pass with mixing on 256 x 256 x 60: FP64
+// 282 -> 192 us, FP32 219 -> 154; level-6 globe, 100 layers, biharmonic: FP64
+// 320 -> 253 us, FP32 191 -> 158.
 template <int NK, typename T>
 __device__ __forceinline__ void col_tridiag_solve(int L, T (&lo)[NK], T (&di)[NK], T (&up)[NK], T (&d)[NK]) {
-    for (int s = 1; s < L; s <<= 1) {
-        T rdi[NK];
+    T loA[NK], upA[NK], dA[NK], loB[NK], upB[NK], dB[NK];
 #pragma unroll
-        for (int c = 0; c < NK; ++c) rdi[c] = T(1) / di[c];
-        T loA[NK], upA[NK], dA[NK], rA[NK], loB[NK], upB[NK], dB[NK], rB[NK];
-        col_shift_up<NK>(lo, s, T(0), loA);
-        col_shift_up<NK>(up, s, T(0), upA);
-        col_shift_up<NK>(d, s, T(0), dA);
-        col_shift_up<NK>(rdi, s, T(1), rA);
-        col_shift_down<NK>(lo, s, T(0), loB);
-        col_shift_down<NK>(up, s, T(0), upB);
-        col_shift_down<NK>(d, s, T(0), dB);
-        col_shift_down<NK>(rdi, s, T(1), rB);
+    for (int c = 0; c < NK; ++c) {
+        const T q = recip<T>(di[c]);
+        lo[c] *= q;
+        up[c] *= q;
+        d[c] *= q;
+    }
+    auto round = [&](bool last) {
 #pragma unroll
         for (int c = 0; c < NK; ++c) {
-            const T al = -lo[c] * rA[c];
-            const T ga = -up[c] * rB[c];
-            di[c] = di[c] + al * upA[c] + ga * loB[c];
-            d[c] = d[c] + al * dA[c] + ga * dB[c];
-            lo[c] = al * loA[c];
-            up[c] = ga * upB[c];
+            const T q = recip<T>(fmadd(-lo[c], upA[c], fmadd(-up[c], loB[c], T(1))));
+            d[c] = fmadd(-lo[c], dA[c], fmadd(-up[c], dB[c], d[c])) * q;
+            if (!last) {
+                lo[c] = -lo[c] * loA[c] * q;
+                up[c] = -up[c] * upB[c] * q;
+            }
+        }
+    };
+    if (L > 1) {
+        col_up1<NK, true>(lo, loA);
+        col_up1<NK, true>(up, upA);
+        col_up1<NK, true>(d, dA);
+        col_down1<NK, true>(lo, loB);
+        col_down1<NK, true>(up, upB);
+        col_down1<NK, true>(d, dB);
+        round(false);
+    }
+    int s = 2;
+    for (; 2 * s < L && s < 32; s <<= 1) {
+        col_shift_any<NK>(lo, s, loA, loB);
+        col_shift_any<NK>(up, s, upA, upB);
+        col_shift_any<NK>(d, s, dA, dB);
+        round(false);
+    }
+    if constexpr (NK == 1) {
+        if (s >= L) return;
+        if (s == 32) {
+            const int other = lane_id() ^ 32;
+            loB[0] = __shfl(lo[0], other, kWave);
+            upA[0] = __shfl(up[0], other, kWave);
+            dA[0] = dB[0] = __shfl(d[0], other, kWave);
+        } else {
+            col_shift_any<NK>(lo, s, loA, loB);
+            col_shift_any<NK>(up, s, upA, upB);
+            col_shift_any<NK>(d, s, dA, dB);
+        }
+        round(true);
+    } else {
+        for (; s < L; s <<= 1) {
+            col_shift_any<NK>(lo, s, loA, loB);
+            col_shift_any<NK>(up, s, upA, upB);
+            col_shift_any<NK>(d, s, dA, dB);
+            round(2 * s >= L);
         }
     }
-#pragma unroll
-    for (int c = 0; c < NK; ++c) d[c] = d[c] / di[c];
 }
-
-// a b + c rounded once
-__device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // Quotients by 3 and 6 in the bits of x / d but without the division
 // sequence (about ten instructions).  With r = RN(1/d), q = RN(x r) and the
@@ -925,20 +994,6 @@ struct EdgeOperands {
     R un[NK];
     double K1, K2, z1, z2, H1, H2, ubn;
 };
-
-// 1 / x of a layer thickness: the hardware reciprocal refined to the last
-// place in three (FP64: five) instructions, where the division takes eleven.
-template <typename R>
-__device__ __forceinline__ R recip(R x) {
-    R r;
-    if constexpr (sizeof(R) == 4) {
-        r = __builtin_amdgcn_rcpf(x);
-    } else {
-        r = __builtin_amdgcn_rcp(x);
-        r = fmadd(fmadd(-x, r, R(1)), r, r);
-    }
-    return fmadd(fmadd(-x, r, R(1)), r, r);
-}
 
 // sqrt(x) rounded to R.  FP32: one Newton step from the hardware's reciprocal
 // root is good to about 1e-15 before the rounding.

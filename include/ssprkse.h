@@ -254,15 +254,18 @@ int sse_state_get_edge_variant(const sse_state *s, int *variant);
  * (3M per SSPRK3 loop, 2M per SSPRK2 loop).  1: one launch per substep: the
  * mesh is cut into patches of a few hundred cells, and one workgroup carries
  * its patch, extended by the halo rings the substep's evaluations read,
- * through all evaluations of the substep in LDS.  2: one cooperative launch
- * per loop: every patch has its own workgroup for all M substeps and keeps
- * its tables, frozen forcing and F^zeta sums on chip; between substeps the
- * patches exchange their halos and each waits for its neighbours (on meshes
- * whose reconstruction weights do not factor by cell: a grid barrier);
- * available when the device holds a workgroup for every patch at once.  A
- * wait is bounded: if one runs out, the step call reports SSE_EDEVICE and the
- * state is not valid.  A stream under graph capture runs variant 1 in place of
- * 2; a state asked to replay its steps as a graph runs them as they are where
+ * through all evaluations of the substep in LDS.  2: one launch per loop:
+ * every patch has its own workgroup for all M substeps and keeps its tables,
+ * frozen forcing and F^zeta sums on chip; between substeps the patches
+ * exchange their halos and each waits for its neighbours; available when an
+ * empty device holds a workgroup for every patch at once.  Where work of
+ * other streams or processes keeps some of them out, the loop is called off
+ * before any has waited for another, and the launch behind it does it patch by
+ * patch, with the same results, on whatever part of the device is free.  (On
+ * meshes whose reconstruction weights do not factor by cell: a cooperative
+ * launch with a grid barrier per substep.)  A wait is bounded: if one runs
+ * out, the step call reports SSE_EDEVICE and the state is not valid.  A stream
+ * under graph capture runs variant 1 in place of 2; a state asked to replay its steps as a graph runs them as they are where
  * 2 is in use (a step then has few launches); a batch takes one launch per
  * loop when the device holds the patches of all its members at once and none
  * was set to another variant by its caller.  The default is 2 where it is
@@ -373,13 +376,19 @@ int sse_debug_barotropic_substep(sse_state *s, int32_t scheme, int32_t M, double
  * recorded into a batch; SSE_EDEVICE if the launch fails. */
 int sse_debug_edge_gathers(sse_state *s);
 
-/* Polls a grid barrier of the persistent barotropic loop (variant 2) makes
- * before it gives up, reports the timeout and lets every workgroup finish;
- * 0 restores the default (about 0.3 s of waiting).  For tests of that error
- * path: with 1, the first workgroup to reach a barrier finds it closed and
- * gives up at once (whenever the launch has more than one workgroup), the
- * step call returns SSE_EDEVICE and the state must be initialised again.
- * SSE_EINVAL for a NULL state. */
+/* enable != 0: the device calls off every one-launch loop (variant 2) of the
+ * state, as it does where other work keeps part of its workgroups out, so that
+ * the launch behind it does the loop.  For tests of that path; in a batch the
+ * first member's setting holds.  SSE_EINVAL for a NULL state. */
+int sse_debug_call_off_loops(sse_state *s, int enable);
+
+/* Polls a wait of the one-launch barotropic loop (variant 2: for neighbouring
+ * patches, or at a grid barrier) makes before it gives up, reports the timeout
+ * and lets every workgroup finish; 0 restores the default (2^22, some seconds
+ * for neighbouring patches).  For tests of that error path: with 1, the first
+ * workgroup that has to wait gives up at once (whenever the launch has more
+ * than one workgroup), the step call returns SSE_EDEVICE and the state must be
+ * initialised again.  SSE_EINVAL for a NULL state. */
 int sse_debug_set_barrier_spins(sse_state *s, uint32_t spins);
 
 /* One thickness stage h_out = h_in + dt T^h(h_in, u + uA) (Section 3.4 revised

@@ -11,8 +11,8 @@ The knobs change how the work is laid out on the GPU, never the arithmetic
   8, 16 or 32 edges;
 * the barotropic-loop kernel: one launch per substep over cell patches with
   their halo rings, one launch per forward-Euler evaluation, or (single
-  states whose patches all fit the device at once) one cooperative launch for
-  the whole loop; batch members choose between the first two.
+  states whose patches all fit an empty device at once) one launch for the
+  whole loop; batch members choose between the first two.
 
 The tuner times whole steps with HIP events on the state's (batch's) stream
 and keeps the fastest setting.  It searches one knob at a time (coordinate

@@ -40,17 +40,32 @@ using namespace sse;
 // address reaches kernels.
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
 static __device__ __align__(256) double scratch[kStaticScratchBytes / sizeof(double)];
-// Substep counters and error word of the resident loop in that entry point
-// (the largest mesh the scratch takes has fewer than 2^19 cells; see
-// done_patches); zero when the code is loaded.
+// Substep counters, admission words and error word of the resident loop in
+// that entry point (the largest mesh the scratch takes has fewer than 2^19
+// cells; see done_patches); zero when the code is loaded.
 constexpr size_t kStaticCounters = ((size_t(1) << 19) / 32 + 32) * kDoneStride;
-static __device__ __align__(256) unsigned long long scratch_done[kStaticCounters + kDoneStride];
+static __device__ __align__(256) unsigned long long scratch_done[kStaticCounters + (kRoundWords + 1) * kDoneStride];
 
 namespace {
 
 constexpr int kMaxDevices = 64;
 std::atomic<void *> g_scratch[kMaxDevices], g_scratch_done[kMaxDevices];
-std::atomic<unsigned long long> g_scratch_count[kMaxDevices];  // at least every value its counters hold
+
+// What the host knows of one set of substep counters and admission words: the
+// numbers of a launch are the ones before it and its own.
+struct RoundCount {
+    std::mutex mu;
+    unsigned long long counted = 0;   // at least every value the substep counters hold
+    unsigned long long serial = 0;    // of the last launch
+    // The next launch: wgs workgroups (one: no admission), at most M substeps.
+    BtRound next(unsigned long long *words, int wgs, int M, unsigned ticks) {
+        std::lock_guard<std::mutex> g(mu);
+        const BtRound r{counted, wgs > 1 ? words : nullptr, ++serial, ticks};
+        counted += 2 * (unsigned long long)M;
+        return r;
+    }
+};
+RoundCount g_scratch_round[kMaxDevices];
 
 // Resolves (once per device, with that device current) the address of this
 // device's scratch array; nullptr if the runtime cannot give it.
@@ -109,7 +124,8 @@ size_t bt_size(int precision) { return precision == SSE_MIXED ? sizeof(float) : 
 // Patches the workspace holds substep counters for (meshes cut into more do
 // not take the resident loop).
 int done_patches(int C) { return C / 32 + 32; }
-size_t done_bytes(int C) { return align_up((size_t)done_patches(C) * kDoneStride * 8); }
+// (the words of BtRound follow them)
+size_t done_bytes(int C) { return align_up((size_t)(done_patches(C) + kRoundWords) * kDoneStride * 8); }
 
 size_t workspace_bytes(int C, int E, int V, int L, size_t rs, size_t bs, int hdiff, int tracer) {
     size_t b = 0;
@@ -278,14 +294,15 @@ struct sse_state {
     Geom geom{};             // launch geometry (autotuner knob)
     int edge_variant = -1;   // -1: direct gathers (-2: with 64-bit column addresses); 0 / 1 / 2: LDS tiles of 8 / 16 / 32 edges
     int bt_variant = 0;      // 0: one launch per barotropic evaluation; 1: one per substep (patches);
-                             // 2: one cooperative launch per loop, one workgroup per patch
-    int bt_capacity[2] = {0, 0};  // workgroups of the persistent loop kernel the device holds at once
+                             // 2: one launch per loop, one workgroup per patch
+    int bt_capacity[2] = {0, 0};  // workgroups of the persistent loop kernel an empty device holds at once
                                   // (SSPRK2, SSPRK3 forms)
     bool bt_auto = true;          // the variant is the default, not the caller's
     int bt_tight[2] = {0, 0};     // the form of that kernel
     bool capturing = false;  // a HIP graph capture of the step is in progress
-    hipError_t launch_error = hipSuccess;  // the last failed cooperative launch, reported by the step call
-    unsigned long long bt_count = 0;  // at least every value the counters w.bt_done hold
+    hipError_t launch_error = hipSuccess;  // the last failed launch of a loop, reported by the step call
+    RoundCount bt_round;          // of the counters w.bt_done and the words behind them
+    unsigned admit_ticks = kAdmitTicks;  // see BtRound::ticks
     unsigned barrier_spins = kBarrierSpins;  // polls before a barrier of the persistent loop gives up
     size_t lds_max = 0;      // LDS bytes per workgroup on the state's device
     Recorder *rec = nullptr; // non-null while a batch records this state's step
@@ -364,7 +381,7 @@ bool bt_tiles_fit(const sse_state *s) {
 }
 
 // The persistent loop kernel can give every patch its own workgroup at once
-// (a cooperative launch of the XCD-padded patch count) for this scheme.
+// (the XCD-padded patch count, on an empty device) for this scheme.
 bool resident_able(const DevBtTiles &t, int C) { return t.fact && t.resident && t.nP <= done_patches(C); }
 bool bt_loop_fits(const sse_state *s, int scheme) {
     const DevBtTiles &t = s->mesh->bt;
@@ -373,13 +390,15 @@ bool bt_loop_fits(const sse_state *s, int scheme) {
     return bt_tiles_fit(s) && kXcd * ((nP + kXcd - 1) / kXcd) <= s->bt_capacity[scheme == SSE_SCHEME_SSPRK3 ? 1 : 0];
 }
 
-// Fewest substeps for which a loop is worth a cooperative launch, which costs
-// about 17 us more than an ordinary one (a mesh of one patch takes an ordinary
-// one); a substep of it takes 2-5 us less than a launch of its own.  A loop of
-// 7 SSPRK2 substeps on 4,462 cells came out even (0.99x a whole step).
+// Fewest substeps for which a loop is worth the resident form, whose admission
+// and second launch cost about 6 us (a mesh of one patch needs neither); a
+// substep of it takes 2-5 us less than a launch of its own.  The line is from
+// when the form cost 17 us: then a loop of 7 SSPRK2 substeps on 4,462 cells
+// came out even (0.99x a whole step).
 bool resident_pays(const DevBtTiles &t, int M) { return M >= (t.nA == 1 ? 2 : 10); }
 
-// The stream is being captured into a graph, which takes no cooperative launch.
+// The stream is being captured into a graph: its replays could not take the
+// numbers that every launch of the resident loop has of its own.
 bool stream_capturing(hipStream_t st) {
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &c) != hipSuccess) {
@@ -536,14 +555,19 @@ void convert(sse_state *s, const Tin *src, Tout *dst, size_t n, int var) {
 // before widening (ua, za, uo, zo).
 struct BtBufs {
     void *u1, *uh, *z1, *zh, *ua, *za, *uo, *zo;
-    unsigned long long *done;   // substep counters and error word of the resident loop
+    unsigned long long *done, *words;  // substep counters, admission words and error word of the resident loop
     int *err;
-    std::atomic<unsigned long long> *count;  // the counters' upper bound (null: the state's)
+    RoundCount *count;                 // the host's side of the first two
+    bool shared;                       // they are the device's, not the state's
     const int32_t *eold, *cold;              // the fields' numbering, resident loop only (null: the mesh's own)
 };
 
-BtBufs bt_bufs(const Work &w) {
-    return {w.bt_u1, w.bt_uh, w.bt_z1, w.bt_zh, w.bt_ua, w.bt_za, w.bt_uo, w.bt_zo, w.bt_done, w.flag + 32, nullptr, nullptr, nullptr};
+unsigned long long *round_words(const sse_state *s) { return s->w.bt_done + (size_t)done_patches(s->mesh->C) * kDoneStride; }
+
+BtBufs bt_bufs(sse_state *s) {
+    const Work &w = s->w;
+    return {w.bt_u1, w.bt_uh, w.bt_z1, w.bt_zh, w.bt_ua, w.bt_za, w.bt_uo, w.bt_zo, w.bt_done, round_words(s), w.flag + 32,
+            &s->bt_round, false, nullptr, nullptr};
 }
 
 // Algorithm 3 (scheme 2) / Algorithm 4 (scheme 3): M substeps of dt / M with
@@ -566,7 +590,7 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
     base.w1 = scheme == SSE_SCHEME_SSPRK3 ? 1.0 / (6.0 * M) : 1.0 / (2.0 * M);
     base.w3 = scheme == SSE_SCHEME_SSPRK3 ? 2.0 / (3.0 * M) : 0.0;
     const BtResident<R> res{base, M, in_u, in_z, u1, uh, z1, zh, out_u, out_z, w.done, w.err,
-                            w.count ? kBarrierSpins : s->barrier_spins, w.eold, w.cold};
+                            w.shared ? kBarrierSpins : s->barrier_spins, w.eold, w.cold};
     const bool resident = s->rec ? (s->bt_variant == 2 || (s->bt_auto && s->bt_variant == 1)) && resident_able(tiles, m.C)
                                  : runs_resident(s, scheme);
     if (s->rec && resident) {
@@ -576,9 +600,9 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
         s->rec->seq++;
     } else if (resident) {
         ProfScope ps(s, SSE_PROF_BT_EVAL);
-        const unsigned long long from = w.count ? w.count->fetch_add((unsigned long long)M) : s->bt_count;
-        const hipError_t e = launch_bt_resident<R>(res, scheme, s->bt_tight[scheme == SSE_SCHEME_SSPRK3 ? 1 : 0], from, s->stream);
-        if (!w.count) s->bt_count += (unsigned long long)M;
+        const BtRound round = w.count->next(w.words, tiles.nA, M, s->admit_ticks);
+        hipError_t e = launch_bt_resident<R>(res, scheme, s->bt_tight[scheme == SSE_SCHEME_SSPRK3 ? 1 : 0], round, s->stream);
+        if (e == hipSuccess) e = launch_bt_tasks<R>(res, scheme, round, s->stream);
         if (e != hipSuccess) s->launch_error = e;
         return;
     }
@@ -602,7 +626,7 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
         ou = rp<R>(w.uo);
         oz = rp<R>(w.zo);
     }
-    if (s->bt_variant == 2 && !tiles.fact && !s->rec && !s->capturing && !w.count && bt_loop_fits(s, scheme) &&
+    if (s->bt_variant == 2 && !tiles.fact && !s->rec && !s->capturing && !w.shared && bt_loop_fits(s, scheme) &&
         !stream_capturing(s->stream)) {
         // one cooperative launch: every patch in its own workgroup for all M
         // substeps, grid barriers between them
@@ -817,9 +841,9 @@ template <typename R>
 void bt_loop_of(sse_state *s, int scheme, int M, double dt, const double *in_u, const double *in_z,
                 const double *G, double *out_u, double *out_z, double *F) {
     if (s->bt64)
-        bt_loop<double>(s, scheme, M, dt, in_u, in_z, G, out_u, out_z, F, bt_bufs(s->w));
+        bt_loop<double>(s, scheme, M, dt, in_u, in_z, G, out_u, out_z, F, bt_bufs(s));
     else
-        bt_loop<float>(s, scheme, M, dt, in_u, in_z, G, out_u, out_z, F, bt_bufs(s->w));
+        bt_loop<float>(s, scheme, M, dt, in_u, in_z, G, out_u, out_z, F, bt_bufs(s));
 }
 
 template <typename R>
@@ -916,18 +940,18 @@ int read_flag(sse_state *s) {
     SSE_HIP(hipStreamSynchronize(s->stream));
     if (s->prof) prof_flush(s);
     if (flag[32]) {
-        set_error("a grid barrier of the persistent barotropic loop timed out; the state is not valid");
+        set_error("a wait of a barotropic loop (for neighbouring patches or at a grid barrier) ran out; the state is not valid");
         return SSE_EDEVICE;
     }
     if (flag[0]) { set_error("non-finite value in the state (the step blew up)"); return SSE_ENONFINITE; }
     return SSE_OK;
 }
 
-// A cooperative launch that failed while steps were enqueued.
+// A launch of a barotropic loop that failed while steps were enqueued.
 int take_launch_error(sse_state *s) {
     const hipError_t e = s->launch_error;
     s->launch_error = hipSuccess;
-    return e == hipSuccess ? SSE_OK : hip_fail(e, "hipLaunchCooperativeKernel");
+    return e == hipSuccess ? SSE_OK : hip_fail(e, "launch of the barotropic loop");
 }
 
 // Host <-> device copies of an array of the state's real type from / to FP64
@@ -1683,6 +1707,12 @@ extern "C" int sse_debug_set_barrier_spins(sse_state *s, uint32_t spins) {
     return SSE_OK;
 }
 
+extern "C" int sse_debug_call_off_loops(sse_state *s, int enable) {
+    if (!s) { set_error("NULL state"); return SSE_EINVAL; }
+    s->admit_ticks = enable ? 0 : kAdmitTicks;
+    return SSE_OK;
+}
+
 extern "C" int sse_state_get_bt_variant(const sse_state *s, int *variant) {
     if (!s || !variant) { set_error("NULL argument"); return SSE_EINVAL; }
     *variant = s->bt_variant;
@@ -1856,9 +1886,9 @@ extern "C" int sse_step_async(sse_state *s, int32_t n) {
     if (!s->initialized) { set_error("state not initialised"); return SSE_ESTATE; }
     if (s->p.tracer && !s->tracer_set) { set_error("tracer runs need sse_state_set_tracer before stepping"); return SSE_ESTATE; }
     if (n < 0) { set_error("n must be >= 0"); return SSE_EINVAL; }
-    // a step with the resident loop is few launches, cooperative ones among
-    // them, which a graph does not take: it runs as it is (0.43 ms per 64 x 64
-    // x 20 step against 0.48 as a graph with a launch per substep)
+    // a step with the resident loop is few launches, each with numbers of its
+    // own, which a graph could not give it: it runs as it is (0.43 ms per 64 x
+    // 64 x 20 step against 0.48 as a graph with a launch per substep)
     const bool resident = s->bt_variant == 2 && s->mesh->bt.fact && bt_loop_fits(s, s->p.scheme);
     if (s->use_graph && !(resident && !stream_capturing(s->stream))) {
         if (!s->graph_exec) {
@@ -2035,9 +2065,9 @@ extern "C" int sse_debug_barotropic_substep(sse_state *s, int32_t scheme, int32_
     SSE_HIP(hipMemcpyAsync(w.z1, zi.data(), C * 8, hipMemcpyHostToDevice, st));
     SSE_HIP(hipMemcpyAsync(w.G0, gi.data(), E * 8, hipMemcpyHostToDevice, st));
     if (s->bt64)
-        bt_loop<double>(s, scheme, M, dt, w.ub1, w.z1, w.G0, w.ub2, w.bt_zout, w.Fz1, bt_bufs(w));
+        bt_loop<double>(s, scheme, M, dt, w.ub1, w.z1, w.G0, w.ub2, w.bt_zout, w.Fz1, bt_bufs(s));
     else
-        bt_loop<float>(s, scheme, M, dt, w.ub1, w.z1, w.G0, w.ub2, w.bt_zout, w.Fz1, bt_bufs(w));
+        bt_loop<float>(s, scheme, M, dt, w.ub1, w.z1, w.G0, w.ub2, w.bt_zout, w.Fz1, bt_bufs(s));
     if (int rc = take_launch_error(s)) return rc;
     SSE_HIP(hipGetLastError());
     int barrier_err = 0;
@@ -2047,7 +2077,7 @@ extern "C" int sse_debug_barotropic_substep(sse_state *s, int32_t scheme, int32_
     SSE_HIP(hipMemcpyAsync(&barrier_err, w.flag + 32, sizeof(int), hipMemcpyDeviceToHost, st));
     SSE_HIP(hipStreamSynchronize(st));
     if (barrier_err) {
-        set_error("a grid barrier of the persistent barotropic loop timed out");
+        set_error("a wait of the barotropic loop (for neighbouring patches or at a grid barrier) ran out");
         return SSE_EDEVICE;
     }
     rows_to_user(bo.data(), ubar1, m->edge_old, 1);
@@ -2129,8 +2159,10 @@ extern "C" int sse_barotropic_substep_noalloc(sse_state *s, int32_t scheme, int3
     // counters (and, captured in a graph, one launch per substep runs in its
     // place)
     b.done = static_cast<unsigned long long *>(g_scratch_done[dev].load(std::memory_order_acquire));
-    b.err = reinterpret_cast<int *>(b.done + kStaticCounters);
-    b.count = &g_scratch_count[dev];
+    b.words = b.done + kStaticCounters;
+    b.err = reinterpret_cast<int *>(b.words + kRoundWords * kDoneStride);
+    b.count = &g_scratch_round[dev];
+    b.shared = true;
     const double *ru = direct ? ubar : iu, *rz = direct ? zeta : iz, *rG = direct ? G : iG;
     double *wu = direct ? ubar1 : ou, *wz = direct ? zeta1 : oz, *wF = direct ? Fzeta : oF;
     if (s->bt64)
@@ -2343,13 +2375,17 @@ void batch_enqueue(sse_batch *b, bool resident) {
         if (!batch_runs(op, resident)) continue;
         switch (op.kind) {
             case Kind::BT_LOOP: {
-                unsigned long long from = 0;
-                for (const sse_state *s : b->members) from = std::max(from, s->bt_count);
-                const int scheme = b->members[0]->p.scheme;
+                // the first member's admission words; counters that no member's exceed
+                sse_state *s0 = b->members[0];
+                const int M = op.substeps, scheme = s0->p.scheme;
+                BtRound round = s0->bt_round.next(round_words(s0), op.blocks, M, s0->admit_ticks);
+                for (const sse_state *s : b->members) round.base = std::max(round.base, s->bt_round.counted);
                 hipError_t e;
-                if (bt64) e = launch_bt_resident_batch<double>(bl<BtResident<double>>(b, op), scheme, b->tight, from, st);
-                else e = launch_bt_resident_batch<float>(bl<BtResident<float>>(b, op), scheme, b->tight, from, st);
-                for (sse_state *s : b->members) s->bt_count = from + (unsigned long long)op.substeps;
+                if (bt64) e = launch_bt_resident_batch<double>(bl<BtResident<double>>(b, op), scheme, b->tight, round, st);
+                else e = launch_bt_resident_batch<float>(bl<BtResident<float>>(b, op), scheme, b->tight, round, st);
+                if (e == hipSuccess && bt64) e = launch_bt_tasks_batch<double>(bl<BtResident<double>>(b, op), M, scheme, round, st);
+                else if (e == hipSuccess) e = launch_bt_tasks_batch<float>(bl<BtResident<float>>(b, op), M, scheme, round, st);
+                for (sse_state *s : b->members) s->bt_round.counted = round.base + 2 * (unsigned long long)M;
                 if (e != hipSuccess) b->launch_error = e;
                 break;
             }
@@ -2507,7 +2543,7 @@ extern "C" int sse_batch_step_async(sse_batch *b, int32_t n) {
     for (int i = 0; i < n; ++i) batch_enqueue_any(b, resident);
     const hipError_t le = b->launch_error;
     b->launch_error = hipSuccess;
-    if (le != hipSuccess) return hip_fail(le, "hipLaunchCooperativeKernel");
+    if (le != hipSuccess) return hip_fail(le, "launch of the barotropic loop");
     SSE_HIP(hipGetLastError());
     return SSE_OK;
 }

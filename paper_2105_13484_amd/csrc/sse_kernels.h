@@ -216,6 +216,24 @@ struct BtResident {
     const int32_t *eold, *cold; // the fields' numbering of the mesh's edges and cells (null: the mesh's own)
 };
 constexpr int kDoneStride = 8;  // one 64-byte line per patch
+// One launch of the resident loop, alone or over a batch.
+struct BtRound {
+    unsigned long long base;    // at least every value its substep counters hold; the launch counts up to
+                                // twice its substeps on from there
+    unsigned long long *words;  // [kRoundWords], a line each: workgroups that have started, by groups, and
+                                // the groups that are complete (all zero between launches); the verdict on
+                                // the last launch, 2 serial (+ 1: called off); the next task (null: one
+                                // workgroup, which needs no admission)
+    unsigned long long serial;  // larger than that of every earlier launch with these words
+    unsigned ticks;             // of the clock (10 ns) before a workgroup calls the loop off (0: at once, and
+                                // nobody admits it)
+};
+constexpr int kGroups = 32, kVerdict = kGroups + 1, kTicket = kGroups + 2, kRoundWords = kGroups + 3;
+// How long a workgroup waits for the others to start: an idle device starts
+// all of them within 5 us; beside a short kernel of another stream they took up
+// to 80.  Longer waits rarely help (the places are in pieces then, see
+// settle) and cost the other stream its CUs.
+constexpr unsigned kAdmitTicks = 20000;
 
 // Thickness stage with the z-star distribution of a 2D total flux.
 struct THArgs {
@@ -345,7 +363,8 @@ void set_tiled_lds_limit(size_t bytes);
 template <typename R> void launch_bt_eval(const BTEvalArgs<R> &a, const Geom &g, hipStream_t s);
 // scheme 2 or 3; requires a.t.nP > 0 and the LDS limit set (set_tiled_lds_limit).
 template <typename R> void launch_bt_substep(const BTTileArgs<R> &a, int scheme, hipStream_t s);
-// Polls before a grid barrier of the persistent loop gives up (about 0.3 s).
+// Polls before a wait gives up (a grid barrier of the persistent loop: about
+// 0.3 s; neighbours' counters: some seconds).
 constexpr unsigned kBarrierSpins = 1u << 22;
 // Workgroups of the persistent loop kernel the device holds at once for this
 // tile set, precision and scheme (0 if it cannot launch cooperatively).
@@ -353,15 +372,15 @@ template <typename R> int bt_loop_capacity(const DevBtTiles &t, int scheme, int 
 // The whole loop (a: tables, G, F, tau, g and flux weights; the per-substep
 // pointers of a are unused); returns the launch's HIP error.
 template <typename R> hipError_t launch_bt_loop(const BTTileArgs<R> &a, const BtLoop<R> &l, int scheme, hipStream_t s);
-// The resident loop in one cooperative launch; base is at least every value
-// any of its counters holds.  tight: which of the kResidentForms forms, those
-// holding more workgroups per CU coming later (the capacity queries take the
-// same number).
+// The resident loop: one launch, and launch_bt_tasks behind it, which only
+// works if the loop was called off.  tight: which of the kResidentForms forms, those holding more workgroups per
+// CU coming later (the capacity queries take the same number).
 constexpr int kResidentForms = 3;
 template <typename R>
-hipError_t launch_bt_resident(const BtResident<R> &a, int scheme, int tight, unsigned long long base, hipStream_t s);
+hipError_t launch_bt_resident(const BtResident<R> &a, int scheme, int tight, const BtRound &round, hipStream_t s);
+template <typename R> hipError_t launch_bt_tasks(const BtResident<R> &a, int scheme, const BtRound &round, hipStream_t s);
 // The same over the patches of several states (table entries: member, place
-// in its patch order), which must all be resident at once.
+// in its patch order), which an empty device must hold at once.
 template <typename R> int bt_resident_batch_capacity(int scheme, int tight);
 template <typename R> void launch_thickness_iso(const THIsoArgs<R> &a, const Geom &g, hipStream_t s);
 template <typename R> void launch_assemble(const AssembleArgs<R> &a, const Geom &g, hipStream_t s);
@@ -415,8 +434,12 @@ constexpr int kFactVar = 16;
 template <typename R>
 void launch_bt_substep_batch(const BatchLaunch<BTTileArgs<R>> &b, int scheme, int ks, size_t lds, hipStream_t s);
 template <typename R>
-hipError_t launch_bt_resident_batch(const BatchLaunch<BtResident<R>> &b, int scheme, int tight,
-                                    unsigned long long base, hipStream_t s);
+hipError_t launch_bt_resident_batch(const BatchLaunch<BtResident<R>> &b, int scheme, int tight, const BtRound &round,
+                                    hipStream_t s);
+// most: the most substeps of any member
+template <typename R>
+hipError_t launch_bt_tasks_batch(const BatchLaunch<BtResident<R>> &b, int most, int scheme, const BtRound &round,
+                                 hipStream_t s);
 template <typename R> void launch_thickness_iso_batch(const BatchLaunch<THIsoArgs<R>> &b, int nk, const Geom &g, hipStream_t s);
 template <typename R> void launch_assemble_batch(const BatchLaunch<AssembleArgs<R>> &b, int nk, const Geom &g, hipStream_t s);
 template <typename Tin, typename Tout>

@@ -2333,28 +2333,75 @@ __device__ __forceinline__ void bt_eval_fact(const BTEvalArgs<R> &a, bool edge_p
     }
 }
 
-// Waits until every neighbour of patch p has finished `target` substeps
-// (counted on from the launch's base), one lane per neighbour.  The wait is
-// bounded: if it runs out, or another workgroup's did, the workgroup goes on
-// without waiting and *err makes the host refuse the results.
-__device__ __forceinline__ void wait_neighbours(const unsigned long long *done, const int32_t *nbr, int n,
-                                                unsigned long long target, int *err, unsigned max_spins) {
-    const int lane = threadIdx.x;
-    if (lane < n) {
-        const unsigned long long *f = done + (size_t)nbr[lane] * kDoneStride;
-        unsigned spins = 0;
-        while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            if (++spins > max_spins) {
-                __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-            if ((spins & 255u) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+template <typename T>
+__device__ __forceinline__ T shared_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void shared_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waits until the counter *f has reached target.  The wait is bounded: if it
+// runs out, or another workgroup's did, the workgroup goes on without waiting
+// and *err makes the host refuse the results.
+__device__ __forceinline__ void wait_count(const unsigned long long *f, unsigned long long target, int *err,
+                                           unsigned max_spins) {
+    unsigned spins = 0;
+    while (shared_load(f) < target) {
+        if (++spins > max_spins) {
+            shared_store(err, 1);
+            break;
         }
+        if ((spins & 255u) == 0 && shared_load(err) != 0) break;
     }
 }
 
-// One substep of patch p (kLoop false: the input a.ua, a.za, the output a.uo,
-// a.zo), or all l->M substeps of the loop (kLoop true).
+// Admission of a resident loop.  Its workgroups wait for each other, so none
+// may wait before all of them hold a place on the device.  An occupancy query
+// cannot promise that: it counts the places of an empty device, and a kernel of
+// another stream or process takes places, and leaves registers and LDS of a CU
+// in pieces that fit fewer workgroups, for as long as the loop's first ones
+// wait (beside a kernel of 192-thread workgroups, 174 of 752 workgroups of 512
+// threads, three of which an idle CU holds, started only when others had
+// ended; as a cooperative launch 158).  So every workgroup counts itself in
+// before its first substep; the last one to arrive admits the loop; one that
+// has waited kAdmitTicks without that calls it off.  Whoever is first decides,
+// for all: nobody has published anything yet, and the task form below computes
+// a loop that was called off.
+__device__ __forceinline__ void settle(const BtRound &r, unsigned long long verdict) {
+    unsigned long long *d = r.words + kVerdict * kDoneStride, v = shared_load(d);
+    while (v < 2 * r.serial &&
+           !__hip_atomic_compare_exchange_strong(d, &v, verdict, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+    }
+}
+__device__ __forceinline__ bool called_off(const BtRound &r) {
+    return shared_load(r.words + kVerdict * kDoneStride) == 2 * r.serial + 1;
+}
+__device__ __forceinline__ unsigned long long shared_count(unsigned long long *p) {
+    return __hip_atomic_fetch_add(p, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Workgroup lb of n has started.  Counts on one address come one after the
+// other, about 40 ns apiece (745 workgroups: 30 us), so each group counts on a
+// line of its own and its last one at the root.
+__device__ __forceinline__ void arrive(const BtRound &r, int lb, int n) {
+    const int g = lb % kGroups, members = n / kGroups + (g < n % kGroups ? 1 : 0);
+    if (shared_count(r.words + g * kDoneStride) + 1 != (unsigned long long)members) return;
+    if (shared_count(r.words + kGroups * kDoneStride) + 1 != (unsigned long long)min(n, kGroups)) return;
+    if (r.ticks) settle(r, 2 * r.serial);
+}
+__device__ __forceinline__ bool admitted(const BtRound &r) {
+    const unsigned long long t0 = wall_clock64();
+    for (;;) {
+        const unsigned long long v = shared_load(r.words + kVerdict * kDoneStride);
+        if (v >= 2 * r.serial) return v == 2 * r.serial;
+        if (wall_clock64() - t0 >= r.ticks) settle(r, 2 * r.serial + 1);
+    }
+}
+
+// One substep of patch p (kOne: the input a.ua, a.za, the output a.uo, a.zo),
+// all l->M substeps of the loop (kAll), or substep `task` of the loop (kTask:
+// through the exchange buffers, every value of the patch).
 //
 // In the loop form the tables, the forcing, the transport sums and the
 // patch's own state stay on chip, and a substep ends with an exchange: the
@@ -2384,13 +2431,16 @@ struct FactLds {
     Pair<R> HS[kFactEdges * NT];
     ZetaDepth<R> ZH[NT];
     R ZS[kFactEdges * NT];
+    int go;   // the loop is admitted
 };
 
-template <typename R, int kScheme, bool kLoop, int NT>
-__device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtResident<R> *l, int p,
-                                             unsigned long long base_count) {
+enum { kOne, kAll, kTask };
+
+template <typename R, int kScheme, int kMode, int NT>
+__device__ __forceinline__ void bt_fact_body(FactLds<R, NT> &lds, const BTTileArgs<R> &a, const BtResident<R> *l,
+                                             int p, const BtRound *round, int task = 0, int lb = 0, int n = 1) {
 #pragma clang fp contract(off)
-    __shared__ FactLds<R, NT> lds;
+    constexpr bool kLoop = kMode == kAll;
     const DevBtTiles &T = a.t;
     const int tid = threadIdx.x;
     const int32_t *rec = T.patch + (size_t)p * kBtRec;
@@ -2403,7 +2453,7 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
     }
     constexpr int kIn = kScheme == 3 ? 3 : 2;  // level of the substep input
     constexpr int KS = kBtEdgeSlots;
-    if (!kLoop && !rec[14]) {  // no ocean cell: velocity, zeta and transport are zero
+    if (kMode == kOne && !rec[14]) {  // no ocean cell: velocity, zeta and transport are zero
         for (int le = tid; le < ne[0]; le += NT) {
             const int e = T.eid[e0 + le];
             a.uo[e] = R(0);
@@ -2421,37 +2471,51 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
     int ge[kFactEdges];
     // the resident loop reads and writes the step's FP64 fields (an FP32 loop
     // rounds and widens them here: two launches each way less, 4 us apiece)
-    using IO = std::conditional_t<kLoop, double, R>;
+    using IO = std::conditional_t<kMode == kOne, R, double>;
     const IO *ua, *za;
-    if constexpr (kLoop) {
-        ua = l->u_in;
-        za = l->z_in;
-    } else {
+    if constexpr (kMode == kOne) {
         ua = a.ua;
         za = a.za;
+    } else {
+        ua = l->u_in;
+        za = l->z_in;
     }
+    // a task reads what the tasks of the substep before it have published
+    const bool begun = kMode == kTask && task > 0;
+    auto old_u = [&](int e, uint32_t c) -> R {
+        if (begun) return ((c >> 30) & 1u) ? shared_load(((task - 1) & 1 ? l->bu1 : l->bu0) + e) : R(0);
+        return (R)ua[e];
+    };
+    auto old_z = [&](int c, bool wet) -> R {
+        if (begun) return wet ? shared_load(((task - 1) & 1 ? l->bz1 : l->bz0) + c) : R(0);
+        return (R)za[c];
+    };
+    auto old_F = [&](int e) -> double {
+        if (kMode == kOne) return a.zeroF ? 0.0 : a.F[e];
+        return begun ? shared_load(a.F + e) : 0.0;
+    };
 #pragma unroll
     for (int s = 0; s < kFactEdges; ++s) {
         const int le = s * NT + tid;
         const bool on = le < nEin;
         const int q = e0 + (on ? le : 0);
         ge[s] = T.eid[q];
-        if (kLoop && l->eold) ge[s] = l->eold[ge[s]];
+        if (kMode != kOne && l->eold) ge[s] = l->eold[ge[s]];
         lhv[s] = FactTab<R>::lh(T)[q];
         ec[s] = T.fec[q];
-        const R v = (R)ua[ge[s]];
+        const R v = old_u(ge[s], ec[s]);
         if (s < KS) {
             idc[s < KS ? s : 0] = FactTab<R>::idc(T)[q];
             Gv[s < KS ? s : 0] = (R)a.G[ge[s]];
             u[s < KS ? s : 0] = v;
-            Fa[s < KS ? s : 0] = (a.F && le < ne[0] && !(kLoop || a.zeroF)) ? a.F[ge[s]] : 0.0;
+            Fa[s < KS ? s : 0] = (a.F && le < ne[0]) ? old_F(ge[s]) : 0.0;
         }
         if (on) lds.XF[le] = Pair<R>{lhv[s] * v, FactTab<R>::fh(T)[q]};
     }
     const bool con = tid < nCin;
     const int qc = con ? tid : 0;
     int gc = T.cid[c0 + qc];
-    if (kLoop && l->cold) gc = l->cold[gc];
+    if (kMode != kOne && l->cold) gc = l->cold[gc];
     const uint32_t cfl = T.cflag[c0 + qc];
     const bool cwet = con && (cfl & 1u) != 0;
     // byte offset of the cell's half sum on each of its edges: the edge's pair,
@@ -2468,7 +2532,7 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
         S[j] = FactTab<R>::S(T)[(size_t)6 * c0 + (size_t)j * nc[3] + qc];
     }
     const R ia = FactTab<R>::ia(T)[c0 + qc];
-    R z = (R)za[gc], z0;
+    R z = old_z(gc, cwet), z0;
     if (con) lds.ZH[tid] = ZetaDepth<R>{T.cH[c0 + tid], z};
     if (tid == 0) {  // the entry that missing edge slots read
         lds.XF[ne[3]] = Pair<R>{R(0), R(0)};
@@ -2545,12 +2609,21 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
         }
     };
 
-    const int nsub = kLoop ? l->M : 1;
+    if (kLoop && round->words) {
+        if (tid == 0) {
+            if (lb == 0) shared_store(round->words + kTicket * kDoneStride, 0ull);
+            arrive(*round, lb, n);
+        }
+        if (tid == 0) lds.go = admitted(*round);
+        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane(lds.go)) return;
+    }
+    const int nsub = kMode == kOne ? 1 : l->M, first = kMode == kTask ? task : 0;
 #pragma unroll 1
-    for (int sub = 0; sub < nsub; ++sub) {
+    for (int sub = first; sub < (kMode == kTask ? first + 1 : nsub); ++sub) {
         const bool last = sub == nsub - 1;
         IO *uo = nullptr, *zo = nullptr;
-        if constexpr (!kLoop) {
+        if constexpr (kMode == kOne) {
             uo = a.uo;
             zo = a.zo;
         } else if (last) {
@@ -2589,22 +2662,25 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
             __syncthreads();
             edges(0, COMB_HALF, uo);
         }
-        if constexpr (kLoop) {
-            if (last) break;
+        if constexpr (kMode != kOne) {
+            if (kLoop && last) break;
             R *bu = (sub & 1) ? l->bu1 : l->bu0, *bz = (sub & 1) ? l->bz1 : l->bz0;
 #pragma unroll
             for (int s = 0; s < KS; ++s)
-                if (s * NT + tid < ne[0] && (ec[s] >> 31))
-                    __hip_atomic_store(bu + ge[s], u[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (tid < nc[0] && (cfl & 2u)) __hip_atomic_store(bz + gc, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (s * NT + tid < ne[0]) {
+                    if (kMode == kTask ? !last : (ec[s] >> 31) != 0) shared_store(bu + ge[s], u[s]);
+                    if (kMode == kTask && a.F) shared_store(a.F + ge[s], Fa[s]);
+                }
+            if (tid < nc[0] && (kMode == kTask ? !last : (cfl & 2u) != 0)) shared_store(bz + gc, z);
             // every wavefront's stores have reached the shared memory before
             // the substep is counted
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            const unsigned long long target = base_count + (unsigned long long)(sub + 1);
-            if (tid == 0)
-                __hip_atomic_store(l->done + (size_t)p * kDoneStride, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            wait_neighbours(l->done, T.nbr + rec[12], rec[13], target, l->err, l->spins);
+            const unsigned long long target = round->base + (unsigned long long)(sub + 1);
+            if (tid == 0) shared_store(l->done + (size_t)p * kDoneStride, target);
+            if (kMode == kTask) return;
+            if (tid < rec[13])
+                wait_count(l->done + (size_t)T.nbr[rec[12] + tid] * kDoneStride, target, l->err, l->spins);
             asm volatile("" ::: "memory");
             __syncthreads();
             // the halo: dry edges and land cells stay zero
@@ -2614,13 +2690,13 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
                 if (le < nEin) {
                     R v = R(0);
                     if (le < ne[0]) v = u[s < KS ? s : 0];
-                    else if ((ec[s] >> 30) & 1u) v = __hip_atomic_load(bu + ge[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    else if ((ec[s] >> 30) & 1u) v = shared_load(bu + ge[s]);
                     if (s < KS) u[s < KS ? s : 0] = v;
                     lds.XF[le].a = lhv[s] * v;
                 }
             }
             if (con && tid >= nc[0]) {
-                z = cwet ? __hip_atomic_load(bz + gc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : R(0);
+                z = cwet ? shared_load(bz + gc) : R(0);
                 lds.ZH[tid].z = z;
             }
         }
@@ -2628,7 +2704,7 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
     if constexpr (kLoop) {
         // after a wait that ran out the results are worthless: they come out
         // as NaN where nobody reads the error word
-        if (__hip_atomic_load(l->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 && tid < nc[0]) l->z_out[gc] = NAN;
+        if (shared_load(l->err) != 0 && tid < nc[0]) l->z_out[gc] = NAN;
     }
     if (a.F) {
 #pragma unroll
@@ -2637,12 +2713,14 @@ __device__ __forceinline__ void bt_fact_body(const BTTileArgs<R> &a, const BtRes
     }
 }
 
-// The resident loop of the patch that workgroup lb of the launch owns (patches
-// without ocean cells have no workgroup: their zeros are written by others).
+// The resident loop of the patch at place i of the order, in workgroup lb of n
+// of the launch (patches without ocean cells have no workgroup: their zeros are
+// written by others).
 template <typename R, int kScheme, int NT>
-__device__ __forceinline__ void bt_resident_body(const BtResident<R> &l, int lb, unsigned long long base) {
+__device__ __forceinline__ void bt_resident_body(const BtResident<R> &l, int at, const BtRound &round, int lb, int n) {
+    __shared__ FactLds<R, NT> lds;
     const DevBtTiles &T = l.a.t;
-    for (int i = T.nA + lb; i < T.nP; i += T.nA) {
+    for (int i = T.nA + at; i < T.nP; i += T.nA) {
         const int32_t *rec = T.patch + (size_t)T.order[i] * kBtRec;
         for (int le = threadIdx.x; le < rec[4]; le += NT) {
             int e = T.eid[rec[0] + le];
@@ -2655,7 +2733,47 @@ __device__ __forceinline__ void bt_resident_body(const BtResident<R> &l, int lb,
             l.z_out[l.cold ? l.cold[c] : c] = 0.0;
         }
     }
-    bt_fact_body<R, kScheme, true, NT>(l.a, &l, T.order[lb], base);
+    bt_fact_body<R, kScheme, kAll, NT>(lds, l.a, &l, T.order[at], &round, 0, lb, n);
+}
+
+// A loop that was called off, as tasks: (substep, patch) in order of substeps,
+// taken one after the other by however many workgroups run.  A task waits only
+// for tasks before it in that order (those of its neighbours and itself in the
+// substep before), which running workgroups hold or have finished, so it gets
+// on with a single workgroup on the device, and it gives the resident loop's
+// bits.  Exits at once after a loop that was admitted, the usual case: with
+// the admission it then costs about 6 us a loop (60 substeps on 64 x 64 cells:
+// 96 us; as a cooperative launch, which needs all of this too, 107).
+template <typename R, int kScheme, int NT>
+__device__ __forceinline__ void bt_task_body(const BtResident<R> *args, const int2 *table, int n, int most,
+                                             const BtRound &round) {
+    __shared__ FactLds<R, NT> lds;
+    __shared__ unsigned long long next;
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0 && tid <= kGroups) shared_store(round.words + tid * kDoneStride, 0ull);  // for the next launch
+    if (!called_off(round)) return;
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) next = shared_count(round.words + kTicket * kDoneStride);
+        __syncthreads();
+        const unsigned long long t = next;
+        if (t >= (unsigned long long)n * (unsigned)most) return;
+        const int sub = __builtin_amdgcn_readfirstlane((int)(t / (unsigned)n));
+        const int i = __builtin_amdgcn_readfirstlane((int)(t % (unsigned)n));
+        const BtResident<R> &l = args[table ? table[i].x : 0];
+        if (sub >= l.M) continue;
+        const DevBtTiles &T = l.a.t;
+        const int p = T.order[table ? table[i].y : i];
+        const int32_t *rec = T.patch + (size_t)p * kBtRec;
+        if (sub > 0) {
+            const unsigned long long target = round.base + (unsigned long long)sub;
+            const int q = tid < rec[13] ? T.nbr[rec[12] + tid] : tid == kFactNbrs ? p : -1;
+            if (q >= 0) wait_count(l.done + (size_t)q * kDoneStride, target, l.err, kBarrierSpins);
+            asm volatile("" ::: "memory");
+            __syncthreads();
+        }
+        bt_fact_body<R, kScheme, kTask, NT>(lds, l.a, &l, p, &round, sub);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -3231,7 +3349,7 @@ __global__ void __launch_bounds__(kBtThreads, kBtWavesPerSimd) bt_loop_kernel(BT
 // body takes 128 VGPRs (two workgroups of kBtThreads per CU), its FP32 body 88.
 // The loop comes in forms that hold one, two or (FP32) three such workgroups
 // per CU, and runs in the roomiest that holds the mesh: at two it keeps to 128
-// VGPRs and in FP64 spills 16 of them, at three to 80 and spills 18, which
+// VGPRs and in FP64 spills 14 of them, at three to 80 and spills 16, which
 // makes a substep 35% slower (0.39 -> 0.53 ms per step of 60 substeps on a 256
 // x 256 mesh) but still halves the time of one launch per substep (level-7
 // sphere: 0.88 ms per step of 90 substeps against 1.85).
@@ -3240,22 +3358,32 @@ constexpr int fact_waves() { return sizeof(R) == 8 ? 4 : 5; }
 template <typename R, int kScheme, int NT>
 __global__ void __launch_bounds__(NT, fact_waves<R>()) bt_fact_kernel(BTTileArgs<R> a) {
     const int p = xcd_block(a.t.nP);
-    if (p >= 0) bt_fact_body<R, kScheme, false, NT>(a, nullptr, p, 0);
+    __shared__ FactLds<R, NT> lds;
+    if (p >= 0) bt_fact_body<R, kScheme, kOne, NT>(lds, a, nullptr, p, nullptr);
 }
 template <typename R, int kScheme>
 __global__ void __launch_bounds__(kBtThreads, fact_waves<R>()) bt_fact_batch(BatchLaunch<BTTileArgs<R>> b) {
     int2 t;
-    if (batch_entry(b.table, b.blocks, t)) bt_fact_body<R, kScheme, false, kBtThreads>(b.args[t.x], nullptr, t.y, 0);
+    __shared__ FactLds<R, kBtThreads> lds;
+    if (batch_entry(b.table, b.blocks, t)) bt_fact_body<R, kScheme, kOne, kBtThreads>(lds, b.args[t.x], nullptr, t.y, nullptr);
 }
 template <typename R, int kScheme, int NT, int kW>
-__global__ void __launch_bounds__(NT, kW) bt_resident_kernel(BtResident<R> l, unsigned long long base) {
+__global__ void __launch_bounds__(NT, kW) bt_resident_kernel(BtResident<R> l, BtRound round) {
     const int lb = xcd_block(l.a.t.nA);
-    if (lb >= 0) bt_resident_body<R, kScheme, NT>(l, lb, base);
+    if (lb >= 0) bt_resident_body<R, kScheme, NT>(l, lb, round, lb, l.a.t.nA);
 }
 template <typename R, int kScheme, int kW>
-__global__ void __launch_bounds__(kBtThreads, kW) bt_resident_batch(BatchLaunch<BtResident<R>> b, unsigned long long base) {
+__global__ void __launch_bounds__(kBtThreads, kW) bt_resident_batch(BatchLaunch<BtResident<R>> b, BtRound round) {
     int2 t;
-    if (batch_entry(b.table, b.blocks, t)) bt_resident_body<R, kScheme, kBtThreads>(b.args[t.x], t.y, base);
+    if (batch_entry(b.table, b.blocks, t)) bt_resident_body<R, kScheme, kBtThreads>(b.args[t.x], t.y, round, xcd_block(b.blocks), b.blocks);
+}
+template <typename R, int kScheme, int NT>
+__global__ void __launch_bounds__(NT, fact_waves<R>()) bt_task_kernel(BtResident<R> l, BtRound round) {
+    bt_task_body<R, kScheme, NT>(&l, nullptr, l.a.t.nA, l.M, round);
+}
+template <typename R, int kScheme>
+__global__ void __launch_bounds__(kBtThreads, fact_waves<R>()) bt_task_batch(BatchLaunch<BtResident<R>> b, int most, BtRound round) {
+    bt_task_body<R, kScheme, kBtThreads>(b.args, b.table, b.blocks, most, round);
 }
 
 __global__ void __launch_bounds__(64) bt_loop_reset_kernel(unsigned *bar, unsigned *gen) {
@@ -3569,7 +3697,8 @@ void launch_bt_substep(const BTTileArgs<R> &a, int scheme, hipStream_t s) {
     }
 }
 
-// Workgroups of a cooperative kernel the device holds at once.
+// Workgroups of a kernel an empty device holds at once (0 if the device takes
+// no cooperative launch).
 static int coop_capacity(const void *fn, int threads, size_t lds) {
     int dev = 0, coop = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
@@ -3598,14 +3727,30 @@ hipError_t launch_bt_loop(const BTTileArgs<R> &a, const BtLoop<R> &l, int scheme
 }
 
 template <typename R>
-hipError_t launch_bt_resident(const BtResident<R> &l, int scheme, int tight, unsigned long long base, hipStream_t s) {
+hipError_t launch_bt_resident(const BtResident<R> &l, int scheme, int tight, const BtRound &round, hipStream_t s) {
     BtResident<R> ll = l;
-    const int nA = l.a.t.nA, nt = l.a.t.nt, blocks = (int)xcd_grid(nA).x;
-    void *args[] = {&ll, &base};
-    const void *fn = bt_resident_fn<R>(scheme, nt, tight);
-    // one patch waits for nobody: an ordinary launch
-    if (nA == 1) return hipLaunchKernel(fn, xcd_grid(1), dim3(nt), args, 0, s);
-    return hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(nt), args, 0, s);
+    BtRound r = round;
+    void *args[] = {&ll, &r};
+    return hipLaunchKernel(bt_resident_fn<R>(scheme, l.a.t.nt, tight), xcd_grid(l.a.t.nA), dim3(l.a.t.nt), args, 0, s);
+}
+
+// Workgroups of the task form: one per CU.
+constexpr int kTaskBlocks = kCus;
+
+template <typename R>
+hipError_t launch_bt_tasks(const BtResident<R> &l, int scheme, const BtRound &round, hipStream_t s) {
+    if (!round.words) return hipSuccess;
+    const dim3 grid(std::min(l.a.t.nA, kTaskBlocks)), block(l.a.t.nt);
+    BtRound r = round;
+    r.base += (unsigned long long)l.M;  // counts that the called-off launch cannot have stored
+    if (l.a.t.nt == kBtThreads) {
+        if (scheme == 3) bt_task_kernel<R, 3, kBtThreads><<<grid, block, 0, s>>>(l, r);
+        else bt_task_kernel<R, 2, kBtThreads><<<grid, block, 0, s>>>(l, r);
+    } else {
+        if (scheme == 3) bt_task_kernel<R, 3, kFactSmall><<<grid, block, 0, s>>>(l, r);
+        else bt_task_kernel<R, 2, kFactSmall><<<grid, block, 0, s>>>(l, r);
+    }
+    return hipGetLastError();
 }
 
 template <typename R>
@@ -3614,12 +3759,23 @@ int bt_resident_batch_capacity(int scheme, int tight) {
 }
 
 template <typename R>
-hipError_t launch_bt_resident_batch(const BatchLaunch<BtResident<R>> &b, int scheme, int tight,
-                                    unsigned long long base, hipStream_t s) {
+hipError_t launch_bt_resident_batch(const BatchLaunch<BtResident<R>> &b, int scheme, int tight, const BtRound &round,
+                                    hipStream_t s) {
     BatchLaunch<BtResident<R>> bb = b;
-    const int blocks = (int)xcd_grid(b.blocks).x;
-    void *args[] = {&bb, &base};
-    return hipLaunchCooperativeKernel(bt_resident_fn<R>(scheme, kBtThreads, tight, true), dim3(blocks), dim3(kBtThreads), args, 0, s);
+    BtRound r = round;
+    void *args[] = {&bb, &r};
+    return hipLaunchKernel(bt_resident_fn<R>(scheme, kBtThreads, tight, true), xcd_grid(b.blocks), dim3(kBtThreads), args, 0, s);
+}
+
+template <typename R>
+hipError_t launch_bt_tasks_batch(const BatchLaunch<BtResident<R>> &b, int most, int scheme, const BtRound &round, hipStream_t s) {
+    if (!round.words) return hipSuccess;
+    const dim3 grid(std::min(b.blocks, kTaskBlocks)), block(kBtThreads);
+    BtRound r = round;
+    r.base += (unsigned long long)most;
+    if (scheme == 3) bt_task_batch<R, 3><<<grid, block, 0, s>>>(b, most, r);
+    else bt_task_batch<R, 2><<<grid, block, 0, s>>>(b, most, r);
+    return hipGetLastError();
 }
 
 template <typename R>
@@ -3751,9 +3907,11 @@ void launch_convert_batch(const BatchLaunch<ConvArgs<Tin, Tout>> &b, const Geom 
     template void launch_bt_substep<R>(const BTTileArgs<R> &, int, hipStream_t);                           \
     template int bt_loop_capacity<R>(const DevBtTiles &, int, int);                                        \
     template hipError_t launch_bt_loop<R>(const BTTileArgs<R> &, const BtLoop<R> &, int, hipStream_t);       \
-    template hipError_t launch_bt_resident<R>(const BtResident<R> &, int, int, unsigned long long, hipStream_t); \
+    template hipError_t launch_bt_resident<R>(const BtResident<R> &, int, int, const BtRound &, hipStream_t); \
     template int bt_resident_batch_capacity<R>(int, int);                                                         \
-    template hipError_t launch_bt_resident_batch<R>(const BatchLaunch<BtResident<R>> &, int, int, unsigned long long, hipStream_t); \
+    template hipError_t launch_bt_resident_batch<R>(const BatchLaunch<BtResident<R>> &, int, int, const BtRound &, hipStream_t); \
+    template hipError_t launch_bt_tasks<R>(const BtResident<R> &, int, const BtRound &, hipStream_t);             \
+    template hipError_t launch_bt_tasks_batch<R>(const BatchLaunch<BtResident<R>> &, int, int, const BtRound &, hipStream_t); \
     template void launch_bt_substep_batch<R>(const BatchLaunch<BTTileArgs<R>> &, int, int, size_t, hipStream_t); \
     template void launch_bt_eval_batch<R>(const BatchLaunch<BTEvalArgs<R>> &, bool, const Geom &, hipStream_t); \
     template void launch_thickness_iso<R>(const THIsoArgs<R> &, const Geom &, hipStream_t);                \

@@ -388,7 +388,8 @@ int sse_debug_call_off_loops(sse_state *s, int enable);
  * for neighbouring patches).  For tests of that error path: with 1, the first
  * workgroup that has to wait gives up at once (whenever the launch has more
  * than one workgroup), the step call returns SSE_EDEVICE and the state must be
- * initialised again.  SSE_EINVAL for a NULL state. */
+ * initialised again; sse_barotropic_substep_noalloc does the loop again
+ * instead.  SSE_EINVAL for a NULL state. */
 int sse_debug_set_barrier_spins(sse_state *s, uint32_t spins);
 
 /* One thickness stage h_out = h_in + dt T^h(h_in, u + uA) (Section 3.4 revised
@@ -414,7 +415,10 @@ int sse_debug_thickness_stage(sse_state *s, const double *h_in, const double *u,
  * device array of 64 MiB per device, reserved when the library's code is
  * loaded on that device and held until the process ends; its address is
  * resolved by sse_state_create.  The call allocates nothing, enqueues its
- * kernels on the state's stream and returns without waiting.  All calls on
+ * kernels on the state's stream and returns without waiting.  A one-launch
+ * loop in which a wait ran out (see sse_state_set_bt_variant) is done again
+ * patch by patch, with the same results; should a wait of that run out too,
+ * all three outputs are NaN, and later calls are not affected.  All calls on
  * one device share that array, which keeps the last call's contents: calls
  * that overlap in time on one device race.  SSE_ENOMEM if the mesh needs more
  * than the array ((6 E + 4 C) x 8 bytes plus alignment); SSE_EINVAL for NULL

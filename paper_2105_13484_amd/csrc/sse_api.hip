@@ -58,9 +58,9 @@ struct RoundCount {
     unsigned long long counted = 0;   // at least every value the substep counters hold
     unsigned long long serial = 0;    // of the last launch
     // The next launch: wgs workgroups (one: no admission), at most M substeps.
-    BtRound next(unsigned long long *words, int wgs, int M, unsigned ticks) {
+    BtRound next(unsigned long long *words, int wgs, int M, unsigned ticks, bool redo = false) {
         std::lock_guard<std::mutex> g(mu);
-        const BtRound r{counted, wgs > 1 ? words : nullptr, ++serial, ticks};
+        const BtRound r{counted, wgs > 1 ? words : nullptr, ++serial, ticks, redo};
         counted += 2 * (unsigned long long)M;
         return r;
     }
@@ -590,7 +590,7 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
     base.w1 = scheme == SSE_SCHEME_SSPRK3 ? 1.0 / (6.0 * M) : 1.0 / (2.0 * M);
     base.w3 = scheme == SSE_SCHEME_SSPRK3 ? 2.0 / (3.0 * M) : 0.0;
     const BtResident<R> res{base, M, in_u, in_z, u1, uh, z1, zh, out_u, out_z, w.done, w.err,
-                            w.shared ? kBarrierSpins : s->barrier_spins, w.eold, w.cold};
+                            s->barrier_spins, w.eold, w.cold};
     const bool resident = s->rec ? (s->bt_variant == 2 || (s->bt_auto && s->bt_variant == 1)) && resident_able(tiles, m.C)
                                  : runs_resident(s, scheme);
     if (s->rec && resident) {
@@ -600,7 +600,8 @@ void bt_loop(sse_state *s, int scheme, int M, double dt, const double *in_u, con
         s->rec->seq++;
     } else if (resident) {
         ProfScope ps(s, SSE_PROF_BT_EVAL);
-        const BtRound round = w.count->next(w.words, tiles.nA, M, s->admit_ticks);
+        // (no host call reads the error word of the device's counters)
+        const BtRound round = w.count->next(w.words, tiles.nA, M, s->admit_ticks, w.shared);
         hipError_t e = launch_bt_resident<R>(res, scheme, s->bt_tight[scheme == SSE_SCHEME_SSPRK3 ? 1 : 0], round, s->stream);
         if (e == hipSuccess) e = launch_bt_tasks<R>(res, scheme, round, s->stream);
         if (e != hipSuccess) s->launch_error = e;

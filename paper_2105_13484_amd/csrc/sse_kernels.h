@@ -211,7 +211,7 @@ struct BtResident {
     R *bu0, *bu1, *bz0, *bz1; // outputs of the substeps before the last, alternating
     double *u_out, *z_out;    // the last substep's output
     unsigned long long *done; // [patch * kDoneStride] substeps finished, counted on from base
-    int *err;                 // set when a wait runs out
+    int *err;                 // set when a wait runs out (see ran_out)
     unsigned spins;           // polls before a wait runs out
     const int32_t *eold, *cold; // the fields' numbering of the mesh's edges and cells (null: the mesh's own)
 };
@@ -227,6 +227,7 @@ struct BtRound {
     unsigned long long serial;  // larger than that of every earlier launch with these words
     unsigned ticks;             // of the clock (10 ns) before a workgroup calls the loop off (0: at once, and
                                 // nobody admits it)
+    bool redo;                  // a loop in which a wait ran out is done again, rather than reported
 };
 constexpr int kGroups = 32, kVerdict = kGroups + 1, kTicket = kGroups + 2, kRoundWords = kGroups + 3;
 // How long a workgroup waits for the others to start: an idle device starts
@@ -373,7 +374,7 @@ template <typename R> int bt_loop_capacity(const DevBtTiles &t, int scheme, int 
 // pointers of a are unused); returns the launch's HIP error.
 template <typename R> hipError_t launch_bt_loop(const BTTileArgs<R> &a, const BtLoop<R> &l, int scheme, hipStream_t s);
 // The resident loop: one launch, and launch_bt_tasks behind it, which only
-// works if the loop was called off.  tight: which of the kResidentForms forms, those holding more workgroups per
+// works if the loop was called off or is to be done again.  tight: which of the kResidentForms forms, those holding more workgroups per
 // CU coming later (the capacity queries take the same number).
 constexpr int kResidentForms = 3;
 template <typename R>

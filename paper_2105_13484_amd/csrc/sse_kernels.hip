@@ -2342,18 +2342,24 @@ __device__ __forceinline__ void shared_store(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// What a launch leaves in an error word when a wait of it ran out: never zero,
+// and no other launch's.
+__device__ __forceinline__ int ran_out(const BtRound &r, bool task) {
+    return 0x40000000 | (int)((2 * r.serial + (task ? 1 : 0)) & 0x3fffffff);
+}
+
 // Waits until the counter *f has reached target.  The wait is bounded: if it
-// runs out, or another workgroup's did, the workgroup goes on without waiting
-// and *err makes the host refuse the results.
-__device__ __forceinline__ void wait_count(const unsigned long long *f, unsigned long long target, int *err,
+// runs out, or another workgroup's did, the workgroup goes on without waiting,
+// and *err = code says that the results are worthless.
+__device__ __forceinline__ void wait_count(const unsigned long long *f, unsigned long long target, int *err, int code,
                                            unsigned max_spins) {
     unsigned spins = 0;
     while (shared_load(f) < target) {
         if (++spins > max_spins) {
-            shared_store(err, 1);
+            shared_store(err, code);
             break;
         }
-        if ((spins & 255u) == 0 && shared_load(err) != 0) break;
+        if ((spins & 255u) == 0 && shared_load(err) == code) break;
     }
 }
 
@@ -2672,6 +2678,16 @@ __device__ __forceinline__ void bt_fact_body(FactLds<R, NT> &lds, const BTTileAr
                     if (kMode == kTask && a.F) shared_store(a.F + ge[s], Fa[s]);
                 }
             if (tid < nc[0] && (kMode == kTask ? !last : (cfl & 2u) != 0)) shared_store(bz + gc, z);
+            if (kMode == kTask && last && shared_load(l->err) == ran_out(*round, true)) {
+                // a wait of this or an earlier task ran out: all three results say so
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    if (s * NT + tid < ne[0]) {
+                        l->u_out[ge[s]] = NAN;
+                        if (a.F) shared_store(a.F + ge[s], (double)NAN);
+                    }
+                if (tid < nc[0]) l->z_out[gc] = NAN;
+            }
             // every wavefront's stores have reached the shared memory before
             // the substep is counted
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -2680,7 +2696,7 @@ __device__ __forceinline__ void bt_fact_body(FactLds<R, NT> &lds, const BTTileAr
             if (tid == 0) shared_store(l->done + (size_t)p * kDoneStride, target);
             if (kMode == kTask) return;
             if (tid < rec[13])
-                wait_count(l->done + (size_t)T.nbr[rec[12] + tid] * kDoneStride, target, l->err, l->spins);
+                wait_count(l->done + (size_t)T.nbr[rec[12] + tid] * kDoneStride, target, l->err, ran_out(*round, false), l->spins);
             asm volatile("" ::: "memory");
             __syncthreads();
             // the halo: dry edges and land cells stay zero
@@ -2704,7 +2720,7 @@ __device__ __forceinline__ void bt_fact_body(FactLds<R, NT> &lds, const BTTileAr
     if constexpr (kLoop) {
         // after a wait that ran out the results are worthless: they come out
         // as NaN where nobody reads the error word
-        if (shared_load(l->err) != 0 && tid < nc[0]) l->z_out[gc] = NAN;
+        if (shared_load(l->err) == ran_out(*round, false) && tid < nc[0]) l->z_out[gc] = NAN;
     }
     if (a.F) {
 #pragma unroll
@@ -2736,7 +2752,7 @@ __device__ __forceinline__ void bt_resident_body(const BtResident<R> &l, int at,
     bt_fact_body<R, kScheme, kAll, NT>(lds, l.a, &l, T.order[at], &round, 0, lb, n);
 }
 
-// A loop that was called off, as tasks: (substep, patch) in order of substeps,
+// A loop that was called off, or (redo) in which a wait ran out, as tasks: (substep, patch) in order of substeps,
 // taken one after the other by however many workgroups run.  A task waits only
 // for tasks before it in that order (those of its neighbours and itself in the
 // substep before), which running workgroups hold or have finished, so it gets
@@ -2751,7 +2767,7 @@ __device__ __forceinline__ void bt_task_body(const BtResident<R> *args, const in
     __shared__ unsigned long long next;
     const int tid = threadIdx.x;
     if (blockIdx.x == 0 && tid <= kGroups) shared_store(round.words + tid * kDoneStride, 0ull);  // for the next launch
-    if (!called_off(round)) return;
+    if (!called_off(round) && !(round.redo && shared_load(args->err) == ran_out(round, false))) return;
     for (;;) {
         __syncthreads();
         if (tid == 0) next = shared_count(round.words + kTicket * kDoneStride);
@@ -2768,7 +2784,7 @@ __device__ __forceinline__ void bt_task_body(const BtResident<R> *args, const in
         if (sub > 0) {
             const unsigned long long target = round.base + (unsigned long long)sub;
             const int q = tid < rec[13] ? T.nbr[rec[12] + tid] : tid == kFactNbrs ? p : -1;
-            if (q >= 0) wait_count(l.done + (size_t)q * kDoneStride, target, l.err, kBarrierSpins);
+            if (q >= 0) wait_count(l.done + (size_t)q * kDoneStride, target, l.err, ran_out(round, true), kBarrierSpins);
             asm volatile("" ::: "memory");
             __syncthreads();
         }

@@ -49,6 +49,31 @@ def test_called_off_loop_gives_the_same_bits(dev, name, scheme, M, precision):
             assert np.array_equal(a, c.cpu().numpy()), off
 
 
+@pytest.mark.parametrize("name", ["two_patches_hex20", "hex64", "land_sphere5"])
+@pytest.mark.parametrize("scheme,precision", [(2, 0), (3, 0), (3, 1)])
+def test_device_arrays_after_a_wait_that_ran_out(dev, name, scheme, precision):
+    """The loop on device arrays, whose error word no host call reads: a wait
+    that runs out (forced with a one-poll limit) costs a second pass and leaves
+    nothing behind for the next call of this or another state."""
+    import torch
+    case = cases.with_params(MESHES[name](), precision=precision)
+    inputs, dt = _inputs(case, 9), case.params.dt / case.params.substeps * 15
+    _, ref = dev.state_from_case(case)
+    assert ref.try_bt_variant(1)
+    want = ref.debug_barotropic_substep(scheme, 15, dt, *inputs)
+    _, st = dev.state_from_case(case)
+    _, other = dev.state_from_case(case)
+    assert st.try_bt_variant(2) and other.try_bt_variant(2), dev.last_error()
+    ins = [torch.from_numpy(a).cuda() for a in inputs]
+    for state, spins in ((st, 1), (st, 1), (other, 0), (st, 0), (st, 1), (other, 0)):
+        state.set_barrier_spins(spins)
+        outs = [torch.full_like(t, 5.0) for t in ins]
+        state.barotropic_substep_noalloc(scheme, 15, dt, *ins, *outs)
+        torch.cuda.synchronize()
+        for a, b in zip(want, outs):
+            assert np.array_equal(a, b.cpu().numpy()), spins
+
+
 @pytest.mark.parametrize("precision", [0, 1])
 def test_called_off_batch_equals_alone(dev, precision):
     import torch

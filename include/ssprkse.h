@@ -376,6 +376,12 @@ int sse_debug_barotropic_substep(sse_state *s, int32_t scheme, int32_t M, double
  * recorded into a batch; SSE_EDEVICE if the launch fails. */
 int sse_debug_edge_gathers(sse_state *s);
 
+/* enable != 0: read-outs of the state (sse_read_state, sse_read_tracer) take
+ * the way they take where no pinned host memory is to be had: through pageable
+ * memory, one array after the other.  For tests of that path.  SSE_EINVAL for a
+ * NULL state. */
+int sse_debug_plain_reads(sse_state *s, int enable);
+
 /* enable != 0: the device calls off every one-launch loop (variant 2) of the
  * state, as it does where other work keeps part of its workgroups out, so that
  * the launch behind it does the loop.  For tests of that path; in a batch the

@@ -304,6 +304,7 @@ struct sse_state {
     RoundCount bt_round;          // of the counters w.bt_done and the words behind them
     unsigned admit_ticks = kAdmitTicks;  // see BtRound::ticks
     unsigned barrier_spins = kBarrierSpins;  // polls before a barrier of the persistent loop gives up
+    bool pinned_reads = true;  // read-outs through pinned memory where it can be had
     size_t lds_max = 0;      // LDS bytes per workgroup on the state's device
     Recorder *rec = nullptr; // non-null while a batch records this state's step
     sse_batch *batch = nullptr;
@@ -1092,9 +1093,22 @@ constexpr size_t kReadSlots = 4;                   // pinned slots in flight
 constexpr size_t kReadThreaded = size_t(4) << 20;  // bytes per thread that places rows
 constexpr int kReadThreads = 8;
 
+// The same through pageable memory, one piece after the other.
+int read_plain(const std::vector<Piece> &pieces, bool identity, hipStream_t st) {
+    std::vector<char> tmp;
+    for (const Piece &p : pieces) {
+        tmp.resize(p.rows() * p.row * p.size);
+        SSE_HIP(hipMemcpyAsync(tmp.data(), p.dev, tmp.size(), hipMemcpyDeviceToHost, st));
+        SSE_HIP(hipStreamSynchronize(st));
+        place_rows(p, tmp.data(), 0, 0, p.rows(), identity);
+    }
+    return SSE_OK;
+}
+
 // Copies the pieces to the host behind the work enqueued on st; returns when
-// they are in place.
-int read_pieces(const std::vector<Piece> &pieces, bool identity, hipStream_t st) {
+// they are in place.  Without pinned memory (none to be had, or pinned false)
+// they take the plain way.
+int read_pieces(const std::vector<Piece> &pieces, bool identity, hipStream_t st, bool pinned) {
     struct Item {
         size_t piece, a, b, off;
     };
@@ -1133,8 +1147,8 @@ int read_pieces(const std::vector<Piece> &pieces, bool identity, hipStream_t st)
     }
     const size_t nfill = fills.size(), nslot = std::min(kReadSlots, nfill);
     for (size_t k = 0; k < nslot; ++k) {
-        slots.v[k].mem = PinnedPool::get().take();
-        if (!slots.v[k].mem) { set_error("no pinned host memory for the read-out"); return SSE_ENOMEM; }
+        slots.v[k].mem = pinned ? PinnedPool::get().take() : nullptr;
+        if (!slots.v[k].mem) return read_plain(pieces, identity, st);
         SSE_HIP(hipEventCreateWithFlags(&slots.v[k].ev, hipEventDisableTiming));
     }
     auto fill = [&](size_t f) -> hipError_t {
@@ -1708,6 +1722,12 @@ extern "C" int sse_debug_set_barrier_spins(sse_state *s, uint32_t spins) {
     return SSE_OK;
 }
 
+extern "C" int sse_debug_plain_reads(sse_state *s, int enable) {
+    if (!s) { set_error("NULL state"); return SSE_EINVAL; }
+    s->pinned_reads = !enable;
+    return SSE_OK;
+}
+
 extern "C" int sse_debug_call_off_loops(sse_state *s, int enable) {
     if (!s) { set_error("NULL state"); return SSE_EINVAL; }
     s->admit_ticks = enable ? 0 : kAdmitTicks;
@@ -1879,7 +1899,7 @@ extern "C" int sse_read_tracer(const sse_state *s, double *T) {
     if (!s->p.tracer || !s->tracer_set) { set_error("the state carries no temperature"); return SSE_ESTATE; }
     const sse_mesh *m = s->mesh;
     const size_t L = s->p.n_layers;
-    return guarded([&] { return read_pieces({{s->w.Tn, 8, T, &m->cell_old, L}}, m->identity, s->stream); });
+    return guarded([&] { return read_pieces({{s->w.Tn, 8, T, &m->cell_old, L}}, m->identity, s->stream, s->pinned_reads); });
 }
 
 extern "C" int sse_step_async(sse_state *s, int32_t n) {
@@ -1953,7 +1973,7 @@ extern "C" int sse_read_state(const sse_state *cs, double *h, double *u, double 
         if (h) v.push_back({w.Hs, 8, h, &m->cell_old, L});
         if (zeta) v.push_back({w.zeta_n, 8, zeta, &m->cell_old, 1});
         if (ubar) v.push_back({w.ubar_n, 8, ubar, &m->edge_old, 1});
-        return read_pieces(v, m->identity, cs->stream);
+        return read_pieces(v, m->identity, cs->stream, cs->pinned_reads);
     });
 }
 

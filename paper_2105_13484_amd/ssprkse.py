@@ -35,7 +35,8 @@ EXPORTED = (
     "sse_batch_set_geometry", "sse_batch_program_bytes", "sse_batch_compile", "sse_batch_launches_per_step",
     "sse_batch_use_graph", "sse_batch_step_async", "sse_batch_sync", "sse_batch_step", "sse_footprint_bytes",
     "sse_state_set_bt_variant", "sse_state_get_bt_variant", "sse_state_set_tracer", "sse_read_tracer",
-    "sse_barotropic_substep_noalloc", "sse_debug_set_barrier_spins", "sse_debug_call_off_loops", "sse_debug_edge_gathers",
+    "sse_barotropic_substep_noalloc", "sse_debug_set_barrier_spins", "sse_debug_call_off_loops", "sse_debug_plain_reads",
+    "sse_debug_edge_gathers",
 )
 
 # Edge-pass variants: -1 direct gathers, 0 / 1 / 2 LDS tiles of 8 / 16 / 32 edges.
@@ -110,6 +111,7 @@ def load():
         "sse_barotropic_substep_noalloc": (c_int, [P, c_int32, c_int32, c_double, P, P, P, P, P, P]),
         "sse_debug_set_barrier_spins": (c_int, [P, ctypes.c_uint32]),
         "sse_debug_call_off_loops": (c_int, [P, c_int]),
+        "sse_debug_plain_reads": (c_int, [P, c_int]),
         "sse_debug_edge_gathers": (c_int, [P]),
         "sse_state_set_edge_variant": (c_int, [P, c_int]),
         "sse_state_get_edge_variant": (c_int, [P, POINTER(c_int)]),
@@ -350,6 +352,10 @@ class DeviceState:
     def set_barrier_spins(self, spins: int = 0):
         """Polls before a wait of the one-launch barotropic loop gives up (0: default)."""
         _check(load().sse_debug_set_barrier_spins(self.handle, int(spins)))
+
+    def plain_reads(self, enable: bool = True):
+        """Have read-outs take the way they take without pinned host memory."""
+        _check(load().sse_debug_plain_reads(self.handle, int(bool(enable))))
 
     def call_off_loops(self, enable: bool = True):
         """Have the device call off the state's one-launch barotropic loops, so

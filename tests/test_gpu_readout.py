@@ -47,3 +47,22 @@ def test_read_returns_what_was_set(dev, name, make, precision, L):
         he = 0.5 * (h[c[:, 0]] + h[c[:, 1]])
         want = np.where(wet, (he * got["u"]).sum(1) / np.where(wet, he.sum(1), 1.0), 0.0)
         assert np.allclose(got["ubar"], want, rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("make", [lambda: cases.c1(n=40, L=7, steps=1),                                    # as numbered
+                                  lambda: cases.sphere_case(5, 41, 5, substeps=5, dt_btr=60.0)])           # renumbered
+@pytest.mark.parametrize("precision", [0, 1])
+def test_read_without_pinned_memory(dev, make, precision):
+    """Where no pinned host memory is to be had the state still reads, the same."""
+    case = cases.with_params(make(), precision=precision, tracer=1)
+    dm = dev.DeviceMesh(case.mesh, case.H, case.cell_mask)
+    st = dev.DeviceState(dm, case.params)
+    st.init(case.h, case.u, case.rho, case.h_ref)
+    st.set_tracer(np.where(case.cell_mask.astype(bool)[:, None], case.rho * 0.01, 0.0))
+    assert st.step(2) == 0
+    want, T = st.read(), st.read_tracer()
+    st.plain_reads()
+    got = st.read()
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
+    assert np.array_equal(st.read_tracer(), T)

@@ -1093,7 +1093,27 @@ constexpr size_t kReadSlots = 4;                   // pinned slots in flight
 constexpr size_t kReadThreaded = size_t(4) << 20;  // bytes per thread that places rows
 constexpr int kReadThreads = 8;
 
-// The same through pageable memory, one piece after the other.
+// Makes a stream's device the calling thread's current one for a while: events
+// are made on the current device and recorded on the stream only there.  (The
+// null stream is the current device's own.)
+class OnDeviceOf {
+  public:
+    explicit OnDeviceOf(hipStream_t st) {
+        int now = 0, want = 0;
+        if (!st || hipGetDevice(&now) != hipSuccess || hipStreamGetDevice(st, &want) != hipSuccess || now == want) return;
+        if (hipSetDevice(want) == hipSuccess) back_ = now;
+    }
+    ~OnDeviceOf() {
+        if (back_ >= 0) (void)hipSetDevice(back_);
+    }
+    OnDeviceOf(const OnDeviceOf &) = delete;
+    OnDeviceOf &operator=(const OnDeviceOf &) = delete;
+
+  private:
+    int back_ = -1;
+};
+
+// Copies the pieces to the host through pageable memory, one after the other.
 int read_plain(const std::vector<Piece> &pieces, bool identity, hipStream_t st) {
     std::vector<char> tmp;
     for (const Piece &p : pieces) {
@@ -1109,6 +1129,7 @@ int read_plain(const std::vector<Piece> &pieces, bool identity, hipStream_t st) 
 // they are in place.  Without pinned memory (none to be had, or pinned false)
 // they take the plain way.
 int read_pieces(const std::vector<Piece> &pieces, bool identity, hipStream_t st, bool pinned) {
+    const OnDeviceOf device(st);
     struct Item {
         size_t piece, a, b, off;
     };

@@ -66,3 +66,19 @@ def test_read_without_pinned_memory(dev, make, precision):
     for k in want:
         assert np.array_equal(got[k], want[k]), k
     assert np.array_equal(st.read_tracer(), T)
+
+
+def test_read_from_a_thread_on_another_device(dev):
+    """A state reads whatever device is current, and leaves it current."""
+    import torch
+    if torch.cuda.device_count() < 2:
+        pytest.skip("one device")
+    case = cases.c1(n=40, L=7, steps=1)
+    with torch.cuda.device(0):
+        _, st = dev.state_from_case(case, device="cuda:0", stream=torch.cuda.Stream())
+        want = st.read()
+    with torch.cuda.device(1):
+        got = st.read()
+        assert torch.cuda.current_device() == 1
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k

@@ -407,8 +407,10 @@ bool build_tiles(const sse_mesh_desc *d, int T, HostTiles &t) {
             for (int q = 0; q < 5; ++q) L[q] = (uint8_t)ids[q];
             const int n = d->n_edges_on_edge[e];
             for (int j = 0; j < kMaxEdges2; ++j) {
-                // padded stencil slots point at the edge itself (zero weight)
-                const int ep = j < n ? d->edges_on_edge[e * me2 + j] : e;
+                // padded stencil slots (beside a pentagon also inside the canonical
+                // order) point at the edge itself (zero weight)
+                const int slot_e = j < n ? d->edges_on_edge[(size_t)e * me2 + j] : -1;
+                const int ep = slot_e < 0 ? e : slot_e;
                 L[5 + j] = (uint8_t)slot(ue, ep);
                 L[15 + 2 * j] = (uint8_t)slot(uv, d->vertices_on_edge[2 * ep]);
                 L[16 + 2 * j] = (uint8_t)slot(uv, d->vertices_on_edge[2 * ep + 1]);

@@ -414,13 +414,8 @@ bool runs_resident(const sse_state *s, int scheme) {
     return s->bt_variant == 2 && s->mesh->bt.fact && !s->capturing && bt_loop_fits(s, scheme) && !stream_capturing(s->stream);
 }
 
-// The forward-Euler pass is split by cells: the mesh has the records, and B and
-// Z together hold the second cells' shares (V + C >= E on the closed surfaces
-// TRiSK meshes cover).
-bool split_pass(const sse_state *s) {
-    const sse_mesh *m = s->mesh;
-    return m->cell_rec && (s->p.hdiff == SSE_HDIFF_DEL4 || (size_t)m->V + m->C >= (size_t)m->E);
-}
+// The forward-Euler pass is split by cells: the mesh has the records.
+bool split_pass(const sse_state *s) { return s->mesh->cell_rec != nullptr; }
 
 template <typename R>
 const CellRec<R> *cell_rec_of(const sse_mesh *m);
@@ -1469,9 +1464,11 @@ extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t byt
         cursor += tiles_bytes(d, kTileSizes[q]);
     }
     // With factored weights no such list is ever needed: their space holds the
-    // cell records of the split pass.
+    // cell records of the split pass, which then always runs.  (It keeps the
+    // second cells' shares in B and Z together; V + C >= E on the closed
+    // surfaces TRiSK meshes cover.)
     std::vector<CellRec<double>> recs;
-    if (build_cell_recs(d, t, recs)) {
+    if ((size_t)d->n_vertices + d->n_cells >= (size_t)d->n_edges && build_cell_recs(d, t, recs)) {
         std::vector<CellRec<float>> recs_f(recs.size());
         for (size_t i = 0; i < recs.size(); ++i) recs_f[i] = narrow(recs[i]);
         const size_t n8 = recs.size() * sizeof(recs[0]), n4 = recs.size() * sizeof(recs_f[0]), at = m->tile_off[0];

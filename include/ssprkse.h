@@ -248,6 +248,9 @@ int sse_profile_read(sse_state *s, int32_t *launches, double *milliseconds);
  * in the Python package calls it. */
 int sse_state_set_edge_variant(sse_state *s, int variant);
 int sse_state_get_edge_variant(const sse_state *s, int *variant);
+/* *split = 1 where the state's pass is the split one, on which the edge variant
+ * has no effect, else 0. */
+int sse_state_get_pass_split(const sse_state *s, int *split);
 
 /* Kernel layout of the barotropic substep loops (Algorithms 3 and 4); the
  * results are bitwise the same.  0: one launch per forward-Euler evaluation
@@ -276,6 +279,10 @@ int sse_state_get_edge_variant(const sse_state *s, int *variant);
  * where they do not apply. */
 int sse_state_set_bt_variant(sse_state *s, int variant);
 int sse_state_get_bt_variant(const sse_state *s, int *variant);
+/* Back to the default variant, as if none had been set; *chosen = 1 where the
+ * caller has set one (which a batch keeps to), else 0. */
+int sse_state_reset_bt_variant(sse_state *s);
+int sse_state_get_bt_chosen(const sse_state *s, int *chosen);
 
 /* Device bytes one state of these parameters on this mesh needs in total:
  * the mesh image (sse_mesh_device_bytes, with its topology checks) plus the

@@ -398,6 +398,13 @@ bool bt_loop_fits(const sse_state *s, int scheme) {
 // came out even (0.99x a whole step).
 bool resident_pays(const DevBtTiles &t, int M) { return M >= (t.nA == 1 ? 2 : 10); }
 
+// The resident loop where an empty device holds all patches at once, else one
+// launch per substep.
+int default_bt_variant(const sse_state *s) {
+    if (!bt_tiles_fit(s)) return 0;
+    return s->mesh->bt.fact && bt_loop_fits(s, s->p.scheme) && resident_pays(s->mesh->bt, s->p.substeps) ? 2 : 1;
+}
+
 // The stream is being captured into a graph: its replays could not take the
 // numbers that every launch of the resident loop has of its own.
 bool stream_capturing(hipStream_t st) {
@@ -1702,10 +1709,7 @@ extern "C" int sse_state_create(const sse_mesh *m, const sse_params *p, void *de
             s->bt_tight[q] = tight;
             if (!s->mesh->bt.fact || bt_loop_fits(s, 2 + q)) break;
         }
-    // the resident loop where the device holds all patches at once, else one launch per substep
-    s->bt_variant = !bt_tiles_fit(s)                                                                           ? 0
-                    : s->mesh->bt.fact && bt_loop_fits(s, s->p.scheme) && resident_pays(s->mesh->bt, s->p.substeps) ? 2
-                                                                                                                     : 1;
+    s->bt_variant = default_bt_variant(s);
     if (hipMemsetAsync(s->w.bt_done, 0, done_bytes(m->C), s->stream) != hipSuccess ||
         hipMemsetAsync(s->w.flag, 0, kAlign, s->stream) != hipSuccess) {
         delete s;
@@ -1731,6 +1735,27 @@ extern "C" int sse_state_set_bt_variant(sse_state *s, int variant) {
     s->bt_auto = false;
     if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
     s->graph_exec = nullptr;
+    return SSE_OK;
+}
+
+extern "C" int sse_state_reset_bt_variant(sse_state *s) {
+    if (!s) { set_error("NULL state"); return SSE_EINVAL; }
+    s->bt_variant = default_bt_variant(s);
+    s->bt_auto = true;
+    if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
+    s->graph_exec = nullptr;
+    return SSE_OK;
+}
+
+extern "C" int sse_state_get_bt_chosen(const sse_state *s, int *chosen) {
+    if (!s || !chosen) { set_error("NULL argument"); return SSE_EINVAL; }
+    *chosen = s->bt_auto ? 0 : 1;
+    return SSE_OK;
+}
+
+extern "C" int sse_state_get_pass_split(const sse_state *s, int *split) {
+    if (!s || !split) { set_error("NULL argument"); return SSE_EINVAL; }
+    *split = split_pass(s) ? 1 : 0;
     return SSE_OK;
 }
 

@@ -36,6 +36,7 @@ EXPORTED = (
     "sse_batch_use_graph", "sse_batch_step_async", "sse_batch_sync", "sse_batch_step", "sse_footprint_bytes",
     "sse_state_set_bt_variant", "sse_state_get_bt_variant", "sse_state_set_tracer", "sse_read_tracer",
     "sse_barotropic_substep_noalloc", "sse_debug_set_barrier_spins", "sse_debug_call_off_loops", "sse_debug_plain_reads",
+    "sse_state_reset_bt_variant", "sse_state_get_bt_chosen", "sse_state_get_pass_split",
     "sse_debug_edge_gathers",
 )
 
@@ -119,6 +120,9 @@ def load():
         "sse_state_set_tracer": (c_int, [P, POINTER(c_double)]),
         "sse_read_tracer": (c_int, [P, POINTER(c_double)]),
         "sse_state_get_bt_variant": (c_int, [P, POINTER(c_int)]),
+        "sse_state_reset_bt_variant": (c_int, [P]),
+        "sse_state_get_bt_chosen": (c_int, [P, POINTER(c_int)]),
+        "sse_state_get_pass_split": (c_int, [P, POINTER(c_int)]),
         "sse_state_set_geometry": (c_int, [P, c_int, c_int]),
         "sse_state_use_graph": (c_int, [P, c_int]),
         "sse_batch_create": (c_int, [P, POINTER(P)]),
@@ -342,6 +346,24 @@ class DeviceState:
     @bt_variant.setter
     def bt_variant(self, variant: int):
         _check(load().sse_state_set_bt_variant(self.handle, int(variant)))
+
+    def reset_bt_variant(self):
+        """Back to the default barotropic loop, as if none had been set."""
+        _check(load().sse_state_reset_bt_variant(self.handle))
+
+    @property
+    def bt_chosen(self) -> bool:
+        """True where the caller has set the barotropic loop (a batch keeps to it)."""
+        v = c_int(0)
+        _check(load().sse_state_get_bt_chosen(self.handle, ctypes.byref(v)))
+        return bool(v.value)
+
+    @property
+    def pass_split(self) -> bool:
+        """True where the forward-Euler pass is split by cells (edge variants have no effect)."""
+        v = c_int(0)
+        _check(load().sse_state_get_pass_split(self.handle, ctypes.byref(v)))
+        return bool(v.value)
 
     def debug_edge_gathers(self):
         """Enqueue one gather-only edge pass on the state's stream (a

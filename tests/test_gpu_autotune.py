@@ -76,3 +76,37 @@ def test_tuned_batch_gives_solo_bits(dev, stream):
     for i, (_, st) in enumerate(keep):
         _same(st.read(), alone[i], f"member {i} after tuning {best}")
     b.close()
+
+
+def test_tuner_leaves_edge_variants_that_are_one_kernel(dev, stream):
+    """Where the pass is split the edge variant changes nothing: no trials of it."""
+    from paper_2105_13484_amd import autotune
+    from tests.test_gpu_split_pass import _with_general_weights
+    case = cases.c1(n=12, L=5, steps=2)
+    for c, split in ((case, True), (_with_general_weights(case), False)):
+        _, st = dev.state_from_case(c, stream=stream)
+        assert st.pass_split == split
+        tried = {cfg["edge_variant"] for cfg, _ in autotune.tune_state(st, steps=1)["trials"]}
+        assert tried == ({-1} if split else {-1, 0, 1, 2})
+
+
+@pytest.mark.parametrize("specs", [[(24, 5), (40, 12)],       # the first member alone takes a launch per substep
+                                   [(16, 12), (512, 12)]])    # the last one alone does not fit one launch per loop
+def test_tuned_batch_starts_from_the_members_own_loops(dev, stream, specs):
+    from paper_2105_13484_amd import autotune
+    b, keep = dev.Batch(stream=stream), []
+    for i, (n, M) in enumerate(specs):
+        keep.append(dev.state_from_case(cases.c1(n=n, L=1, substeps=M, member=i, steps=2, dt_btr=5.0), stream=stream))
+        b.add(keep[-1][1])
+    default, own = b.launches_per_step(), [st.bt_variant for _, st in keep]
+    assert len(set(own)) == 2
+    res = autotune.tune_batch(b, steps=1)
+    assert res["trials"][0][0]["bt_variant"] is None and res["default_ms"] is not None
+    if res["best"]["bt_variant"] is None:
+        assert [st.bt_variant for _, st in keep] == own and not any(st.bt_chosen for _, st in keep)
+        assert b.launches_per_step() == default
+    for _, st in keep:
+        st.reset_bt_variant()
+    b.set_geometry()
+    assert b.launches_per_step() == default
+    b.close()

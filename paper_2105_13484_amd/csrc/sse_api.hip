@@ -938,6 +938,16 @@ int check_params(const sse_params *p) {
     return SSE_OK;
 }
 
+// Clears the state's flags, substep counters and admission words, by kernels: a
+// caller may have the stream captured while it creates a state, and memset
+// nodes have gone wrong in graphs that are replayed.  (sse_state_init, which
+// cannot be captured, clears them again, so such a state does not depend on
+// the replay.)
+void clear_flags(sse_state *s) {
+    launch_zero(s->w.bt_done, done_bytes(s->mesh->C), s->stream);
+    launch_zero(s->w.flag, kAlign, s->stream);
+}
+
 int read_flag(sse_state *s) {
     int flag[33] = {};
     SSE_HIP(hipMemcpyAsync(flag, s->w.flag, sizeof(flag), hipMemcpyDeviceToHost, s->stream));
@@ -1710,10 +1720,10 @@ extern "C" int sse_state_create(const sse_mesh *m, const sse_params *p, void *de
             if (!s->mesh->bt.fact || bt_loop_fits(s, 2 + q)) break;
         }
     s->bt_variant = default_bt_variant(s);
-    if (hipMemsetAsync(s->w.bt_done, 0, done_bytes(m->C), s->stream) != hipSuccess ||
-        hipMemsetAsync(s->w.flag, 0, kAlign, s->stream) != hipSuccess) {
+    clear_flags(s);
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) {
         delete s;
-        return hip_fail(hipGetLastError(), "clearing the substep counters");
+        return hip_fail(e, "clearing the substep counters");
     }
     PinnedPool::get().state_made();
     *out = s;
@@ -1863,7 +1873,7 @@ extern "C" int sse_state_init(sse_state *s, const double *h, const double *u, co
     SSE_TRY(upload_real(s, w.U, um.data(), EL));
     SSE_HIP(hipMemcpyAsync(w.rho, ri.data(), CL * 8, hipMemcpyHostToDevice, s->stream));
     SSE_HIP(hipMemcpyAsync(w.frac, frac.data(), CL * 8, hipMemcpyHostToDevice, s->stream));
-    SSE_HIP(hipMemsetAsync(w.flag, 0, kAlign, s->stream));
+    clear_flags(s);
     launch_zeta_from_h(m->d, L, w.Hs, w.zeta_n, s->stream);
     if (s->rs == 4) {
         AssembleArgs<float> a{m->d, L, rp<float>(w.U), nullptr, w.Hs, rp<float>(w.U), w.ubar_n, w.flag};

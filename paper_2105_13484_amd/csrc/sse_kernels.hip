@@ -3859,6 +3859,14 @@ void launch_assemble_batch(const BatchLaunch<AssembleArgs<R>> &b, int nk, const 
     if (nk == 1) assemble_batch<1, R><<<xcd_grid(b.blocks), col_block(g), 0, s>>>(b);
     else assemble_batch<2, R><<<xcd_grid(b.blocks), col_block(g), 0, s>>>(b);
 }
+__global__ void __launch_bounds__(256) zero_kernel(unsigned long long *p, size_t n) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = 0ull;
+}
+void launch_zero(void *p, size_t bytes, hipStream_t s) {
+    const size_t n = bytes / 8;
+    zero_kernel<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(static_cast<unsigned long long *>(p), n);
+}
 void launch_zeta_from_h(const DevMesh &m, int L, const double *h, double *zeta, hipStream_t s) {
     const dim3 grid = xcd_grid((m.C + 3) / 4);
     if (L <= kWave) zeta_kernel<1><<<grid, 256, 0, s>>>(m, L, h, zeta);

@@ -133,3 +133,30 @@ def test_loops_that_fill_the_device_on_several_streams(dev):
         got, want = st.read(), alone.read()
         for k in want:
             assert np.array_equal(got[k], want[k]), k
+
+
+def test_state_created_while_its_stream_is_captured(dev):
+    """Creation is recorded, not run: the counters of its loops are clear once
+    the state is initialised, and replays between steps do no harm."""
+    import torch
+    case = cases.c1(n=48, L=3, substeps=12, dt_btr=5.0, steps=1)
+    stream = torch.cuda.Stream()
+    dm, ref = dev.state_from_case(case, stream=stream)
+    assert ref.bt_variant == 2 and ref.step(3) == 0
+    want = ref.read()
+    x, g = torch.zeros(1, device="cuda"), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        x += 1
+        st = dev.DeviceState(dm, case.params, stream=stream)
+    st.buf.fill_(255)                       # memory that held something else before
+    torch.cuda.synchronize()
+    st.init(case.h, case.u, case.rho, case.h_ref)
+    for _ in range(3):
+        assert st.step(1) == 0
+        with torch.cuda.stream(stream):
+            g.replay()
+        torch.cuda.synchronize()
+    got = st.read()
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
+    assert x.item() == 3

@@ -1004,6 +1004,23 @@ int download_real(const sse_state *s, double *dst, const void *src, size_t n) {
 //
 // The slots come from a bounded pool shared by all states of the process and
 // freed with the last of them.
+
+// Pinned memory is taken and freed in the relaxed capture mode: otherwise the
+// runtime refuses both while any thread captures a graph, and breaks the capture.
+class RelaxedCapture {
+  public:
+    RelaxedCapture() { set_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess; }
+    ~RelaxedCapture() {
+        if (set_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+    }
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+
+  private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+    bool set_ = false;
+};
+
 class PinnedPool {
   public:
     static constexpr size_t kSlot = size_t(4) << 20;
@@ -1021,6 +1038,7 @@ class PinnedPool {
                 return p;
             }
         }
+        const RelaxedCapture relaxed;
         void *p = nullptr;
         if (hipHostMalloc(&p, kSlot, hipHostMallocPortable) != hipSuccess) {
             (void)hipGetLastError();
@@ -1036,6 +1054,7 @@ class PinnedPool {
                 return;
             }
         }
+        const RelaxedCapture relaxed;
         (void)hipHostFree(p);
     }
     void state_made() {
@@ -1048,6 +1067,8 @@ class PinnedPool {
             std::lock_guard<std::mutex> g(mu_);
             if (--states_ == 0) drop.swap(free_);
         }
+        if (drop.empty()) return;
+        const RelaxedCapture relaxed;
         for (void *p : drop) (void)hipHostFree(p);
     }
 

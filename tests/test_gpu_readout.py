@@ -82,3 +82,41 @@ def test_read_from_a_thread_on_another_device(dev):
         assert torch.cuda.current_device() == 1
     for k in want:
         assert np.array_equal(got[k], want[k]), k
+
+
+_CLOSE_IN_CAPTURE = """
+import threading
+import torch
+from paper_2105_13484_amd import ssprkse as dev
+from synthetic import cases
+for other_thread in (False, True):
+    stream = torch.cuda.Stream()
+    dm, st = dev.state_from_case(cases.c1(n=24, L=7, steps=1), stream=stream)
+    st.read()
+    x, g = torch.zeros(1, device="cuda"), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=stream):
+        x += 1
+        if other_thread:
+            t = threading.Thread(target=st.close)
+            t.start()
+            t.join()
+        else:
+            st.close()
+        x += 1
+    g.replay()
+    torch.cuda.synchronize()
+    assert x.item() == 2
+print("captured")
+"""
+
+
+def test_last_state_closed_while_a_graph_is_captured(dev):
+    """The pool's pinned memory goes with the last state of a process (hence a
+    process of its own); a graph that is being captured meanwhile is not broken."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", _CLOSE_IN_CAPTURE], cwd=root, capture_output=True, text=True, timeout=100)
+    assert res.returncode == 0 and "captured" in res.stdout, res.stderr

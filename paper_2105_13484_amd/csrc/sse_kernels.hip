@@ -3750,8 +3750,11 @@ hipError_t launch_bt_resident(const BtResident<R> &l, int scheme, int tight, con
     return hipLaunchKernel(bt_resident_fn<R>(scheme, l.a.t.nt, tight), xcd_grid(l.a.t.nA), dim3(l.a.t.nt), args, 0, s);
 }
 
-// Workgroups of the task form: one per CU.
-constexpr int kTaskBlocks = kCus;
+// Workgroups of the task form: two per CU, what its FP64 body allows.  A mixed
+// level-7 and an FP64 level-6 globe of 60 layers stepped together on two
+// streams (the first's loops are called off) take 3.39 ms per step of both,
+// with one per CU 4.15, with one launch per substep 3.93; one after the other 3.21.
+constexpr int kTaskBlocks = 2 * kCus;
 
 template <typename R>
 hipError_t launch_bt_tasks(const BtResident<R> &l, int scheme, const BtRound &round, hipStream_t s) {

@@ -358,7 +358,15 @@ __device__ __forceinline__ double fmadd(double a, double b, double c) { return _
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // 1 / x (layer thicknesses, pivots): the hardware reciprocal refined to the
-// last place in three (FP64: five) instructions, where the division takes eleven.
+// last place in three (FP64: five) instructions, where the division takes
+// eleven (with divisions and the FP64 root in their places, in turn on one
+// device: level-7 globe of 60 layers, mixed, 84.3 against 80.5 ms; 256 x 256 x
+// 60 with the column solve 69.2 against 66.6; 512 x 512 x 60 1.002x).  Not
+// rounded correctly, but the results' errors against 64 bits come out the same
+// with either.  0 and infinity give NaN where a division gives infinity and 0:
+// a column with such a thickness has no finite value either way, since its sums
+// (of thickness, and of thickness x velocity) are then not finite or 0 x
+// infinity.
 template <typename R>
 __device__ __forceinline__ R recip(R x) {
     R r;
@@ -644,9 +652,9 @@ __device__ __forceinline__ void fe_cell_body(const FECellArgs<R> &a, int col) {
 // no vorticity array in between), and writes the cell's share of each edge's
 // horizontal terms.  The edge pass then reads the two shares.  On that mesh in
 // FP64 the cell, vertex and edge passes took 0.22 + 0.12 + 1.07 ms; the split
-// takes 0.55 (cells) + 0.59 (edges), in FP32 0.14 + 0.09 + 0.76 against 0.28 +
-// 0.52.  Both parts are now near the rate of HBM: 2.34 and 2.5 GB per launch
-// by the counters, 4.3 TB/s where a copy reaches 5.1.
+// takes 0.55 (cells) + 0.53 (edges), in FP32 0.14 + 0.09 + 0.76 against 0.29 +
+// 0.48.  Both parts are now near the rate of HBM: 2.45 and 2.41 GB per launch
+// by the counters, 4.4 and 4.5 TB/s where a copy reaches 5.1.
 //
 // With x = s l u / 2, t the same of ut, f / 2, q = zeta_e / 2 (zeta_e the mean
 // of the edge's two vertex vorticities) and y = f t + q x, edge a's share of
@@ -995,8 +1003,9 @@ struct EdgeOperands {
     double K1, K2, z1, z2, H1, H2, ubn;
 };
 
-// sqrt(x) rounded to R.  FP32: one Newton step from the hardware's reciprocal
-// root is good to about 1e-15 before the rounding.
+// sqrt(x) rounded to R (of the bottom layer's kinetic energy; NaN of an infinite
+// one).  FP32: one Newton step from the hardware's reciprocal root is good to
+// about 1e-15 before the rounding.
 template <typename R>
 __device__ __forceinline__ R sqrt_to(double x) {
     if constexpr (sizeof(R) == 4) {
@@ -1334,7 +1343,7 @@ __device__ __forceinline__ void fe_edge_body(const FEEdgeArgs<R> &a, int col) {
 // compiler, u^n, the shares and the cells' scalars came one after the other
 // behind the scans.  With the column sums two to a butterfly and the
 // reciprocals refined rather than divided, one call on 512 x 512 x 60 went
-// from 595 to 526 us (FP64, 4.8 TB/s) and 523 to 458 (FP32), on a level-7
+// from 595 to 526 us (FP64, 4.5 TB/s) and 523 to 458 (FP32), on a level-7
 // globe from 343 to 285 and 305 to 241.
 template <int NK, typename R, bool kAdd, int kVar>
 __device__ __forceinline__ void fe_edge_split_body(const FEEdgeArgs<R> &a, int e) {
@@ -2160,10 +2169,10 @@ __device__ __forceinline__ void bt_substep_body(const BTTileArgs<R> &a, int p) {
 // What the weight tables cost: they are streamed once per substep, 80 bytes
 // of FP64 weights and 20 of indices per region edge, 270 MB per substep of a
 // 262,144-cell mesh, and that traffic bounds the substep (46.9 us).  The
-// factored form reads six numbers per cell and three per edge instead, 145 MB
-// (39.9 us; its loads alone take 27, the rest is the barriers and evaluations
-// that two workgroups per CU do not hide), and small enough tables stay on
-// chip for a whole loop (the resident form).  It works on a cell's six edges
+// factored form reads six numbers per cell and three per edge instead, 160 MB
+// by the counters (36 us; its loads alone take 27, the rest is the barriers and
+// evaluations that two workgroups per CU do not hide), and small enough tables
+// stay on chip for a whole loop (the resident form).  It works on a cell's six edges
 // at once and leaves the edges two half sums to subtract.  One evaluation is two phases with a barrier between them:
 //   edges  finish the velocity of the previous stage, publish x = l u / 2 and
 //          the flux x (h_c1 + h_c2), keep zeta_c2 - zeta_c1;

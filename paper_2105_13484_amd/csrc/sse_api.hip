@@ -1002,8 +1002,11 @@ int download_real(const sse_state *s, double *dst, const void *src, size_t n) {
 // several threads take the rows of the previous slots to their places, widened
 // from FP32 on the way.
 //
-// The slots come from a bounded pool shared by all states of the process and
-// freed with the last of them.
+// The slots come from a bounded pool shared by all states of the process.  It
+// is freed with the last mesh and state, not with the last state: a program that
+// keeps a mesh and makes one state after the other on it would pay for the
+// slots with each (about 70 us a slot, on a 64 x 64 x 20 state 700 -> 630 us from
+// its creation through one read to its end).
 
 // Pinned memory is taken and freed in the relaxed capture mode: otherwise the
 // runtime refuses both while any thread captures a graph, and breaks the capture.
@@ -1049,7 +1052,7 @@ class PinnedPool {
     void give(void *p) {
         {
             std::lock_guard<std::mutex> g(mu_);
-            if (states_ > 0 && free_.size() < kKept) {
+            if (users_ > 0 && free_.size() < kKept) {
                 free_.push_back(p);
                 return;
             }
@@ -1057,15 +1060,16 @@ class PinnedPool {
         const RelaxedCapture relaxed;
         (void)hipHostFree(p);
     }
-    void state_made() {
+    // A mesh or state is made, is gone.
+    void add_user() {
         std::lock_guard<std::mutex> g(mu_);
-        ++states_;
+        ++users_;
     }
-    void state_gone() {
+    void drop_user() {
         std::vector<void *> drop;
         {
             std::lock_guard<std::mutex> g(mu_);
-            if (--states_ == 0) drop.swap(free_);
+            if (--users_ == 0) drop.swap(free_);
         }
         if (drop.empty()) return;
         const RelaxedCapture relaxed;
@@ -1076,7 +1080,7 @@ class PinnedPool {
     PinnedPool() { free_.reserve(kKept); }
     std::mutex mu_;
     std::vector<void *> free_;
-    long states_ = 0;
+    long users_ = 0;
 };
 
 // One array to read: rows of `row` values (FP64, or FP32 when size is 4), row
@@ -1614,6 +1618,7 @@ extern "C" int sse_mesh_create(const sse_mesh_desc *d, void *dev_buf, size_t byt
     dm.wpair_f = reinterpret_cast<const float *>(base + cursor);
     cursor += wpair_f_bytes(d);
     m->host_desc.reset(new PermutedDesc(std::move(pd)));
+    PinnedPool::get().add_user();
     *out = m;
     return SSE_OK;
 }
@@ -1675,7 +1680,9 @@ int ensure_tiles(const sse_mesh *cm, int q, hipStream_t s) {
 }  // namespace
 
 extern "C" int sse_mesh_destroy(sse_mesh *m) {
+    if (!m) return SSE_OK;
     delete m;
+    PinnedPool::get().drop_user();
     return SSE_OK;
 }
 
@@ -1746,7 +1753,7 @@ extern "C" int sse_state_create(const sse_mesh *m, const sse_params *p, void *de
         delete s;
         return hip_fail(e, "clearing the substep counters");
     }
-    PinnedPool::get().state_made();
+    PinnedPool::get().add_user();
     *out = s;
     return SSE_OK;
 }
@@ -1851,7 +1858,7 @@ extern "C" int sse_state_destroy(sse_state *s) {
     if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
     for (auto e : s->events) (void)hipEventDestroy(e);
     delete s;
-    PinnedPool::get().state_gone();
+    PinnedPool::get().drop_user();
     return SSE_OK;
 }
 

@@ -95,14 +95,19 @@ for other_thread in (False, True):
     st.read()
     x, g = torch.zeros(1, device="cuda"), torch.cuda.CUDAGraph()
     torch.cuda.synchronize()
+
+    def close():
+        st.close()
+        dm.close()
+
     with torch.cuda.graph(g, stream=stream):
         x += 1
         if other_thread:
-            t = threading.Thread(target=st.close)
+            t = threading.Thread(target=close)
             t.start()
             t.join()
         else:
-            st.close()
+            close()
         x += 1
     g.replay()
     torch.cuda.synchronize()
@@ -111,9 +116,9 @@ print("captured")
 """
 
 
-def test_last_state_closed_while_a_graph_is_captured(dev):
-    """The pool's pinned memory goes with the last state of a process (hence a
-    process of its own); a graph that is being captured meanwhile is not broken."""
+def test_last_state_and_mesh_closed_while_a_graph_is_captured(dev):
+    """The pool's pinned memory goes with the last state and mesh of a process
+    (hence a process of its own); a graph that is being captured meanwhile is not broken."""
     import os
     import subprocess
     import sys

@@ -1124,14 +1124,24 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
     if constexpr (kMix) {
         // Algorithm 2: u1 - dt D^u(u1) = ut1 + ubar with the drag speed of the
         // input, then ut1 = u1 - ubar (ubar: the input's barotropic velocity).
+        // Solved for the change y of ut1: (1 - dt D^u) y = dt D^u(ut1 + ubar),
+        // whose right-hand side takes the differences between layers, in which
+        // ubar drops out but for the drag.  The rounding of the solve is then
+        // relative to y, not to the whole velocity.  Relative error of u against
+        // 64 bits after 20 mixed steps on 64 x 64 cells, solved for u1 with rows
+        // as they are, with rows divided by their diagonal, and for y (6.1e-7
+        // without mixing): 30 layers 7.1e-7, 7.9e-7, 6.2e-7; 60 layers 2.0e-6,
+        // 1.1e-6, 6.3e-7.  Time within 1% (256 x 256 x 60, FP64 and FP32).
         const R ubin = (R)((a.ubar_add ? a.ubar_add[e] : 0.0) + (a.ubar_sub ? a.ubar_sub[e] : 0.0));
-        R Aup[NK], Adn[NK], lo[NK], di[NK], up[NK];
+        R Aup[NK], Adn[NK], lo[NK], di[NK], up[NK], xu[NK], xd[NK], y[NK];
 #pragma unroll
         for (int c = 0; c < NK; ++c) {
             const int k = lane + c * kWave;
             Aup[c] = (k >= 1 && k < L) ? nu_v / (R(0.5) * (hu[c] + he[c])) : R(0);
         }
         col_down1<NK, kDppFor<R>>(Aup, Adn);
+        col_up1<NK, kDppFor<R>>(x, xu);
+        col_down1<NK, kDppFor<R>>(x, xd);
 #pragma unroll
         for (int c = 0; c < NK; ++c) {
             const int k = lane + c * kWave;
@@ -1140,11 +1150,12 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
             lo[c] = in ? -dt * Aup[c] / he[c] : R(0);
             up[c] = (in && k < L - 1) ? -dt * Adn[c] / he[c] : R(0);
             di[c] = in ? R(1) + dt * (Aup[c] + Adn[c]) / he[c] : R(1);
-            x[c] = in ? x[c] + ubin : R(0);
+            y[c] = lo[c] * (x[c] - xu[c]) + up[c] * (x[c] - xd[c]);
+            if (k == L - 1) y[c] -= dt * Adn[c] / he[c] * (x[c] + ubin);
         }
-        col_tridiag_solve<NK, R>(L, lo, di, up, x);
+        col_tridiag_solve<NK, R>(L, lo, di, up, y);
 #pragma unroll
-        for (int c = 0; c < NK; ++c) x[c] = (lane + c * kWave < L) ? x[c] - ubin : R(0);
+        for (int c = 0; c < NK; ++c) x[c] = (lane + c * kWave < L) ? x[c] + y[c] : R(0);
     }
     const double ubn = a.Un ? (kSplit ? o.ubn : a.ubar_n[e]) : 0.0;
     R outv[NK];

@@ -1989,8 +1989,8 @@ extern "C" int sse_step_async(sse_state *s, int32_t n) {
     if (s->p.tracer && !s->tracer_set) { set_error("tracer runs need sse_state_set_tracer before stepping"); return SSE_ESTATE; }
     if (n < 0) { set_error("n must be >= 0"); return SSE_EINVAL; }
     // a step with the resident loop is few launches, each with numbers of its
-    // own, which a graph could not give it: it runs as it is (0.43 ms per 64 x
-    // 64 x 20 step against 0.48 as a graph with a launch per substep)
+    // own, which a graph could not give it: it runs as it is (0.29 ms per 64 x
+    // 64 x 20 FP64 step against 0.36 as a graph with a launch per substep)
     const bool resident = s->bt_variant == 2 && s->mesh->bt.fact && bt_loop_fits(s, s->p.scheme);
     if (s->use_graph && !(resident && !stream_capturing(s->stream))) {
         if (!s->graph_exec) {
@@ -2456,7 +2456,8 @@ int batch_record(sse_batch *b) {
         if (b->resident) break;
     }
     b->launches_per_step = 0;
-    for (const BatchOp &op : b->prog) b->launches_per_step += batch_runs(op, b->resident);
+    for (const BatchOp &op : b->prog)
+        if (batch_runs(op, b->resident)) b->launches_per_step += op.kind == Kind::BT_LOOP && op.blocks > 1 ? 2 : 1;
     b->recorded = true;
     return SSE_OK;
 }

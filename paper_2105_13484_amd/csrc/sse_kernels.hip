@@ -1131,7 +1131,7 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
         // 64 bits after 20 mixed steps on 64 x 64 cells, solved for u1 with rows
         // as they are, with rows divided by their diagonal, and for y (6.1e-7
         // without mixing): 30 layers 7.1e-7, 7.9e-7, 6.2e-7; 60 layers 2.0e-6,
-        // 1.1e-6, 6.3e-7.  Time within 1% (256 x 256 x 60, FP64 and FP32).
+        // 1.1e-6, 6.3e-7.  Times within 1% (256 x 256 x 60 FP64, level-6 globe x 100 mixed).
         const R ubin = (R)((a.ubar_add ? a.ubar_add[e] : 0.0) + (a.ubar_sub ? a.ubar_sub[e] : 0.0));
         R Aup[NK], Adn[NK], lo[NK], di[NK], up[NK], xu[NK], xd[NK], y[NK];
 #pragma unroll

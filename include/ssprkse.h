@@ -303,7 +303,9 @@ int sse_state_set_geometry(sse_state *s, int cols_per_block, int block_2d);
  * step on the state's stream into a HIP graph and every step then replays
  * it (one graph launch per step).  The stream must not be the null stream
  * (SSE_EINVAL).  Changing the geometry, the edge variant or this flag drops the
- * graph.  Per-class profiling does not apply to graph replays. */
+ * graph.  Per-class profiling does not apply to graph replays.  Steps whose
+ * barotropic loops take one launch each are enqueued as they are instead (see
+ * sse_state_set_bt_variant); results are the same. */
 int sse_state_use_graph(sse_state *s, int enable);
 
 /*
@@ -340,7 +342,8 @@ int sse_batch_compile(sse_batch *b, void *dev_buf, size_t bytes);
 /* Number of batched launches in one step of the compiled program. */
 int sse_batch_launches_per_step(sse_batch *b, int32_t *n);
 /* enable != 0: one step of the batch is captured into a HIP graph on first
- * use and replayed (non-null stream required). */
+ * use and replayed (non-null stream required), unless its barotropic loops
+ * take one launch each. */
 int sse_batch_use_graph(sse_batch *b, int enable);
 /* Enqueue n steps of every member / wait and check every member's
  * non-finite flag (SSE_ENONFINITE if any member blew up; sse_sync on a

@@ -1204,6 +1204,7 @@ int read_pieces(const std::vector<Piece> &pieces, bool identity, hipStream_t st,
         }
     }
     const size_t nfill = fills.size(), nslot = std::min(kReadSlots, nfill);
+    if (!nfill) SSE_HIP(hipStreamSynchronize(st));  // a call for no array waits all the same
     for (size_t k = 0; k < nslot; ++k) {
         slots.v[k].mem = pinned ? PinnedPool::get().take() : nullptr;
         if (!slots.v[k].mem) return read_plain(pieces, identity, st);

@@ -84,6 +84,16 @@ def test_read_from_a_thread_on_another_device(dev):
         assert np.array_equal(got[k], want[k]), k
 
 
+def test_read_of_nothing_waits_for_the_steps(dev):
+    import torch
+    case = cases.c1(n=128, L=40, steps=1)
+    stream = torch.cuda.Stream()
+    _, st = dev.state_from_case(case, stream=stream)
+    st.step_async(60)
+    assert dev.load().sse_read_state(st.handle, None, None, None, None) == dev.SSE_OK
+    assert stream.query()
+
+
 _CLOSE_IN_CAPTURE = """
 import threading
 import torch

@@ -943,9 +943,9 @@ int check_params(const sse_params *p) {
 // nodes have gone wrong in graphs that are replayed.  (sse_state_init, which
 // cannot be captured, clears them again, so such a state does not depend on
 // the replay.)
-void clear_flags(sse_state *s) {
-    launch_zero(s->w.bt_done, done_bytes(s->mesh->C), s->stream);
-    launch_zero(s->w.flag, kAlign, s->stream);
+hipError_t clear_flags(sse_state *s) {
+    const hipError_t e = launch_zero(s->w.bt_done, done_bytes(s->mesh->C), s->stream);
+    return e != hipSuccess ? e : launch_zero(s->w.flag, kAlign, s->stream);
 }
 
 int read_flag(sse_state *s) {
@@ -1749,8 +1749,7 @@ extern "C" int sse_state_create(const sse_mesh *m, const sse_params *p, void *de
             if (!s->mesh->bt.fact || bt_loop_fits(s, 2 + q)) break;
         }
     s->bt_variant = default_bt_variant(s);
-    clear_flags(s);
-    if (const hipError_t e = hipGetLastError(); e != hipSuccess) {
+    if (const hipError_t e = clear_flags(s); e != hipSuccess) {
         delete s;
         return hip_fail(e, "clearing the substep counters");
     }
@@ -1902,7 +1901,7 @@ extern "C" int sse_state_init(sse_state *s, const double *h, const double *u, co
     SSE_TRY(upload_real(s, w.U, um.data(), EL));
     SSE_HIP(hipMemcpyAsync(w.rho, ri.data(), CL * 8, hipMemcpyHostToDevice, s->stream));
     SSE_HIP(hipMemcpyAsync(w.frac, frac.data(), CL * 8, hipMemcpyHostToDevice, s->stream));
-    clear_flags(s);
+    SSE_HIP(clear_flags(s));
     launch_zeta_from_h(m->d, L, w.Hs, w.zeta_n, s->stream);
     if (s->rs == 4) {
         AssembleArgs<float> a{m->d, L, rp<float>(w.U), nullptr, w.Hs, rp<float>(w.U), w.ubar_n, w.flag};

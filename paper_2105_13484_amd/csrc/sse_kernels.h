@@ -392,8 +392,8 @@ template <typename Tin, typename Tout>
 void launch_convert(const ConvArgs<Tin, Tout> &a, const Geom &g, hipStream_t s);
 void launch_thickness(const THArgs &a, const Geom &g, hipStream_t s);
 void launch_recon(const ReconArgs &a, const Geom &g, hipStream_t s);
-// bytes: a multiple of 8
-void launch_zero(void *p, size_t bytes, hipStream_t s);
+// bytes: a multiple of 8; returns the launch's own error
+hipError_t launch_zero(void *p, size_t bytes, hipStream_t s);
 void launch_zeta_from_h(const DevMesh &m, int L, const double *h, double *zeta, hipStream_t s);
 // dst[i] = src[idx[i]] (scatter false) or dst[idx[i]] = src[i] (scatter true), i < n;
 // idx is a permutation of 0 .. n-1 and dst does not alias src.

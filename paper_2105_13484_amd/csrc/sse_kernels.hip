@@ -3779,17 +3779,16 @@ constexpr int kTaskBlocks = 2 * kCus;
 template <typename R>
 hipError_t launch_bt_tasks(const BtResident<R> &l, int scheme, const BtRound &round, hipStream_t s) {
     if (!round.words) return hipSuccess;
-    const dim3 grid(std::min(l.a.t.nA, kTaskBlocks)), block(l.a.t.nt);
+    const bool small = l.a.t.nt != kBtThreads;
+    const void *fn = scheme == 3 ? (small ? reinterpret_cast<const void *>(bt_task_kernel<R, 3, kFactSmall>)
+                                          : reinterpret_cast<const void *>(bt_task_kernel<R, 3, kBtThreads>))
+                                 : (small ? reinterpret_cast<const void *>(bt_task_kernel<R, 2, kFactSmall>)
+                                          : reinterpret_cast<const void *>(bt_task_kernel<R, 2, kBtThreads>));
+    BtResident<R> ll = l;
     BtRound r = round;
     r.base += (unsigned long long)l.M;  // counts that the called-off launch cannot have stored
-    if (l.a.t.nt == kBtThreads) {
-        if (scheme == 3) bt_task_kernel<R, 3, kBtThreads><<<grid, block, 0, s>>>(l, r);
-        else bt_task_kernel<R, 2, kBtThreads><<<grid, block, 0, s>>>(l, r);
-    } else {
-        if (scheme == 3) bt_task_kernel<R, 3, kFactSmall><<<grid, block, 0, s>>>(l, r);
-        else bt_task_kernel<R, 2, kFactSmall><<<grid, block, 0, s>>>(l, r);
-    }
-    return hipGetLastError();
+    void *args[] = {&ll, &r};
+    return hipLaunchKernel(fn, dim3(std::min(l.a.t.nA, kTaskBlocks)), dim3(l.a.t.nt), args, 0, s);
 }
 
 template <typename R>
@@ -3809,12 +3808,13 @@ hipError_t launch_bt_resident_batch(const BatchLaunch<BtResident<R>> &b, int sch
 template <typename R>
 hipError_t launch_bt_tasks_batch(const BatchLaunch<BtResident<R>> &b, int most, int scheme, const BtRound &round, hipStream_t s) {
     if (!round.words) return hipSuccess;
-    const dim3 grid(std::min(b.blocks, kTaskBlocks)), block(kBtThreads);
+    const void *fn = scheme == 3 ? reinterpret_cast<const void *>(bt_task_batch<R, 3>)
+                                 : reinterpret_cast<const void *>(bt_task_batch<R, 2>);
+    BatchLaunch<BtResident<R>> bb = b;
     BtRound r = round;
     r.base += (unsigned long long)most;
-    if (scheme == 3) bt_task_batch<R, 3><<<grid, block, 0, s>>>(b, most, r);
-    else bt_task_batch<R, 2><<<grid, block, 0, s>>>(b, most, r);
-    return hipGetLastError();
+    void *args[] = {&bb, &most, &r};
+    return hipLaunchKernel(fn, dim3(std::min(b.blocks, kTaskBlocks)), dim3(kBtThreads), args, 0, s);
 }
 
 template <typename R>
@@ -3886,9 +3886,10 @@ __global__ void __launch_bounds__(256) zero_kernel(unsigned long long *p, size_t
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) p[i] = 0ull;
 }
-void launch_zero(void *p, size_t bytes, hipStream_t s) {
-    const size_t n = bytes / 8;
-    zero_kernel<<<dim3((unsigned)((n + 255) / 256)), 256, 0, s>>>(static_cast<unsigned long long *>(p), n);
+hipError_t launch_zero(void *p, size_t bytes, hipStream_t s) {
+    size_t n = bytes / 8;
+    void *args[] = {&p, &n};
+    return hipLaunchKernel(reinterpret_cast<const void *>(zero_kernel), dim3((unsigned)((n + 255) / 256)), dim3(256), args, 0, s);
 }
 void launch_zeta_from_h(const DevMesh &m, int L, const double *h, double *zeta, hipStream_t s) {
     const dim3 grid = xcd_grid((m.C + 3) / 4);

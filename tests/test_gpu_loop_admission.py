@@ -160,3 +160,20 @@ def test_state_created_while_its_stream_is_captured(dev):
     for k in want:
         assert np.array_equal(got[k], want[k]), k
     assert x.item() == 3
+
+
+def test_state_created_after_an_error_of_the_callers(dev):
+    """An error that the caller's own runtime call left behind is not taken for
+    one of the state's creation."""
+    import ctypes
+    import torch
+    case = cases.c1(n=24, L=2, substeps=12, dt_btr=5.0, steps=1)
+    dm = dev.DeviceMesh(case.mesh, case.H, case.cell_mask)
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    value = ctypes.c_int()
+    assert hip.hipDeviceGetAttribute(ctypes.byref(value), -5, 0) != 0     # no such attribute
+    st = dev.DeviceState(dm, case.params)
+    hip.hipGetLastError()
+    st.init(case.h, case.u, case.rho, case.h_ref)
+    assert st.step(1) == 0
+    torch.cuda.synchronize()

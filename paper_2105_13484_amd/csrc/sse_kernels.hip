@@ -1148,10 +1148,11 @@ __device__ __forceinline__ void fe_edge_finish(const FEEdgeArgs<R> &a, int e, in
             if (k == L - 1) Adn[c] = c_drag * speed;
             const bool in = k < L;
             lo[c] = in ? -dt * Aup[c] / he[c] : R(0);
-            up[c] = (in && k < L - 1) ? -dt * Adn[c] / he[c] : R(0);
+            const R below = dt * Adn[c] / he[c];   // the drag's, at the bottom
+            up[c] = (in && k < L - 1) ? -below : R(0);
             di[c] = in ? R(1) + dt * (Aup[c] + Adn[c]) / he[c] : R(1);
             y[c] = lo[c] * (x[c] - xu[c]) + up[c] * (x[c] - xd[c]);
-            if (k == L - 1) y[c] -= dt * Adn[c] / he[c] * (x[c] + ubin);
+            if (k == L - 1) y[c] -= below * (x[c] + ubin);
         }
         col_tridiag_solve<NK, R>(L, lo, di, up, y);
 #pragma unroll

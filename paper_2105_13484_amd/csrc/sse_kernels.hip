@@ -2458,7 +2458,7 @@ struct FactLds {
     Pair<R> HS[kFactEdges * NT];
     ZetaDepth<R> ZH[NT];
     R ZS[kFactEdges * NT];
-    int go;   // the loop is admitted
+    int go;   // the workgroup goes on: the loop is admitted, or there are tasks
 };
 
 enum { kOne, kAll, kTask };
@@ -2640,8 +2640,8 @@ __device__ __forceinline__ void bt_fact_body(FactLds<R, NT> &lds, const BTTileAr
         if (tid == 0) {
             if (lb == 0) shared_store(round->words + kTicket * kDoneStride, 0ull);
             arrive(*round, lb, n);
+            lds.go = admitted(*round);
         }
-        if (tid == 0) lds.go = admitted(*round);
         __syncthreads();
         if (!__builtin_amdgcn_readfirstlane(lds.go)) return;
     }
@@ -2773,14 +2773,15 @@ __device__ __forceinline__ void bt_resident_body(const BtResident<R> &l, int at,
     bt_fact_body<R, kScheme, kAll, NT>(lds, l.a, &l, T.order[at], &round, 0, lb, n);
 }
 
-// A loop that was called off, or (redo) in which a wait ran out, as tasks: (substep, patch) in order of substeps,
-// taken one after the other by however many workgroups run.  A task waits only
-// for tasks before it in that order (those of its neighbours and itself in the
-// substep before), which running workgroups hold or have finished, so it gets
-// on with a single workgroup on the device, and it gives the resident loop's
-// bits.  Exits at once after a loop that was admitted, the usual case: with
-// the admission it then costs about 6 us a loop (60 substeps on 64 x 64 cells:
-// 96 us; as a cooperative launch, which needs all of this too, 107).
+// A loop that was called off, or (redo) in which a wait ran out, as tasks:
+// (substep, patch) in order of substeps, taken one after the other by however
+// many workgroups run.  A task waits only for tasks before it in that order
+// (those of its neighbours and itself in the substep before), which running
+// workgroups hold or have finished, so it gets on with a single workgroup on
+// the device, and it gives the resident loop's bits.  Exits at once after a
+// loop that was admitted, the usual case: with the admission it then costs
+// about 6 us a loop (60 substeps on 64 x 64 cells: 92 to 96 us; as a cooperative
+// launch, which needs all of this too, 107 without it).
 template <typename R, int kScheme, int NT>
 __device__ __forceinline__ void bt_task_body(const BtResident<R> *args, const int2 *table, int n, int most,
                                              const BtRound &round) {
@@ -2788,7 +2789,11 @@ __device__ __forceinline__ void bt_task_body(const BtResident<R> *args, const in
     __shared__ unsigned long long next;
     const int tid = threadIdx.x;
     if (blockIdx.x == 0 && tid <= kGroups) shared_store(round.words + tid * kDoneStride, 0ull);  // for the next launch
-    if (!called_off(round) && !(round.redo && shared_load(args->err) == ran_out(round, false))) return;
+    // one thread decides for the workgroup: a wait of another one's task may set
+    // the error word meanwhile
+    if (tid == 0) lds.go = called_off(round) || (round.redo && shared_load(args->err) == ran_out(round, false));
+    __syncthreads();
+    if (!__builtin_amdgcn_readfirstlane(lds.go)) return;
     for (;;) {
         __syncthreads();
         if (tid == 0) next = shared_count(round.words + kTicket * kDoneStride);
